@@ -60,6 +60,8 @@ struct NodeBits {
         x += 0x9e3779b9u;
         return x;
     }
+    // leaves out the bits of n values
+    __device__ void skip(uint32_t n) { x += n * 0x9e3779b9u; }
 };
 
 // Whether stores round (FP32 storage of FP64 arithmetic).

@@ -2,17 +2,23 @@
 // D3Q19 or D3Q27 lattice, the force of Eq. (7) with Guo's term, any segregation law, in
 // FP64, FP32, or FP32 storage with FP64 arithmetic (stochastic rounding on store).
 //
-// State: the recoloured populations before streaming, 3Q planes B[k][i][z][y][x] (pull
-// scheme: f_{i,k}(x) = B_{i,k}(x - e_i)), two buffers.  A step is one launch of the fused
-// march (k3_march): workgroups own x-y blocks of a z segment and march up z, keeping the
-// concentrations and the stress of three planes in LDS rings, so that the state is read
-// and written once per update (912 B for D3Q19 in FP64, 1296 B for D3Q27) and nothing else
-// goes through HBM.
+// State: factored per node, Q + 9 values before streaming: f_dag_i (Q), c_k (3), V_0 and V_1
+// (3 each; V_2 = -(V_0 + V_1)), from which Eq. (13) gives every recoloured population,
+// f_ddag_{i,k} = c_k f_dag_i + w_i V_k . e_i.  Two buffers (read one, write the other), 28
+// values per node for D3Q19 and 36 for D3Q27 in place of the 57 and 81 populations.  A freshly initialised lattice holds its three densities instead (FP64, at the
+// start of the first buffer); the first step reads those.
+//
+// A step is one launch of the fused march (k3_march): workgroups own x-y blocks of a z
+// segment and march up z.  What a node's densities need of its neighbours' factored values
+// splits by source plane, and so does the divergence of the stress, so that one plane of
+// c_k and V_k and one plane of stress in LDS serve the whole step; every sum that spans planes
+// is carried in registers from plane to plane.
 #include <algorithm>
 #include <cmath>
 #include <new>
 #include <vector>
 
+#include "lbm3_device.h"
 #include "lbm3_handle.h"
 #include "lbm3_rounding.h"
 
@@ -50,20 +56,59 @@ constexpr int PK3[3] = {0, 0, 1}, PL3[3] = {1, 2, 2};
 struct Geo3 {
     int nx, ny, nz;
     int64_t N;
+    int64_t zbytes;  // bytes of one z plane of a factored state
 };
 
-// Loads and stores at a byte offset from a plane's base: with at most 2^29 nodes the
-// offset of any node within a plane fits 32 bits, so the uniform base stays in scalar
-// registers and each lane holds a 32-bit offset.
+// Layout of a factored state.  The nodes of a z plane, in order y nx + x, form groups of 128
+// bytes' worth (16 FP64, 32 FP32); a group holds value after value, one 128-byte line each, and
+// groups and planes follow one another.  All values of a node are then at constant
+// distances, so a plane's Q loads share one base address in scalar registers and one offset per
+// lateral neighbour, with the value in the instruction (separate planes of values cost
+// four scalar and one 64-bit vector instruction per access to form the address).
+constexpr int kLine = 128;
 template <typename S>
-__device__ __forceinline__ S ld_plane(const S* __restrict__ base, uint32_t byte_off)
+constexpr int64_t group3()
 {
-    return *reinterpret_cast<const S*>(reinterpret_cast<const char*>(base) + byte_off);
+    return kLine / (int64_t)sizeof(S);
+}
+// byte offset of node n = y nx + x of a z plane
+template <typename S, int Q, typename Off>
+__host__ __device__ __forceinline__ Off node_off3(int64_t n)
+{
+    const int64_t G = group3<S>();
+    return (Off)(n / G) * (Off)((Q + 9) * kLine) + (Off)(n % G) * (Off)sizeof(S);
 }
 template <typename S>
-__device__ __forceinline__ void st_plane(S* __restrict__ base, uint32_t byte_off, S v)
+int64_t zbytes3(int nx, int ny, int q)
 {
-    *reinterpret_cast<S*>(reinterpret_cast<char*>(base) + byte_off) = v;
+    return ((int64_t)nx * ny + group3<S>() - 1) / group3<S>() * (q + 9) * kLine;
+}
+
+// Makes a lane's 32-bit offset a value the optimiser must take afresh from here: left alone, it
+// widens the offsets to 64 bits outside the march's loop, which doubles their registers and
+// replaces the scalar-base form of every access by a 64-bit vector address.
+__device__ __forceinline__ void refresh(uint32_t& o) { asm volatile("" : "+v"(o)); }
+__device__ __forceinline__ void refresh(uint64_t&) {}
+// Has x computed here: a sum that only the next iteration reads would be moved to the end of
+// this one, with everything that it is made of kept in registers till then.
+template <typename C>
+__device__ __forceinline__ void settle(C& x) { asm volatile("" : "+v"(x)); }
+
+// Value `v` (a constant) at byte offset `off` of the plane at the uniform address `base`.  The
+// instruction's offset is 13 bits with sign: the base is taken 16 values up.
+template <typename S, typename Off>
+__device__ __forceinline__ S ld_value(uint64_t base, Off off, int v)
+{
+    typedef const __attribute__((address_space(1))) char gchar;
+    typedef const __attribute__((address_space(1))) S gS;
+    return *(gS*)((gchar*)(base + 16 * kLine) + off + (v - 16) * kLine);
+}
+template <typename S, typename Off>
+__device__ __forceinline__ void st_value(uint64_t base, Off off, int v, S x)
+{
+    typedef __attribute__((address_space(1))) char gchar;
+    typedef __attribute__((address_space(1))) S gS;
+    *(gS*)((gchar*)(base + 16 * kLine) + off + (v - 16) * kLine) = x;
 }
 
 // The node indices of (x, y, z) and its neighbours: the wrapped coordinates at offsets -1,
@@ -83,18 +128,6 @@ struct Nb3 {
     // the node at offset (dx, dy, dz), each in -1..1
     __device__ __forceinline__ int64_t at(int dx, int dy, int dz) const { return zo[dz + 1] + yo[dy + 1] + xo[dx + 1]; }
 };
-
-// The post-streaming populations of node (x, y, z): f_{i,k} = B_{i,k}(x - e_i).
-template <typename S, int Q>
-__device__ __forceinline__ void pull3(const S* __restrict__ B, const Geo3& g, const Nb3& nb, double (&f)[3][Q])
-{
-#pragma unroll
-    for (int i = 0; i < Q; ++i) {
-        const int64_t src = nb.at(-L3X[i], -L3Y[i], -L3Z[i]);
-#pragma unroll
-        for (int k = 0; k < 3; ++k) f[k][i] = double(B[(int64_t)(k * Q + i) * g.N + src]);
-    }
-}
 
 // e_i . (a0, a1, a2) over the nonzero components of link i (each +-1), added in x, y, z
 // order.  A zero component would only add an exact zero, so this is the value of the full
@@ -119,145 +152,133 @@ __device__ __forceinline__ C edot(int i, C a0, C a1, C a2)
 
 // Eq. (12) over the (Q - 1)/2 pairs of opposite links: 3 sum_i w_i e_i [phi(x + e_i) -
 // phi(x - e_i)], phi(dx, dy, dz) the field at offset (dx, dy, dz) from the node (zero
-// components of e_i skipped, as in edot)
+// components of e_i skipped, as in edot); the differences of a weight class are added before
+// they are weighted
 template <typename C, int Q, typename Get>
 __device__ __forceinline__ void grad3(Get phi, C (&d)[3])
 {
-    d[0] = d[1] = d[2] = C(0);
+    C a[3], e[3] = {C(0), C(0), C(0)}, c[3] = {C(0), C(0), C(0)};
 #pragma unroll
     for (int i = 1; i < Q; i += 2) {
         const C df = phi(L3X[i], L3Y[i], L3Z[i]) - phi(-L3X[i], -L3Y[i], -L3Z[i]);
-        if (L3X[i] != 0) d[0] += w3<C, Q>(i) * C(L3X[i]) * df;
-        if (L3Y[i] != 0) d[1] += w3<C, Q>(i) * C(L3Y[i]) * df;
-        if (L3Z[i] != 0) d[2] += w3<C, Q>(i) * C(L3Z[i]) * df;
-    }
+        const int v[3] = {L3X[i], L3Y[i], L3Z[i]};
 #pragma unroll
-    for (int a = 0; a < 3; ++a) d[a] *= C(3);
+        for (int q = 0; q < 3; ++q) {
+            if (v[q] == 0) continue;
+            if (i < 7) a[q] = df;  // the links +x, +y, +z
+            else if (i < 19) e[q] += v[q] > 0 ? df : -df;
+            else c[q] += v[q] > 0 ? df : -df;
+        }
+    }
+    const C wa = C(3) * w3<C, Q>(1), we = C(3) * w3<C, Q>(7);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        d[q] = fma(wa, a[q], we * e[q]);
+        if constexpr (Q == 27) d[q] = fma(C(3) * w3<C, Q>(19), c[q], d[q]);
+    }
 }
 
-// Stress T = sum_pairs sigma C (|G|^2 I - G G^T)/|G| (xx, xy, xz, yy, yz, zz) and the pair
-// normals n_kl (n[3p + a]; zero at or below the guard) of a node from its concentrations
-// cc, their gradients gc and its densities rk (Eq. 7 with C_kl of Eq. 6).
+// Eq. (12)'s weighted differences of a vector field v over one plane of nodes, split by the
+// plane they serve: sum_i w_i e_i . v(x + e_i) at a node of the plane itself takes M from it, at
+// the node below (the plane is its e_z = +1 neighbour) P + Z, at the node above P - Z.
+// v(a, ox, oy): component a at lateral offset (ox, oy).  Opposite neighbours are subtracted
+// first, so data symmetric about the node give exact zeros.
+template <typename C, int Q, typename Get>
+__device__ __forceinline__ void plane_div(Get v, C& M, C& P, C& Z)
+{
+    const C wa = w3<C, Q>(1), we = w3<C, Q>(7);
+    const C axis = (v(0, 1, 0) - v(0, -1, 0)) + (v(1, 0, 1) - v(1, 0, -1));
+    const C diag = ((v(0, 1, 1) - v(0, -1, -1)) + (v(0, 1, -1) - v(0, -1, 1))) +
+                   ((v(1, 1, 1) - v(1, -1, -1)) + (v(1, -1, 1) - v(1, 1, -1)));
+    M = wa * axis + we * diag;
+    P = we * axis;
+    Z = wa * v(2, 0, 0) + we * ((v(2, 1, 0) + v(2, -1, 0)) + (v(2, 0, 1) + v(2, 0, -1)));
+    if constexpr (Q == 27) {
+        const C wc = w3<C, Q>(19);
+        P += wc * diag;
+        Z += wc * ((v(2, 1, 1) + v(2, -1, -1)) + (v(2, 1, -1) + v(2, -1, 1)));
+    }
+}
+
+// Stress T = sum_pairs sigma C (|G|^2 I - G G^T)/|G| (xx, xy, xz, yy, yz, zz; Eq. 7 with C_kl
+// of Eq. 6) and the recolouring vectors V_0, V_1 (V[3k + a]; Eq. 13 with the segregation law,
+// V_k = sum_{l != k} beta_kl (rho_k rho_l / rho) n_kl) of a node from its concentrations cc,
+// their gradients gc and its densities rk.
 template <typename C>
 __device__ __forceinline__ void stress3(const C (&gc)[3][3], const C (&cc)[3], const C (&rk)[3], const KParams& kp,
-                                         C (&t)[6], C (&nrm)[9])
+                                        C (&t)[6], C (&V)[6])
 {
+    C ct = C(kp.ct_coef) * (cc[0] * cc[1] * cc[2]);
+    ct = ct < C(1) ? ct : C(1);
+    C an[3][3];  // a_p n_p with a_p = beta_p rho_k rho_l / rho
 #pragma unroll
     for (int q = 0; q < 6; ++q) t[q] = C(0);
 #pragma unroll
     for (int p = 0; p < 3; ++p) {
         const int k = PK3[p], l = PL3[p];
-        C G[3];
+        C G[3], xx, yy, zz;
+        {
+            // the products of G nearly cancel where a fluid is present only as a trace; their
+            // rounding is left as the plain evaluation's
+#pragma clang fp contract(off)
 #pragma unroll
-        for (int a = 0; a < 3; ++a) G[a] = cc[l] * gc[k][a] - cc[k] * gc[l][a];
-        const C g2 = G[0] * G[0] + G[1] * G[1] + G[2] * G[2];
-        C n[3] = {C(0), C(0), C(0)};
-        if (g2 > C(kp.guard * kp.guard)) {
-            const C m = sqrt(g2), im = C(1) / m;
-#pragma unroll
-            for (int a = 0; a < 3; ++a) n[a] = G[a] * im;
-            C cf = C(kp.cfac[p]) * (rk[k] * rk[l]);
-            cf = cf < C(1) ? cf : C(1);
-            const C s = C(kp.sigma[p]) * cf * m;  // sigma C |G| (I - n n)
-            t[0] += s * (C(1) - n[0] * n[0]);
-            t[1] -= s * (n[0] * n[1]);
-            t[2] -= s * (n[0] * n[2]);
-            t[3] += s * (C(1) - n[1] * n[1]);
-            t[4] -= s * (n[1] * n[2]);
-            t[5] += s * (C(1) - n[2] * n[2]);
+            for (int a = 0; a < 3; ++a) G[a] = cc[l] * gc[k][a] - cc[k] * gc[l][a];
+            xx = G[0] * G[0];
+            yy = G[1] * G[1];
+            zz = G[2] * G[2];
         }
+        const C g2 = (xx + yy) + zz;
+        // zero at or below the guard (selected, not branched over: the three pairs' chains of
+        // dependent operations then run beside one another)
+        const C inv = g2 > C(kp.guard * kp.guard) ? rsqrt_nr(g2) : C(0);
+        const C a_p = fma(ct, C(kp.beta0 * kp.g[p]), C(kp.beta0)) * (rk[k] * cc[l]) * inv;
 #pragma unroll
-        for (int a = 0; a < 3; ++a) nrm[3 * p + a] = n[a];
+        for (int a = 0; a < 3; ++a) an[p][a] = a_p * G[a];
+        C cf = C(kp.cfac[p]) * (rk[k] * rk[l]);
+        cf = cf < C(1) ? cf : C(1);
+        const C s = C(kp.sigma[p]) * cf * inv;
+        t[0] += s * (yy + zz);
+        t[1] -= s * (G[0] * G[1]);
+        t[2] -= s * (G[0] * G[2]);
+        t[3] += s * (xx + zz);
+        t[4] -= s * (G[1] * G[2]);
+        t[5] += s * (xx + yy);
     }
-}
-
-// F_b = sum_a d_a T_ab with the symmetric T stored as (xx, xy, xz, yy, yz, zz);
-// T(q, dx, dy, dz) is component q at offset (dx, dy, dz) from the node
-template <typename C, int Q, typename Get>
-__device__ __forceinline__ void force3(Get T, C (&F)[3])
-{
-    constexpr int QI[3][3] = {{0, 1, 2}, {1, 3, 4}, {2, 4, 5}};
-    F[0] = F[1] = F[2] = C(0);
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-        for (int b = 0; b < 3; ++b) {
-            C d[3];
-            grad3<C, Q>([&](int dx, int dy, int dz) { return T(QI[a][b], dx, dy, dz); }, d);
-            F[b] += d[a];
-        }
-}
-
-// Collision with Guo's term (Eqs. 1-3, 8-11) and recolouring (Eq. 13 with the segregation
-// law) of one node from its densities rk, totals ft, force F and pair normals nrm.  With OBS
-// the node's observables go to acc (rho_k, rho u, kinetic energy, |u|); otherwise every
-// recoloured population is handed to put(k, i, value).
-template <typename C, int Q, bool OBS, typename Put>
-__device__ __forceinline__ void collide3(const C (&rk)[3], const C (&ft)[Q], const C (&F)[3], const C (&nrm)[9],
-                                         const KParams& kp, double (&acc)[8], Put put)
-{
-    const C rho = rk[0] + rk[1] + rk[2], irho = C(1) / rho;
-    C m[3] = {C(0), C(0), C(0)};
-#pragma unroll
-    for (int i = 0; i < Q; ++i) {
-        if (L3X[i] != 0) m[0] += L3X[i] > 0 ? ft[i] : -ft[i];
-        if (L3Y[i] != 0) m[1] += L3Y[i] > 0 ? ft[i] : -ft[i];
-        if (L3Z[i] != 0) m[2] += L3Z[i] > 0 ? ft[i] : -ft[i];
-    }
-    C u[3], uu = C(0), uF = C(0);
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        u[a] = (m[a] + C(0.5) * F[a]) * irho;
-        uu += u[a] * u[a];
-        uF += u[a] * F[a];
+        V[a] = an[0][a] + an[1][a];
+        V[3 + a] = an[2][a] - an[0][a];
     }
-    if constexpr (OBS) {
+}
+
+// Collision with Guo's term (Eqs. 1-3, 8-11) of one node from its density rho, 1/tau, totals
+// ft, force F and half-force velocity u: f_dag_i = (1 - 1/tau) f_i + (1/tau) f_eq_i + Phi_i, each
+// handed to put(i, value).  With A = (1/tau) w rho and B = w (1 - 1/(2 tau)) of a weight class,
+//   (1/tau) f_eq_i + Phi_i = [A (1 - 1.5 u.u) - 3 B u.F] + e.u e.(4.5 A u + 9 B F) + e.(3 A u + 3 B F):
+// the first two terms are the same for a link and its opposite, the last changes sign, so
+// each pair of links forms them once (half the operations of forming them per link).
+template <typename C, int Q, typename Put>
+__device__ __forceinline__ void collide3(C rho, C itau, const C (&ft)[Q], const C (&F)[3], const C (&u)[3], Put put)
+{
+    const C uu = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
+    const C uF = u[0] * F[0] + u[1] * F[1] + u[2] * F[2];
+    const C omi = C(1) - itau, c0 = C(1) - C(1.5) * uu, tr = itau * rho, pref = C(1) - C(0.5) * itau;
+    const C s0 = tr * c0 - C(3) * pref * uF;  // the symmetric part without the weight and e
+    C X[3], Y[3];  // 4.5 A u + 9 B F and 3 A u + 3 B F without the weight
 #pragma unroll
-        for (int k = 0; k < 3; ++k) acc[k] += double(rk[k]);
+    for (int a = 0; a < 3; ++a) {
+        const C tu = tr * u[a], pF = pref * F[a];
+        X[a] = C(4.5) * tu + C(9) * pF;
+        Y[a] = C(3) * tu + C(3) * pF;
+    }
+    put(0, fma(ft[0], omi, w3<C, Q>(0) * s0));
 #pragma unroll
-        for (int a = 0; a < 3; ++a) acc[3 + a] += double(rho * u[a]);
-        acc[6] += 0.5 * double(rho) * double(uu);
-        const double um = sqrt(double(uu));
-        acc[7] = (um > acc[7] || um != um) ? um : acc[7];
-    } else {
-        // tau = 3 nu + 1/2 with rho / nu = sum_k rho_k / nu_k (Eqs. 10-11)
-        const C rho_over_nu = rk[0] * C(kp.inv_nu[0]) + rk[1] * C(kp.inv_nu[1]) + rk[2] * C(kp.inv_nu[2]);
-        const C itau = rho_over_nu / (C(3) * rho + C(0.5) * rho_over_nu);
-        const C pref = C(1) - C(0.5) * itau;
-        // C_t and beta_kl of the segregation law; a_p = beta_p rho_k rho_l / rho
-        C ct = C(kp.ct_coef) * rk[0] * rk[1] * rk[2] * (irho * irho * irho);
-        ct = ct < C(1) ? ct : C(1);
-        C ap[3];
-#pragma unroll
-        for (int p = 0; p < 3; ++p) ap[p] = C(kp.beta0) * (C(1) + ct * C(kp.g[p])) * (rk[PK3[p]] * rk[PL3[p]]) * irho;
-        // V_k = sum_{l != k} a_kl n_kl (n_lk = -n_kl)
-        C V[3][3];
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            const C n0 = nrm[0 + a], n1 = nrm[3 + a], n2 = nrm[6 + a];
-            V[0][a] = ap[0] * n0 + ap[1] * n1;
-            V[1][a] = ap[2] * n2 - ap[0] * n0;
-            V[2][a] = -(ap[1] * n1 + ap[2] * n2);
-        }
-        C ck[3];
-#pragma unroll
-        for (int k = 0; k < 3; ++k) ck[k] = rk[k] * irho;
-#pragma unroll
-        for (int i = 0; i < Q; ++i) {
-            const C eu = edot<C>(i, u[0], u[1], u[2]);
-            const C eF = edot<C>(i, F[0], F[1], F[2]);
-            const C feq = w3<C, Q>(i) * rho * (C(1) + C(3) * eu + C(4.5) * eu * eu - C(1.5) * uu);
-            const C phi = w3<C, Q>(i) * pref * (C(3) * (eF - uF) + C(9) * eu * eF);
-            const C fd = ft[i] - (ft[i] - feq) * itau + phi;
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                const C ve = edot<C>(i, V[k][0], V[k][1], V[k][2]);
-                put(k, i, ck[k] * fd + w3<C, Q>(i) * ve);
-            }
-            // each link's values leave before the next link's are formed (otherwise the
-            // compiler holds all 3Q for one burst of stores)
-            __builtin_amdgcn_sched_barrier(0);
-        }
+    for (int i = 1; i < Q; i += 2) {
+        const C w = w3<C, Q>(i);
+        const C E = w * fma(edot<C>(i, u[0], u[1], u[2]), edot<C>(i, X[0], X[1], X[2]), s0);
+        const C O = w * edot<C>(i, Y[0], Y[1], Y[2]);
+        put(i, fma(ft[i], omi, E + O));
+        put(i + 1, fma(ft[i + 1], omi, E - O));
     }
 }
 
@@ -265,203 +286,391 @@ __device__ __forceinline__ void collide3(const C (&rk)[3], const C (&ft)[Q], con
 // A workgroup of TX x TY lanes (lane t at tile column t % TX, tile row t / TX; each wave is
 // two whole tile rows) owns the output nodes [x0, x0 + cols) x [y0, y0 + rows) x
 // [z0, z0 + depth), cols <= TX - 4 and rows <= TY - 4.  Lane (tx, ty) sits on node column
-// (x0 - 2 + tx, y0 - 2 + ty) (wrapped) and marches up z.  Iteration j, three phases closed
-// by barriers:
-//   stage 1, plane z0 - 2 + j: pull the 3Q populations; totals f_i and densities rho_k (kept
-//            in registers for two more iterations); c_k into the LDS ring (all lanes with
-//            tx <= cols + 3, ty <= rows + 3);
-//   stage 2, plane z0 - 3 + j: grad c_k (Eq. 12) from the ring, stress and pair normals
-//            (lanes 1 .. cols + 2, 1 .. rows + 2); T into its LDS ring;
-//   stage 3, plane z0 - 4 + j: F = div T from the ring, collision and recolouring of the
-//            owned nodes (lanes 2 .. cols + 1, 2 .. rows + 1), stored.
-// Rings hold three planes, by plane mod 3.  depth + 4 iterations output the tile's planes.
-// The arithmetic of every node is that of stress3 / force3 / collide3 in a fixed order, so
-// the result does not depend on the tile shape.  With FP64 arithmetic (CB = 8 bytes) D3Q19
-// takes tiles of 32 x 16 lanes and D3Q27 32 x 14, so that its larger park still leaves the
-// rings within the 160 KB of LDS (145 KB against 148 KB).  FP32 arithmetic halves every
-// ring and fits three waves per SIMD in registers (146 and 157 VGPRs), so it takes 32 x 24
-// lanes (118 and 136 KB): 560 owned columns of 768 lanes instead of 336 of 512, measured
-// 7% (D3Q19) and 28% (D3Q27) faster at 128^3.
-template <int Q, int CB = 8>
+// (x0 - 2 + tx, y0 - 2 + ty) (wrapped).  Iteration j takes source plane s = z0 - 3 + j, two
+// barriers:
+//   stage 1 (lanes 0 .. cols + 3, 0 .. rows + 3): the densities that plane s streams to planes
+//            s + 1, s and s - 1, from the lane's f_dag_i(x - e_i) of plane s and the c_k, V_k of
+//            plane s in LDS (one ring of nodes beyond the lanes').  sum_i w_i e_i . V_k(x - e_i)
+//            is plane_div of V_k.  Plane s - 1 is then complete; its c_k go into a
+//            three-plane LDS ring.
+//   stage 2, plane s - 2 (lanes 1 .. cols + 2, 1 .. rows + 2): grad c_k (Eq. 12) from the ring,
+//            stress into LDS, V_k; the owned nodes store c_k, V_0, V_1.  The next plane's c_k,
+//            V_k go into LDS.
+//   stage 3, plane s - 3 (lanes 2 .. cols + 1, 2 .. rows + 1): the stress of plane s - 2 completes
+//            F = div T; collision, f_dag_i stored.
+// The totals f_i = f_dag_i(x - e_i) (the c_k sum to 1 and the V_k to 0) are not kept from
+// stage 1 to stage 3, three iterations later: each owning lane loads its Q values again.
+// Holding them would take 4 Q values per node (three planes waiting and one arriving), more
+// than registers and LDS have.
+// Global loads are issued up to an iteration before their use, into the registers that their
+// previous values have just left (D3Q27 in FP64 issues its f_dag_i after stage 2, so that
+// they are not in registers beside stage 2's: no spills, 735 -> 462 us at 128^3).
+// What bounds it: memory.  At 128^3 in FP64 a D3Q19 step moves 1.7 GB between L2 and the
+// memory behind it (2.5x the state's bytes in reads: the second read of the f_dag_i and the
+// halos that L2 misses; 1.03x in writes) at 4.8 TB/s; without its loads and stores it would
+// take 135 us.  Small boxes are bound by the loads' path through L1 (about 15 cycles per wave
+// instruction, whatever its width).  Measured against the march over 3 Q stored populations
+// that it replaced, us per step at 128^3 (FP64 / FP32 storage / FP32): D3Q19 723 / 413 / 338 ->
+// 345 / 242 / 198, D3Q27 1159 / 667 / 460 -> 462 / 301 / 263; D3Q19 48^3 FP64 63 -> 39.
+// Non-temporal stores made it 1-15% slower, non-temporal loads 10-20%.
+// The arithmetic of every node has a fixed order, so the result does not depend on the tile
+// shape.  With FP64 arithmetic two waves per SIMD fit in registers (512 lanes of 256), with
+// FP32 three (768 lanes): 336 owned columns of 512 lanes, 560 of 768.
+template <int CB>
 struct Tile3Shape {
-    static constexpr int TX = 32, TY = CB == 4 ? 24 : (Q == 27 ? 14 : 16), T = TX * TY;
-    static constexpr int TS = (TX - 2) * (TY - 2);  // lanes that form the stress
-    static constexpr int TP = (TX - 4) * (TY - 4);  // lanes that own output nodes
+    static constexpr int TX = 32, TY = CB == 4 ? 24 : 16, T = TX * TY;
+    static constexpr int CX = TX + 2, CY = TY + 2;  // nodes whose c_k, V_k the lanes need
+    static constexpr int SX = TX - 2, SY = TY - 2;  // lanes that form the stress
 };
 
 struct Tile3 {
     int32_t x0, y0, z0, cols, rows, depth;
 };
 
-template <typename C, int Q>
+// What a state holds: the three initial densities (FP64) or the factored values.
+enum class In3 : int { Rho = 0, Fac = 1 };
+
+template <typename C>
 struct alignas(16) March3Lds {
-    using Sh = Tile3Shape<Q, sizeof(C)>;
-    C c[3][3][Sh::T];    // c_k by plane mod 3
-    C T[3][6][Sh::TS];   // stress by plane mod 3, on the stress lanes
-    C park[Q][Sh::TP];   // per owning lane: the totals f_i of one waiting plane
+    using Sh = Tile3Shape<sizeof(C)>;
+    C cv[9][Sh::CX * Sh::CY];  // c_k, V_0, V_1 of the source plane
+    C c[3][3][Sh::T];          // c_k of the new densities, by plane mod 3
+    C T[6][Sh::SX * Sh::SY];   // stress of one plane
 };
 
-// S: storage type, C: compute type.  With FP32 storage of FP64 arithmetic each stored value
-// is rounded stochastically with the random bits of its node (key: node index and the
-// step's salt), in store order.
-template <typename S, typename C, bool OBS, int Q>
-__global__ __launch_bounds__((Tile3Shape<Q, sizeof(C)>::T)) __attribute__((amdgpu_waves_per_eu(sizeof(C) == 4 ? 3 : 2))) void k3_march(
-    const S* __restrict__ B, Geo3 g, KParams kp, const Tile3* __restrict__ tiles, S* __restrict__ Bout,
-    double* __restrict__ partials, uint32_t salt)
+// The population of link i of a fluid at rest with density r, as a state in S holds it.
+template <typename S, typename C, int Q>
+__device__ __forceinline__ C rest_pop(int i, double r)
 {
-    using Sh = Tile3Shape<Q, sizeof(C)>;
-    constexpr int kTX = Sh::TX, kT3 = Sh::T;
-    static_assert(kT3 % 64 == 0 && (2 * kTX) % 64 == 0, "each wave is whole tile rows");
-    static_assert(sizeof(double) * 8 * (kT3 / 64) <= sizeof(C) * 3 * 3 * kT3, "c ring too small for the reduction");
-    __shared__ March3Lds<C, Q> L;
-    const Tile3 tl = tiles[blockIdx.x];
-    const int t = threadIdx.x, tx = t % kTX, ty = t / kTX;
-    const bool in1 = tx <= tl.cols + 3 && ty <= tl.rows + 3;
+    return C(S(w3<C, Q>(i) * C(r)));
+}
+
+template <typename S, typename C, bool OBS, int Q, In3 IN, typename Off>
+__device__ __forceinline__ void march3(const void* __restrict__ in, const Geo3& g, const KParams& kp, const Tile3& tl,
+                                       S* __restrict__ out, March3Lds<C>& L, double (&acc)[8],
+                                       double* __restrict__ rho_out, uint32_t salt)
+{
+    using Sh = Tile3Shape<sizeof(C)>;
+    constexpr int TX = Sh::TX, T3 = Sh::T;
+    const int t = threadIdx.x, tx = t % TX, ty = t / TX;
     const bool in2 = tx >= 1 && tx <= tl.cols + 2 && ty >= 1 && ty <= tl.rows + 2;
     const bool in3 = tx >= 2 && tx <= tl.cols + 1 && ty >= 2 && ty <= tl.rows + 1;
-    auto wrap = [](int a, int n) {
-        const int r = a % n;
-        return r < 0 ? r + n : r;
+    const int x = wrapi(tl.x0 - 2 + tx, g.nx), y = wrapi(tl.y0 - 2 + ty, g.ny);
+    // byte offsets within a plane of the nine lateral neighbours, by 3 (e_y + 1) + e_x + 1
+    Off lo[9];
+    {
+        const int xs[3] = {x == 0 ? g.nx - 1 : x - 1, x, x == g.nx - 1 ? 0 : x + 1};
+        const int64_t ys[3] = {(int64_t)(y == 0 ? g.ny - 1 : y - 1) * g.nx, (int64_t)y * g.nx,
+                               (int64_t)(y == g.ny - 1 ? 0 : y + 1) * g.nx};
+#pragma unroll
+        for (int a = 0; a < 9; ++a) lo[a] = node_off3<S, Q, Off>(ys[a / 3] + xs[a % 3]);
+    }
+    const int64_t pl = (int64_t)g.nx * g.ny, np = (int64_t)y * g.nx + x;  // nodes of a plane; the lane's
+    const uint64_t fin = (uint64_t)in, fout = (uint64_t)out;
+    const double* rin = (const double*)in;
+    // the lane's node in cv, c and T.  Each is one LDS address, kept opaque: an access reaches 64
+    // KiB past its address register, and the optimiser would otherwise take all three from
+    // the start of LDS and hold the sums that do not fit in registers.
+    typedef __attribute__((address_space(3))) C lds_t;
+    lds_t* cv = (lds_t*)&L.cv[0][0] + ((ty + 1) * Sh::CX + tx + 1);
+    lds_t* cl = (lds_t*)&L.c[0][0][0] + t;
+    lds_t* Tl = (lds_t*)&L.T[0][0] + ((ty - 1) * Sh::SX + (tx - 1));
+    constexpr int NC = Sh::CX * Sh::CY, NT = Sh::SX * Sh::SY;
+    settle(cv);
+    settle(cl);
+    settle(Tl);
+    // The ring of nodes around the lanes': one more c_k, V_k for most lanes of the first and the
+    // last wave, which own no node (their tile rows are the halo's) and so load no totals.
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const bool edge = wave == 0 || wave == T3 / 64 - 1;
+    const int e = wave == 0 ? t : t - (T3 - 128);  // 0 .. 127
+    int ru, rw;
+    if (e < Sh::CX) ru = e, rw = 0;
+    else if (e < 2 * Sh::CX) ru = e - Sh::CX, rw = Sh::CY - 1;
+    else if (e < 2 * Sh::CX + Sh::TY) ru = 0, rw = e - 2 * Sh::CX + 1;
+    else ru = Sh::CX - 1, rw = e - 2 * Sh::CX - Sh::TY + 1;
+    const bool ring = edge && e < 2 * Sh::CX + 2 * Sh::TY && ru <= tl.cols + 5 && rw <= tl.rows + 5;
+    Off ro = node_off3<S, Q, Off>((int64_t)wrapi(tl.y0 - 3 + rw, g.ny) * g.nx + wrapi(tl.x0 - 3 + ru, g.nx));
+    lds_t* cr = (lds_t*)&L.cv[0][0] + rw * Sh::CX + ru;
+    settle(cr);
+
+    // f_dag_i(x - e_i) of source plane s for every link; the c_k, V_k of source plane s; the
+    // f_dag_i(x - e_i) that meet at plane p
+    auto at = [](int i) { return 3 * (1 - L3Y[i]) + 1 - L3X[i]; };
+    auto load_f = [&](int s, S (&v)[Q]) {
+        const uint64_t base = fin + s * g.zbytes;
+#pragma unroll
+        for (int a = 0; a < 9; ++a) refresh(lo[a]);
+#pragma unroll
+        for (int i = 0; i < Q; ++i) v[i] = ld_value<S>(base, lo[at(i)], i);
     };
-    const int x = wrap(tl.x0 - 2 + tx, g.nx), y = wrap(tl.y0 - 2 + ty, g.ny);
-    // node offsets within a plane at x - 1, x, x + 1 and y - 1, y, y + 1 (N <= 2^29: the
-    // byte offset of any node fits 32 bits)
-    const uint32_t xo[3] = {(uint32_t)(x == 0 ? g.nx - 1 : x - 1), (uint32_t)x, (uint32_t)(x == g.nx - 1 ? 0 : x + 1)};
-    const uint32_t yo[3] = {(uint32_t)((y == 0 ? g.ny - 1 : y - 1) * g.nx), (uint32_t)(y * g.nx),
-                            (uint32_t)((y == g.ny - 1 ? 0 : y + 1) * g.nx)};
-    const uint32_t pl = (uint32_t)(g.nx * g.ny);
-    // the stress lanes' and owning lanes' slots in the T ring and the park
-    const int tS = (ty - 1) * (kTX - 2) + (tx - 1), tP = (ty - 2) * (kTX - 4) + (tx - 2);
-    double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    // The totals f_i of a plane are used two iterations after its pull, so three planes of
-    // them are live at a time: the one pulled (ft), the one waiting (W) and the one collided
-    // (ftB).  Each owning lane parks one of them in LDS (its own slots, so no barrier is
-    // involved): after the pull, ftB comes out of the park, W goes in, and ft becomes W.
-    C W[Q], rA[3], rB[3], nB[9];
+    auto load_cv = [&](int s, Off& o, auto& v) {
+        const uint64_t base = fin + s * g.zbytes;
+        refresh(o);
 #pragma unroll
-    for (int i = 0; i < Q; ++i) W[i] = C(0);
-#pragma unroll
-    for (int k = 0; k < 3; ++k) rA[k] = rB[k] = C(1);
-#pragma unroll
-    for (int q = 0; q < 9; ++q) nB[q] = C(0);
-    const int J = tl.depth + 4;
-    // plane offset of plane z (wrapped) and the source of link i for planes zo[]
-    auto zoff = [&](int z) { return (uint32_t)wrap(z, g.nz) * pl; };
-    auto src = [&](const uint32_t (&zo)[3], int i) {
-        return (zo[1 - L3Z[i]] + yo[1 - L3Y[i]] + xo[1 - L3X[i]]) * (uint32_t)sizeof(S);
+        for (int i = 0; i < 9; ++i) v[i] = ld_value<S>(base, o, Q + i);
     };
+    auto load_t = [&](int p, S (&v)[Q]) {
+        const uint64_t base[3] = {fin + (p == 0 ? g.nz - 1 : p - 1) * g.zbytes, fin + p * g.zbytes,
+                                  fin + (p == g.nz - 1 ? 0 : p + 1) * g.zbytes};
+#pragma unroll
+        for (int a = 0; a < 9; ++a) refresh(lo[a]);
+#pragma unroll
+        for (int i = 0; i < Q; ++i) v[i] = ld_value<S>(base[1 - L3Z[i]], lo[at(i)], i);
+    };
+
+    C D0[3], D1[3], rA[3], rB[3], Fa[3], Fb[3], rhoA = C(1), itauA = C(1);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        D0[k] = D1[k] = Fa[k] = Fb[k] = C(0);
+        rA[k] = rB[k] = C(1);
+    }
+    // vf: f_dag_i; vc: c_k, V_k of the lane's node; vx: totals, or in the two edge waves the c_k,
+    // V_k of the ring
+    S vf[Q], vx[Q], vc[9];
+#pragma unroll
+    for (int i = 0; i < Q; ++i) vf[i] = vx[i] = S(0);
+
+    constexpr bool kLate = Q == 27 && sizeof(S) == 8;
+    const int J = tl.depth + 6;
+    RowCursor sf(tl.z0 - 3, g.nz), sc(tl.z0 - 3, g.nz);  // the next plane of load_f and of load_cv
+    RowCursor dst(tl.z0 - 4, g.nz), tot(tl.z0, g.nz);    // plane s - 1; the next plane of load_t
+    auto publish = [&]() {
+#pragma unroll
+        for (int i = 0; i < 9; ++i) cv[i * NC] = C(vc[i]);
+        if (ring) {
+#pragma unroll
+            for (int i = 0; i < 9; ++i) cr[i * NC] = C(vx[i]);
+        }
+    };
+    auto load_next_cv = [&]() {
+        const int s = sc.next();
+        load_cv(s, lo[4], vc);
+        if (edge) load_cv(s, ro, vx);
+    };
+    if constexpr (IN == In3::Fac) {
+        load_next_cv();
+        load_f(sf.next(), vf);
+        publish();
+        load_next_cv();
+    }
+    __syncthreads();
+    int slot = 0;  // ring slot of plane s - 1
 #pragma unroll 1
     for (int j = 0; j < J; ++j) {
-        const int zc = wrap(tl.z0 - 2 + j, g.nz);
-        const int s0 = j % 3, s1 = (j + 2) % 3, s2 = (j + 1) % 3;  // planes zc, zc - 1, zc - 2
-        // ---- stage 1: pull of plane zc
-        C ft[Q], rk[3] = {C(1), C(1), C(1)};
-#pragma unroll
-        for (int i = 0; i < Q; ++i) ft[i] = C(0);
-        if (in1) {
-            const uint32_t zo[3] = {zoff(zc - 1), zoff(zc), zoff(zc + 1)};
-            rk[0] = rk[1] = rk[2] = C(0);
-            if constexpr (Q == 19 || sizeof(S) == 4) {
-                // one memory round trip per plane: the 3Q loads are issued together, and a
-                // scheduling barrier keeps the compiler from interleaving the sums with them
-                // (which serialises the loads).  The values stay in the storage type until
-                // summed (half the registers with FP32 storage: D3Q27 FP32 storage then fits
-                // one batch, 18% faster than one per fluid).
-                S v[3 * Q];
-#pragma unroll
-                for (int i = 0; i < Q; ++i) {
-                    const uint32_t o = src(zo, i);
-#pragma unroll
-                    for (int k = 0; k < 3; ++k) v[k * Q + i] = ld_plane(B + (int64_t)(k * Q + i) * g.N, o);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int i = 0; i < Q; ++i) {
-                    const C a = C(v[i]), b = C(v[Q + i]), c = C(v[2 * Q + i]);
-                    ft[i] = a + b + c;
-                    rk[0] += a;
-                    rk[1] += b;
-                    rk[2] += c;
-                }
-            } else {
-                // D3Q27 in FP64: one round trip per fluid (all 81 values of a plane would not
-                // fit beside the live registers); the totals add the fluids in the same order
-#pragma unroll
-                for (int k = 0; k < 3; ++k) {
-                    C v[Q];
-#pragma unroll
-                    for (int i = 0; i < Q; ++i) v[i] = C(ld_plane(B + (int64_t)(k * Q + i) * g.N, src(zo, i)));
-                    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                    for (int i = 0; i < Q; ++i) {
-                        ft[i] = k == 0 ? v[i] : ft[i] + v[i];
-                        rk[k] += v[i];
-                    }
-                }
-            }
-            const C ir = C(1) / (rk[0] + rk[1] + rk[2]);
-#pragma unroll
-            for (int k = 0; k < 3; ++k) L.c[s0][k][t] = rk[k] * ir;
-        }
-        C ftB[Q];
-#pragma unroll
-        for (int i = 0; i < Q; ++i) ftB[i] = C(0);
-        if (in3) {
-#pragma unroll
-            for (int i = 0; i < Q; ++i) {
-                ftB[i] = L.park[i][tP];
-                L.park[i][tP] = W[i];
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < Q; ++i) W[i] = ft[i];
-        __syncthreads();
-        // ---- stage 2: stress of plane zc - 1
-        C nA[9];
-#pragma unroll
-        for (int q = 0; q < 9; ++q) nA[q] = C(0);
-        if (j >= 2 && in2) {
-            const int sl[3] = {s2, s1, s0};  // by dz + 1
-            C gc[3][3], cc[3], tt[6];
+        // the ring's planes s - 1, s - 2, s - 3
+        lds_t* const c0 = cl + slot * (3 * T3);
+        lds_t* const c1 = cl + (slot == 0 ? 2 : slot - 1) * (3 * T3);
+        slot = slot == 2 ? 0 : slot + 1;
+        lds_t* const c2 = cl + slot * (3 * T3);
+        const int zd = dst.next();
+        // ---- stage 1 (every lane: those past the tile's halo sum what is never read)
+        __builtin_amdgcn_sched_barrier(0);
+        C rk[3];
+        if constexpr (IN == In3::Fac) {
+            C P0[3] = {C(0), C(0), C(0)};  // plane s + 1
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
-                grad3<C, Q>([&](int dx, int dy, int dz) { return L.c[sl[dz + 1]][k][t + dy * kTX + dx]; }, gc[k]);
-                cc[k] = L.c[s1][k][t];
+                rk[k] = D1[k];
+                D1[k] = D0[k];
             }
-            stress3<C>(gc, cc, rA, kp, tt, nA);
 #pragma unroll
-            for (int q = 0; q < 6; ++q) L.T[s1][q][tS] = tt[q];
+            for (int oy = -1; oy <= 1; ++oy)
+#pragma unroll
+                for (int ox = -1; ox <= 1; ++ox) {
+                    const int n = oy * Sh::CX + ox;
+                    const C c0 = cv[n], c1 = cv[NC + n], c2 = cv[2 * NC + n];
+#pragma unroll
+                    for (int i = 0; i < Q; ++i)
+                        if (L3X[i] == -ox && L3Y[i] == -oy) {
+                            const C f = C(vf[i]);
+                            C(&d)[3] = L3Z[i] < 0 ? rk : (L3Z[i] == 0 ? D1 : P0);
+                            d[0] = fma(c0, f, d[0]);
+                            d[1] = fma(c1, f, d[1]);
+                            d[2] = fma(c2, f, d[2]);
+                        }
+                }
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                settle(rk[k]);
+                settle(P0[k]);
+                settle(D1[k]);
+            }
+            if constexpr (!kLate) load_f(sf.next(), vf);
+            __builtin_amdgcn_sched_barrier(0);
+            C m[2], p[2], z[2];
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                plane_div<C, Q>([&](int a, int ox, int oy) { return cv[(3 + 3 * k + a) * NC + oy * Sh::CX + ox]; }, m[k],
+                                p[k], z[k]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            const C dn[2] = {p[0] + z[0], p[1] + z[1]}, up[2] = {p[0] - z[0], p[1] - z[1]};
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                rk[k] -= dn[k];
+                D1[k] -= m[k];
+                P0[k] -= up[k];
+            }
+            rk[2] += dn[0] + dn[1];
+            D1[2] += m[0] + m[1];
+            P0[2] += up[0] + up[1];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                D0[k] = P0[k];
+                settle(rk[k]);
+                settle(D0[k]);
+                settle(D1[k]);
+            }
+        } else {
+            double r[3];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) r[k] = rin[k * g.N + (int64_t)zd * pl + np];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                rk[k] = C(0);
+#pragma unroll
+                for (int i = 0; i < Q; ++i) rk[k] += rest_pop<S, C, Q>(i, r[k]);
+            }
+        }
+        const C irho = recip((rk[0] + rk[1]) + rk[2]);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) c0[k * T3] = rk[k] * irho;
+        __syncthreads();
+        // ---- stage 2
+        const C rho3 = rhoA, itau3 = itauA;  // of plane s - 3
+        if (j >= 4 && in2) {
+            lds_t* const cz[3] = {c2, c1, c0};  // by dz + 1
+            C gc[3][3], cc[3], tt[6], V[6];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                grad3<C, Q>([&](int dx, int dy, int dz) { return cz[dz + 1][k * T3 + dy * TX + dx]; }, gc[k]);
+                cc[k] = c1[k * T3];
+            }
+            stress3<C>(gc, cc, rA, kp, tt, V);
+#pragma unroll
+            for (int q = 0; q < 6; ++q) Tl[q * NT] = tt[q];
+            // tau = 3 nu + 1/2 with rho / nu = sum_k rho_k / nu_k (Eqs. 10-11)
+            rhoA = (rA[0] + rA[1]) + rA[2];
+            const C rn = rA[0] * C(kp.inv_nu[0]) + rA[1] * C(kp.inv_nu[1]) + rA[2] * C(kp.inv_nu[2]);
+            itauA = rn * recip(C(3) * rhoA + C(0.5) * rn);
+            if constexpr (!OBS) {
+                const int z2 = tl.z0 - 5 + j;  // plane s - 2
+                if (in3 && z2 >= tl.z0 && z2 < tl.z0 + tl.depth) {
+                    NodeBits bits((uint32_t)(z2 * pl + np) * (3u * Q) ^ salt);
+                    bits.skip(Q);
+                    const uint64_t base = fout + z2 * g.zbytes;
+                    refresh(lo[4]);
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) st_value<S>(base, lo[4], Q + k, to_storage<S, C>(cc[k], bits));
+#pragma unroll
+                    for (int a = 0; a < 6; ++a) st_value<S>(base, lo[4], Q + 3 + a, to_storage<S, C>(V[a], bits));
+                }
+            }
+        }
+        if constexpr (IN == In3::Fac) {
+            publish();
+            if constexpr (kLate) load_f(sf.next(), vf);
+            load_next_cv();
         }
         __syncthreads();
-        // ---- stage 3: collision and recolouring of plane zc - 2
+        // ---- stage 3
         if (j >= 4 && in3) {
-            const int sl[3] = {s0, s2, s1};  // T of planes zc - 3, zc - 2, zc - 1 by dz + 1
             C F[3];
-            force3<C, Q>([&](int q, int dx, int dy, int dz) { return L.T[sl[dz + 1]][q][tS + dy * (kTX - 2) + dx]; },
-                         F);
-            const uint32_t node = (uint32_t)(tl.z0 - 4 + j) * pl + yo[1] + (uint32_t)x;
-            const uint32_t o = node * (uint32_t)sizeof(S);
-            NodeBits bits(node * (3u * Q) ^ salt);
-            collide3<C, Q, OBS>(rB, ftB, F, nB, kp, acc, [&](int k, int i, C v) {
-                st_plane(Bout + (int64_t)(k * Q + i) * g.N, o, to_storage<S, C>(v, bits));
-            });
+            constexpr int QI[3][3] = {{0, 1, 2}, {1, 3, 4}, {2, 4, 5}};
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                C m, p, z;
+                plane_div<C, Q>([&](int a, int ox, int oy) { return Tl[QI[a][b] * NT + oy * Sh::SX + ox]; }, m, p, z);
+                F[b] = C(3) * (Fb[b] + (p + z));
+                Fb[b] = Fa[b] + m;
+                Fa[b] = p - z;
+            }
+            const int z3 = tl.z0 - 6 + j;  // plane s - 3
+            if (j >= 6) {
+                C ft[Q];
+                if constexpr (IN == In3::Fac) {
+#pragma unroll
+                    for (int i = 0; i < Q; ++i) ft[i] = C(vx[i]);
+                } else {
+                    double r[3];
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) r[k] = rin[k * g.N + (int64_t)z3 * pl + np];
+#pragma unroll
+                    for (int i = 0; i < Q; ++i)
+                        ft[i] = (rest_pop<S, C, Q>(i, r[0]) + rest_pop<S, C, Q>(i, r[1])) + rest_pop<S, C, Q>(i, r[2]);
+                }
+                C u[3] = {C(0), C(0), C(0)};
+                const C ir = recip(rho3);
+#pragma unroll
+                for (int i = 0; i < Q; ++i) {
+                    if (L3X[i] != 0) u[0] += L3X[i] > 0 ? ft[i] : -ft[i];
+                    if (L3Y[i] != 0) u[1] += L3Y[i] > 0 ? ft[i] : -ft[i];
+                    if (L3Z[i] != 0) u[2] += L3Z[i] > 0 ? ft[i] : -ft[i];
+                }
+#pragma unroll
+                for (int a = 0; a < 3; ++a) u[a] = (u[a] + C(0.5) * F[a]) * ir;
+                if constexpr (OBS) {
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) acc[k] += double(rB[k]);
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) acc[3 + a] += double(rho3 * u[a]);
+                    const double uu = double(u[0] * u[0] + u[1] * u[1] + u[2] * u[2]);
+                    acc[6] += 0.5 * double(rho3) * uu;
+                    const double um = sqrt(uu);
+                    acc[7] = (um > acc[7] || um != um) ? um : acc[7];
+                    if (rho_out) {
+#pragma unroll
+                        for (int k = 0; k < 3; ++k) rho_out[k * g.N + (int64_t)z3 * pl + np] = double(rB[k]);
+                    }
+                } else {
+                    NodeBits bits((uint32_t)(z3 * pl + np) * (3u * Q) ^ salt);
+                    const uint64_t base = fout + z3 * g.zbytes;
+                    refresh(lo[4]);
+                    collide3<C, Q>(rho3, itau3, ft, F, u,
+                                   [&](int i, C v) { st_value<S>(base, lo[4], i, to_storage<S, C>(v, bits)); });
+                }
+            }
+        }
+        // the totals of the next iteration's plane
+        if constexpr (IN == In3::Fac) {
+            if (j >= 5 && !edge) load_t(tot.next(), vx);
         }
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            rB[k] = rA[k];
+            if constexpr (OBS) rB[k] = rA[k];
             rA[k] = rk[k];
         }
-#pragma unroll
-        for (int q = 0; q < 9; ++q) nB[q] = nA[q];
     }
+}
+
+// S: storage type, C: compute type.  With FP32 storage of FP64 arithmetic each stored value
+// is rounded stochastically with the random bits of its node (key: node index and the step's
+// salt; f_dag_i first, then c_k, V_0, V_1).  OBS: the observables of the state instead of its
+// next step, and with rho_out the densities.
+template <typename S, typename C, bool OBS, int Q, In3 IN, typename Off>
+__global__ __launch_bounds__((Tile3Shape<sizeof(C)>::T)) __attribute__((amdgpu_waves_per_eu(Tile3Shape<sizeof(C)>::T / 256))) void k3_march(
+    const void* __restrict__ in, Geo3 g, KParams kp, const Tile3* __restrict__ tiles, S* __restrict__ out,
+    double* __restrict__ partials, double* __restrict__ rho_out, uint32_t salt)
+{
+    using Sh = Tile3Shape<sizeof(C)>;
+    constexpr int T3 = Sh::T;
+    static_assert(T3 % 64 == 0 && (2 * Sh::TX) % 64 == 0, "each wave is whole tile rows");
+    static_assert(2 * Sh::CX + 2 * Sh::TY <= 128, "one lane of two waves per node of the outer ring");
+    static_assert(sizeof(double) * 8 * (T3 / 64) <= sizeof(C) * 3 * 3 * T3, "c ring too small for the reduction");
+    __shared__ March3Lds<C> L;
+    const Tile3 tl = tiles[blockIdx.x];
+    const int t = threadIdx.x;
+    double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    march3<S, C, OBS, Q, IN, Off>(in, g, kp, tl, out, L, acc, rho_out, salt);
     if constexpr (OBS) {
-        // wavefront reductions, then the eight waves' results in order (the c ring is free
-        // once every lane has passed the last barrier of the march)
+        // wavefront reductions, then the waves' results in order (the c ring is free once
+        // every lane has passed the last barrier of the march)
         __syncthreads();
         for (int q = 0; q < 7; ++q) acc[q] = wave_sum(acc[q]);
         acc[7] = wave_max(acc[7]);
         double* red = reinterpret_cast<double*>(&L.c[0][0][0]);
-        constexpr int W = kT3 / 64;
+        constexpr int W = T3 / 64;
         if ((t & 63) == 0)
             for (int q = 0; q < 8; ++q) red[q * W + (t >> 6)] = acc[q];
         __syncthreads();
@@ -498,42 +707,46 @@ __device__ __forceinline__ bool node3(const Geo3& g, int& x, int& y, int& z)
     return true;
 }
 
-// B_{i,k}(y) = w_i rho_k(y + e_i): the pulled state is f_{i,k} = w_i rho_k (fluid at rest)
+// the post-streaming populations f[3][Q][N] of the state, f_{i,k} = c_k f_dag_i + w_i V_k . e_i
+// at x - e_i (or those of the fluid at rest)
 template <typename S, typename C, int Q>
-__global__ __launch_bounds__(256) void k3_init(const double* __restrict__ rho, Geo3 g, S* __restrict__ B)
+__global__ __launch_bounds__(256) void k3_export(const void* __restrict__ in, In3 fmt, Geo3 g, double* __restrict__ f)
 {
     int x, y, z;
     if (!node3(g, x, y, z)) return;
     const Nb3 nb(g, x, y, z);
     const int64_t j = nb.at(0, 0, 0);
+    if (fmt == In3::Rho) {
+        const double* rho = (const double*)in;
+#pragma unroll
+        for (int i = 0; i < Q; ++i)
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                f[(int64_t)(k * Q + i) * g.N + j] = double(rest_pop<S, C, Q>(i, rho[k * g.N + j]));
+        return;
+    }
+    const int64_t pl = (int64_t)g.nx * g.ny;
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
-        const int64_t src = nb.at(L3X[i], L3Y[i], L3Z[i]);
+        const int64_t zs = nb.zo[1 - L3Z[i]];
+        const int64_t o = node_off3<S, Q, int64_t>(nb.at(-L3X[i], -L3Y[i], -L3Z[i]) - zs);
+        const char* b = (const char*)in + zs / pl * g.zbytes + o;
+        auto value = [&](int v) { return C(*(const S*)(b + v * kLine)); };
+        const C fd = value(i);
+        C V[3][3];
 #pragma unroll
-        for (int k = 0; k < 3; ++k) B[(int64_t)(k * Q + i) * g.N + j] = S(w3<C, Q>(i) * C(rho[k * g.N + src]));
+        for (int a = 0; a < 3; ++a) {
+            V[0][a] = value(Q + 3 + a);
+            V[1][a] = value(Q + 6 + a);
+            V[2][a] = -(V[0][a] + V[1][a]);
+        }
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            f[(int64_t)(k * Q + i) * g.N + j] =
+                double(fma(value(Q + k), fd, w3<C, Q>(i) * edot<C>(i, V[k][0], V[k][1], V[k][2])));
     }
 }
 
-// the post-streaming populations [3][Q][N] and densities [3][N] of the state
-template <typename S, int Q>
-__global__ __launch_bounds__(256) void k3_export(const S* __restrict__ B, Geo3 g, double* __restrict__ fout,
-                                                 double* __restrict__ rho)
-{
-    int x, y, z;
-    if (!node3(g, x, y, z)) return;
-    const Nb3 nb(g, x, y, z);
-    const int64_t j = nb.at(0, 0, 0);
-    double f[3][Q];
-    pull3<S, Q>(B, g, nb, f);
-    for (int k = 0; k < 3; ++k) {
-        double s = 0.0;
-        for (int i = 0; i < Q; ++i) {
-            s += f[k][i];
-            if (fout) fout[(int64_t)(k * Q + i) * g.N + j] = f[k][i];
-        }
-        rho[k * g.N + j] = s;
-    }
-}
 
 }  // namespace
 }  // namespace tcg
@@ -548,10 +761,11 @@ struct lbm3d {
     Prec prec = Prec::F64;
     int q = 19;                         // links: 19 or 27
     void* buf[2] = {nullptr, nullptr};  // the state, in the storage type of prec
+    In3 fmt = In3::Rho;                 // what buf[cur] holds
     Tile3* dtiles = nullptr;     // the march's tile list
     int ntiles = 0;
     double* partials = nullptr;  // [ntiles][8]
-    double* staging = nullptr;   // [3q][N] for exports and uploads
+    double* staging = nullptr;   // [3q][N] for exports
     double* rho = nullptr;       // [3][N] densities for exports
     int cur = 0;
     int64_t step = 0;
@@ -578,15 +792,14 @@ static void split_even(int n, int parts, int q, int& start, int& len)
 }
 
 // The march's tiles: the x-y plane cut into at most (TX - 4) x (TY - 4) node blocks (the
-// lattice's tile shape), the z axis into `nseg` segments chosen so that rounds of resident
-// workgroups x (segment depth + 4 warm-up planes) is least.  Workgroups go to the XCDs in
-// turn, so the list is permuted for each XCD to take a contiguous run of it (neighbouring
-// blocks, whose halos it then finds in its own L2).
-static std::vector<Tile3> plan3(const Geo3& g, int slots, int q, Prec prec)
+// tile shape of the compute type), the z axis into `nseg` segments chosen so that rounds of
+// resident workgroups x (segment depth + 6 warm-up planes) is least, down to one plane a segment
+// (48^3 D3Q19 FP64: 12 segments of 4 planes 56 us, 24 of 2 planes 48 us).  Workgroups go to the
+// XCDs in turn, so the list is permuted for each XCD to take a contiguous run of it
+// (neighbouring blocks, whose halos it then finds in its own L2).
+static std::vector<Tile3> plan3(const Geo3& g, int slots, Prec prec)
 {
-    const bool f32 = prec == Prec::F32;
-    const int TX = 32;
-    const int TY = f32 ? Tile3Shape<19, 4>::TY : (q == 27 ? Tile3Shape<27>::TY : Tile3Shape<19>::TY);
+    const int TX = Tile3Shape<8>::TX, TY = prec == Prec::F32 ? Tile3Shape<4>::TY : Tile3Shape<8>::TY;
     const int ntx = (g.nx + TX - 5) / (TX - 4), nty = (g.ny + TY - 5) / (TY - 4);
     const int64_t per_seg = (int64_t)ntx * nty;
     if (slots < 1) slots = 1;
@@ -595,12 +808,11 @@ static std::vector<Tile3> plan3(const Geo3& g, int slots, int q, Prec prec)
     for (int s = 1; s <= g.nz; ++s) {
         const int depth = (g.nz + s - 1) / s;
         const int64_t rounds = (per_seg * s + slots - 1) / slots;
-        const double cost = (double)rounds * (depth + 4) * (1.0 + 1e-9 * s);
+        const double cost = (double)rounds * (depth + 6) * (1.0 + 1e-9 * s);
         if (cost < best) {
             best = cost;
             nseg = s;
         }
-        if (depth <= 4) break;
     }
     std::vector<Tile3> L;
     L.reserve((size_t)per_seg * nseg);
@@ -621,48 +833,60 @@ static std::vector<Tile3> plan3(const Geo3& g, int slots, int q, Prec prec)
     return out;
 }
 
-template <typename S, typename C, int Q>
-static hipError_t launch_march_t(lbm3d* h, bool obs)
+template <typename S, typename C, int Q, In3 IN, typename Off>
+static hipError_t launch_march_f(lbm3d* h, bool obs, double* rho_out)
 {
-    const S* in = (const S*)h->buf[h->cur];
-    const uint32_t salt = step_salt(h->step);
-    constexpr int T = Tile3Shape<Q, sizeof(C)>::T;
+    const void* in = h->buf[h->cur];
+    const dim3 grid(h->ntiles), block(Tile3Shape<sizeof(C)>::T);
     if (obs)
-        hipLaunchKernelGGL((k3_march<S, C, true, Q>), dim3(h->ntiles), dim3(T), 0, h->stream, in, h->g, h->kp,
-                           (const Tile3*)h->dtiles, (S*)nullptr, h->partials, 0u);
+        hipLaunchKernelGGL((k3_march<S, C, true, Q, IN, Off>), grid, block, 0, h->stream, in, h->g, h->kp,
+                           (const Tile3*)h->dtiles, (S*)nullptr, h->partials, rho_out, 0u);
     else
-        hipLaunchKernelGGL((k3_march<S, C, false, Q>), dim3(h->ntiles), dim3(T), 0, h->stream, in, h->g, h->kp,
-                           (const Tile3*)h->dtiles, (S*)h->buf[h->cur ^ 1], (double*)nullptr, salt);
+        hipLaunchKernelGGL((k3_march<S, C, false, Q, IN, Off>), grid, block, 0, h->stream, in, h->g, h->kp,
+                           (const Tile3*)h->dtiles, (S*)h->buf[h->cur ^ 1], (double*)nullptr, (double*)nullptr,
+                           step_salt(h->step));
     return hipGetLastError();
 }
 
-template <int Q>
-static hipError_t launch_march_q(lbm3d* h, bool obs)
+// Offsets within a z plane fit 32 bits below 4 GiB a plane (15 to 38 million nodes); larger
+// planes, and every first step, take the 64-bit instantiation.
+template <typename S, typename C, int Q>
+static hipError_t launch_march_q(lbm3d* h, bool obs, double* rho_out)
 {
-    switch (h->prec) {
-        case Prec::F64: return launch_march_t<double, double, Q>(h, obs);
-        case Prec::F32S: return launch_march_t<float, double, Q>(h, obs);
-        case Prec::F32: return launch_march_t<float, float, Q>(h, obs);
-    }
-    return hipErrorInvalidValue;
+    if (h->fmt == In3::Rho) return launch_march_f<S, C, Q, In3::Rho, uint64_t>(h, obs, rho_out);
+    if (h->g.zbytes >= ((int64_t)1 << 32)) return launch_march_f<S, C, Q, In3::Fac, uint64_t>(h, obs, rho_out);
+    return launch_march_f<S, C, Q, In3::Fac, uint32_t>(h, obs, rho_out);
 }
 
-static hipError_t launch_march(lbm3d* h, bool obs)
+template <typename S, typename C>
+static hipError_t launch_march_t(lbm3d* h, bool obs, double* rho_out)
 {
-    return h->q == 27 ? launch_march_q<27>(h, obs) : launch_march_q<19>(h, obs);
+    return h->q == 27 ? launch_march_q<S, C, 27>(h, obs, rho_out) : launch_march_q<S, C, 19>(h, obs, rho_out);
+}
+
+// One step into the other buffer, or (obs) the observables' partial sums and, with rho_out,
+// the densities [3][N].
+static hipError_t launch_march(lbm3d* h, bool obs, double* rho_out = nullptr)
+{
+    switch (h->prec) {
+        case Prec::F64: return launch_march_t<double, double>(h, obs, rho_out);
+        case Prec::F32S: return launch_march_t<float, double>(h, obs, rho_out);
+        case Prec::F32: return launch_march_t<float, float>(h, obs, rho_out);
+    }
+    return hipErrorInvalidValue;
 }
 
 template <int Q>
 static hipError_t march_occupancy_q(Prec prec, int* per_cu)
 {
-    constexpr int T = Tile3Shape<Q>::T, T4 = Tile3Shape<Q, 4>::T;
+    constexpr int T8 = Tile3Shape<8>::T, T4 = Tile3Shape<4>::T;
     switch (prec) {
         case Prec::F64:
-            return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, k3_march<double, double, false, Q>, T, 0);
+            return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, k3_march<double, double, false, Q, In3::Fac, uint32_t>, T8, 0);
         case Prec::F32S:
-            return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, k3_march<float, double, false, Q>, T, 0);
+            return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, k3_march<float, double, false, Q, In3::Fac, uint32_t>, T8, 0);
         case Prec::F32:
-            return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, k3_march<float, float, false, Q>, T4, 0);
+            return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, k3_march<float, float, false, Q, In3::Fac, uint32_t>, T4, 0);
     }
     return hipErrorInvalidValue;
 }
@@ -673,44 +897,21 @@ static hipError_t march_occupancy(Prec prec, int q, int* per_cu)
 }
 
 template <int Q>
-static hipError_t launch_init3_q(lbm3d* h, const double* rho)
+static hipError_t launch_export3_q(lbm3d* h, double* fout)
 {
     const dim3 gr = grid3(h->g), bl(256);
+    const void* in = h->buf[h->cur];
     switch (h->prec) {
-        case Prec::F64:
-            hipLaunchKernelGGL((k3_init<double, double, Q>), gr, bl, 0, h->stream, rho, h->g, (double*)h->buf[0]);
-            break;
-        case Prec::F32S:
-            hipLaunchKernelGGL((k3_init<float, double, Q>), gr, bl, 0, h->stream, rho, h->g, (float*)h->buf[0]);
-            break;
-        case Prec::F32:
-            hipLaunchKernelGGL((k3_init<float, float, Q>), gr, bl, 0, h->stream, rho, h->g, (float*)h->buf[0]);
-            break;
+        case Prec::F64: hipLaunchKernelGGL((k3_export<double, double, Q>), gr, bl, 0, h->stream, in, h->fmt, h->g, fout); break;
+        case Prec::F32S: hipLaunchKernelGGL((k3_export<float, double, Q>), gr, bl, 0, h->stream, in, h->fmt, h->g, fout); break;
+        case Prec::F32: hipLaunchKernelGGL((k3_export<float, float, Q>), gr, bl, 0, h->stream, in, h->fmt, h->g, fout); break;
     }
     return hipGetLastError();
 }
 
-static hipError_t launch_init3(lbm3d* h, const double* rho)
+static hipError_t launch_export3(lbm3d* h, double* fout)
 {
-    return h->q == 27 ? launch_init3_q<27>(h, rho) : launch_init3_q<19>(h, rho);
-}
-
-template <int Q>
-static hipError_t launch_export3_q(lbm3d* h, double* fout, double* rho)
-{
-    const dim3 gr = grid3(h->g), bl(256);
-    if (h->prec == Prec::F64)
-        hipLaunchKernelGGL((k3_export<double, Q>), gr, bl, 0, h->stream, (const double*)h->buf[h->cur], h->g, fout,
-                           rho);
-    else
-        hipLaunchKernelGGL((k3_export<float, Q>), gr, bl, 0, h->stream, (const float*)h->buf[h->cur], h->g, fout,
-                           rho);
-    return hipGetLastError();
-}
-
-static hipError_t launch_export3(lbm3d* h, double* fout, double* rho)
-{
-    return h->q == 27 ? launch_export3_q<27>(h, fout, rho) : launch_export3_q<19>(h, fout, rho);
+    return h->q == 27 ? launch_export3_q<27>(h, fout) : launch_export3_q<19>(h, fout);
 }
 
 extern "C" {
@@ -750,7 +951,8 @@ int lbm3d_create_lattice(const lbm3_params* p, int32_t nz, int32_t q, void* hip_
     h->prec = prec_of(p->precision);
     h->q = q;
     derive(p, &h->kp, nullptr, nullptr, nullptr);
-    h->g = Geo3{p->nx, p->ny, nz, (int64_t)p->nx * p->ny * nz};
+    h->g = Geo3{p->nx, p->ny, nz, (int64_t)p->nx * p->ny * nz,
+                h->prec == Prec::F64 ? zbytes3<double>(p->nx, p->ny, q) : zbytes3<float>(p->nx, p->ny, q)};
     h->stream = (hipStream_t)hip_stream;
     const int64_t N = h->g.N;
     hipError_t e = hipSuccess;
@@ -760,11 +962,10 @@ int lbm3d_create_lattice(const lbm3_params* p, int32_t nz, int32_t q, void* hip_
     if (e == hipSuccess) e = march_occupancy(h->prec, q, &per_cu);
     std::vector<Tile3> tiles;
     if (e == hipSuccess) {
-        tiles = plan3(h->g, per_cu * cus, q, h->prec);
+        tiles = plan3(h->g, per_cu * cus, h->prec);
         h->ntiles = (int)tiles.size();
     }
-    const size_t eb = h->prec == Prec::F64 ? sizeof(double) : sizeof(float);
-    if (e == hipSuccess) e = alloc_state_pair((size_t)3 * q * N * eb, h->buf);
+    if (e == hipSuccess) e = alloc_state_pair((size_t)h->g.zbytes * nz, h->buf);
     if (e == hipSuccess) e = hipMalloc(&h->dtiles, tiles.size() * sizeof(Tile3));
     if (e == hipSuccess)
         e = hipMemcpy(h->dtiles, tiles.data(), tiles.size() * sizeof(Tile3), hipMemcpyHostToDevice);
@@ -795,13 +996,13 @@ int lbm3d_init_fields(lbm3d_t* h, const double* rho)
     const int64_t N = h->g.N;
     int rc = check_rho_fields(rho, nullptr, N);
     if (rc) return rc;
-    hipError_t e = hipMemcpyAsync(h->staging, rho, (size_t)3 * N * sizeof(double), hipMemcpyHostToDevice, h->stream);
-    if (e == hipSuccess) {
-        e = launch_init3(h, (const double*)h->staging);
-    }
+    // the densities are the state until the first step (Q + 9 values of at least 4 bytes hold
+    // three of 8)
+    hipError_t e = hipMemcpyAsync(h->buf[0], rho, (size_t)3 * N * sizeof(double), hipMemcpyHostToDevice, h->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
     if (e != hipSuccess) return hip_fail(e, "three-dimensional init");
     h->cur = 0;
+    h->fmt = In3::Rho;
     h->step = 0;
     h->ready = true;
     return LBM3_OK;
@@ -821,6 +1022,7 @@ int lbm3d_step(lbm3d_t* h, int64_t n)
         hipError_t e = launch_march(h, false);
         if (e != hipSuccess) return hip_fail(e, "three-dimensional step launch");
         h->cur ^= 1;
+        h->fmt = In3::Fac;
         h->step += 1;
     }
     return LBM3_OK;
@@ -838,15 +1040,15 @@ int lbm3d_observables(lbm3d_t* h, lbm3d_obs* out, double* rho_out, double* f_out
     }
     const size_t nblocks = (size_t)h->ntiles;
     const int64_t N = h->g.N;
-    hipError_t e = launch_march(h, true);
+    hipError_t e = launch_march(h, true, rho_out ? h->rho : nullptr);
     std::vector<double> part(nblocks * 8);
     if (e == hipSuccess)
         e = hipMemcpyAsync(part.data(), h->partials, part.size() * sizeof(double), hipMemcpyDeviceToHost, h->stream);
-    if (e == hipSuccess && (rho_out || f_out)) {
-        e = launch_export3(h, f_out ? h->staging : nullptr, h->rho);
-        if (e == hipSuccess && rho_out)
-            e = hipMemcpyAsync(rho_out, h->rho, (size_t)3 * N * sizeof(double), hipMemcpyDeviceToHost, h->stream);
-        if (e == hipSuccess && f_out)
+    if (e == hipSuccess && rho_out)
+        e = hipMemcpyAsync(rho_out, h->rho, (size_t)3 * N * sizeof(double), hipMemcpyDeviceToHost, h->stream);
+    if (e == hipSuccess && f_out) {
+        e = launch_export3(h, h->staging);
+        if (e == hipSuccess)
             e = hipMemcpyAsync(f_out, h->staging, (size_t)3 * h->q * N * sizeof(double), hipMemcpyDeviceToHost,
                                h->stream);
     }

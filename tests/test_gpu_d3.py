@@ -198,3 +198,35 @@ def test_reduced_precision_mass_drift(precision, bar, q):
         runs.append(r)
     if len(runs) == 2:
         assert np.array_equal(runs[0], runs[1])
+
+
+@pytest.mark.parametrize("precision,rtol", [("fp64", 1e-11), ("fp32", 2e-5)])
+@pytest.mark.parametrize("q", QS)
+@pytest.mark.parametrize("shape", [(28, 12, 2), (29, 13, 5), (56, 25, 1), (17, 31, 12), (33, 47, 3), (1, 40, 9), (130, 1, 4)])
+def test_factored_march_at_the_edges_of_its_tiles(shape, q, precision, rtol):
+    """Lattices whose sides are a tile's 28 x 12 (FP32: 28 x 20) columns, one more, ragged
+    parts of them and a single node, with one to many planes per segment; the factored state
+    after 1 step (read from the initial densities) and 4 (read from itself)."""
+    nx, ny, nz = shape
+    rho = inputs.random_mixture_3d(nx, ny, nz, 21, tiny_fraction=0.0)
+    for steps in (1, 4):
+        o = _oracle(rho, steps, q=q)
+        err = np.abs(_gpu(rho, steps, q=q, precision=precision) - o).max() / np.abs(o).max()
+        print(shape, q, precision, steps, err)
+        assert err <= rtol
+
+
+def test_plane_beyond_32_bit_offsets_equals_the_2d_step():
+    """A plane of 4.1 GiB (5000 x 3840 nodes, D3Q19, FP64) takes the march with 64-bit offsets;
+    one plane deep, the lattice is uniform along z and its densities follow the two-dimensional
+    step (1e-12, as in the uniform-lattice test)."""
+    nx, ny = 5000, 3840
+    w = inputs.droplet_tiling(nx if nx == ny else 256, cell=128, R=24.0)
+    rho = np.ascontiguousarray(np.tile(w.rho, (1, -(-ny // 256), -(-nx // 256)))[:, :ny, :nx])
+    L3 = lbm3.Lattice3D(nx, ny, 1, SIG, TAU).init(rho[:, None])
+    r3 = L3.step(3).densities()[:, 0]
+    L3.close()
+    L2 = lbm3.Lattice(nx, ny, SIG, TAU).init(rho)
+    r2 = L2.step(3).densities()
+    L2.close()
+    assert np.abs(r3 - r2).max() <= 1e-12
