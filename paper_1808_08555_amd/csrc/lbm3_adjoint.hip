@@ -887,10 +887,10 @@ int lbm3_adjoint(lbm3_t* h, const double* drho1_T, double dsigma[3], double* drh
     const dim3 grid((kp.nx + 255) / 256, kp.ny), blk(256);
     const int64_t nblocks = (int64_t)grid.x * grid.y;
     // tiles of the fused A2 + A3 pass: blocks where the forward takes its one-step blocks
-    // (ntilesb > 0: at most 2^20 nodes and no march shape chosen by lbm3_set_tile or
+    // (h->blocks: at most 2^20 nodes and no march shape chosen by lbm3_set_tile or
     // lbm3_set_steps_per_launch(2)), else strips of at most sf_width - 2 columns, rows
     // fitted to the resident workgroups
-    const bool sf_block = h->ntilesb > 0 && N <= kSfBlockMaxNodes;
+    const bool sf_block = h->blocks && N <= kSfBlockMaxNodes;
     const bool fused = sf_block && N <= kAdjFusedMaxNodes;
     const int sfw = sf_block ? 0 : sf_width(kp.nx);
     std::vector<Tile> sf_plan;
@@ -988,9 +988,8 @@ int lbm3_adjoint(lbm3_t* h, const double* drho1_T, double dsigma[3], double* drh
             const Fmt fj = j == 0 ? in : Fmt::FAC;
             double* tj = tape[b] + (size_t)j * kTapeFields * N;
             // small lattices: the block step (as the forward steps took), else the march
-            r = fj == Fmt::FAC && h->ntilesb > 0
-                    ? tiles_f64_block_tape(fwd[b][j & 1], fwd[b][(j + 1) & 1], h->dinst, h->dtilesb, h->ntilesb, tj,
-                                           q)
+            r = fj == Fmt::FAC && h->blocks
+                    ? tiles_f64_block_tape(fwd[b][j & 1], fwd[b][(j + 1) & 1], h->bgrid, tj, q)
                     : tiles_f64_tape(fj, fwd[b][j & 1], fwd[b][(j + 1) & 1], h->dinst, h->dtiles, h->ntiles,
                                      h->threads, tj, q);
         }

@@ -274,19 +274,16 @@ int upload_plan(lbm3* h)
     h->threads2 = t2;
     // Single steps of a small lattice go to the block kernel (no march warm-up), unless
     // lbm3_set_tile chose a march shape or steps-per-launch mode 2 asks for pairs.
-    std::vector<Tile> LB;
-    if (!h->tile_set && h->pass_mode != 2 && (int64_t)h->kp.nx * h->kp.ny <= kBlockMaxNodes)
-        plan_blocks(0, h->kp.nx, h->kp.ny, kBlockCols, kBlockRows, LB);
-    std::vector<Tile> T = xcd_order(L, 8), T2 = xcd_order(L2, 8), TB = xcd_order(LB, 8);
+    h->blocks = !h->tile_set && h->pass_mode != 2 && (int64_t)h->kp.nx * h->kp.ny <= kBlockMaxNodes;
+    h->bgrid = block_grid(h->kp, device_cus());
+    std::vector<Tile> T = xcd_order(L, 8), T2 = xcd_order(L2, 8);
     (void)hipStreamSynchronize(h->stream);
     if (h->dtiles) (void)hipFree(h->dtiles);
     if (h->dtiles2) (void)hipFree(h->dtiles2);
-    if (h->dtilesb) (void)hipFree(h->dtilesb);
-    h->dtiles = h->dtiles2 = h->dtilesb = nullptr;
-    h->ntiles = h->ntiles2 = h->ntilesb = 0;
+    h->dtiles = h->dtiles2 = nullptr;
+    h->ntiles = h->ntiles2 = 0;
     hipError_t e = hipMalloc((void**)&h->dtiles, T.size() * sizeof(Tile));
     if (e == hipSuccess && !T2.empty()) e = hipMalloc((void**)&h->dtiles2, T2.size() * sizeof(Tile));
-    if (e == hipSuccess && !TB.empty()) e = hipMalloc((void**)&h->dtilesb, TB.size() * sizeof(Tile));
     if (e == hipSuccess && !h->dinst) e = hipMalloc((void**)&h->dinst, sizeof(Instance));
     Instance I{};
     I.kp = h->kp;
@@ -294,13 +291,10 @@ int upload_plan(lbm3* h)
     if (e == hipSuccess) e = hipMemcpy(h->dtiles, T.data(), T.size() * sizeof(Tile), hipMemcpyHostToDevice);
     if (e == hipSuccess && !T2.empty())
         e = hipMemcpy(h->dtiles2, T2.data(), T2.size() * sizeof(Tile), hipMemcpyHostToDevice);
-    if (e == hipSuccess && !TB.empty())
-        e = hipMemcpy(h->dtilesb, TB.data(), TB.size() * sizeof(Tile), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(h->dinst, &I, sizeof I, hipMemcpyHostToDevice);
     if (e != hipSuccess) return hip_fail(e, "tile plan upload");
     h->ntiles = (int)T.size();
     h->ntiles2 = (int)T2.size();
-    h->ntilesb = (int)TB.size();
     h->rows = rows;
     return LBM3_OK;
 }
@@ -318,9 +312,8 @@ int step_handle(lbm3* h, int64_t n)
             e = launch_pair(h->prec, h->buf[h->cur], h->buf[h->cur ^ 1], h->dinst, h->dtiles2, h->ntiles2,
                             h->threads2, h->step, h->stream, pt);
             done = 2;
-        } else if (h->fmt == Fmt::FAC && h->ntilesb > 0) {
-            e = launch_block(h->prec, h->buf[h->cur], h->buf[h->cur ^ 1], h->dinst, h->dtilesb, h->ntilesb,
-                             h->step, h->stream, pt);
+        } else if (h->fmt == Fmt::FAC && h->blocks) {
+            e = launch_block(h->prec, h->buf[h->cur], h->buf[h->cur ^ 1], h->bgrid, h->step, h->stream, pt);
         } else {
             e = launch_tiles(h->prec, h->fmt, Fmt::FAC, h->buf[h->cur], h->buf[h->cur ^ 1], h->dinst,
                              h->dtiles, h->ntiles, h->threads, h->step, 0, h->stream, pt);
@@ -642,7 +635,6 @@ int lbm3_destroy(lbm3_t* h)
     if (h->obs_host) (void)hipHostFree(h->obs_host);
     if (h->dtiles) (void)hipFree(h->dtiles);
     if (h->dtiles2) (void)hipFree(h->dtiles2);
-    if (h->dtilesb) (void)hipFree(h->dtilesb);
     if (h->dinst) (void)hipFree(h->dinst);
     adjoint_destroy(h);
     delete h;

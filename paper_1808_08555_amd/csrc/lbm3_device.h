@@ -61,6 +61,15 @@ __device__ __forceinline__ void st_at(T* base, unsigned byte_off, T v)
     __builtin_nontemporal_store(v, (gT*)(b + byte_off));
 }
 
+template <typename T>
+__device__ __forceinline__ void st_plain(T* base, unsigned byte_off, T v)
+{
+    typedef __attribute__((address_space(1))) char gchar;
+    typedef __attribute__((address_space(1))) T gT;
+    gchar* b = (gchar*)uniform_u64(reinterpret_cast<uint64_t>(base));
+    *(gT*)(b + byte_off) = v;
+}
+
 // The plane stride as a value the optimiser must take afresh at each row: left alone, it
 // hoists the 18 or 27 plane offsets of a row out of the march loop and keeps them all live
 // in scalar registers, which then spill to vector lanes (FP32 storage: 91 spilled scalars,

@@ -111,8 +111,7 @@ void plan_lattice(int inst, int nx, int ny, int threads, int rows, int elem_byte
 // receives one contiguous run of it, keeping neighbouring tiles, and the halos they share, in
 // the same L2.
 std::vector<Tile> xcd_order(const std::vector<Tile>& L, int nxcd);
-// Blocks of one lattice: at most cmax x rmax nodes each (kBlockCols x kBlockRows for
-// launch_block), sizes spread evenly over nx and ny, row of blocks after row of blocks.
+// Blocks of one lattice: at most cmax x rmax nodes each, sizes spread evenly over nx and ny, row of blocks after row of blocks.
 void plan_blocks(int inst, int nx, int ny, int cmax, int rmax, std::vector<Tile>& out);
 // The two state buffers of a step (read one, write the other) in one allocation, the second
 // an odd number of MiB after the first (see lbm3_plan.hip); buf[1] is not freed on its own.
@@ -120,6 +119,7 @@ hipError_t alloc_state_pair(size_t bytes, void* buf[2]);
 void free_state_pair(void* buf[2]);
 // Rows per segment that fit the tile count to the resident workgroup slots.
 int auto_rows(int nx, int ny, int threads, int slots, int elem_bytes, int halo = 3);
+int device_cus();
 int device_slots(Prec prec, int threads);
 // resident slots of the two-step pass (0 where it does not exist: FP32 storage, 512 threads)
 int device_slots_pair(Prec prec, int threads);
@@ -173,23 +173,47 @@ int tiles_f32s_pair_occupancy(int threads);
 hipError_t launch_pair(Prec prec, const void* fin, void* fout, const Instance* inst, const Tile* tiles,
                        int ntiles, int threads, int64_t step, hipStream_t stream, bool pt = false,
                        const int64_t* step_dev = nullptr);
-// One step (factored state in and out) on two-dimensional blocks: tiles from plan_blocks,
-// workgroups of kBlockThreads lanes; bitwise the same as the march's step.  pt, step and
-// step_dev as for launch_tiles.
-constexpr int kBlockCols = 28, kBlockRows = 12, kBlockThreads = 512;
-hipError_t tiles_f64_block(const void* fin, void* fout, const Instance* inst, const Tile* tiles, int ntiles,
-                           uint32_t salt, const int64_t* step_dev, bool pt, hipStream_t stream);
-hipError_t tiles_f32_block(const void* fin, void* fout, const Instance* inst, const Tile* tiles, int ntiles,
-                           uint32_t salt, const int64_t* step_dev, bool pt, hipStream_t stream);
-hipError_t tiles_f32s_block(const void* fin, void* fout, const Instance* inst, const Tile* tiles, int ntiles,
-                            uint32_t salt, const int64_t* step_dev, bool pt, hipStream_t stream);
+// One step (factored state in and out) on two-dimensional blocks of one lattice, workgroups of
+// 32 x lanes_y lanes owning at most kBlockCols x (lanes_y - 4) nodes; bitwise the same as the
+// march's step.  pt and step as for launch_tiles.
+// The lattice's constants and the blocks' geometry are launch arguments: a table of tiles and
+// one of instances cost a small lattice's step two more dependent loads before its own.
+constexpr int kBlockY = 16, kBlockYSmall = 8;  // rows of lanes
+constexpr int kBlockCols = 28, kBlockRows = kBlockY - 4;
+struct BlockGrid {
+    KParams kp;
+    int32_t lanes_y;     // kBlockY or kBlockYSmall
+    int32_t count;       // blocks
+    int32_t nbx;         // blocks per row of blocks
+    uint32_t inv;        // ceil(2^32 / nbx): b / nbx = (b inv) >> 32 for b nbx < 2^32
+    int32_t bw, rw;      // nx = bw nbx + rw: the first rw blocks of a row are bw + 1 wide
+    int32_t bh, rh;      // ny likewise
+    // Block of workgroup wg: the workgroups, dealt to the 8 XCDs in turn, take the blocks (row of
+    // blocks after row of blocks) so that each XCD has one contiguous run of them.
+    __host__ __device__ void block(int wg, int& x0, int& y0, int& cols, int& rows) const
+    {
+        const int d = wg & 7, q = count >> 3, r = count & 7;
+        const int b = d * q + (d < r ? d : r) + (wg >> 3);
+        const int by = nbx == 1 ? b : (int)(((uint64_t)(uint32_t)b * inv) >> 32), bx = b - by * nbx;
+        x0 = bx * bw + (bx < rw ? bx : rw);
+        cols = bw + (bx < rw ? 1 : 0);
+        y0 = by * bh + (by < rh ? by : rh);
+        rows = bh + (by < rh ? 1 : 0);
+    }
+};
+// cus: compute units of the device
+BlockGrid block_grid(const KParams& kp, int cus);
+hipError_t tiles_f64_block(const void* fin, void* fout, const BlockGrid& bg, uint32_t salt, bool pt,
+                           hipStream_t stream);
+hipError_t tiles_f32_block(const void* fin, void* fout, const BlockGrid& bg, uint32_t salt, bool pt,
+                           hipStream_t stream);
+hipError_t tiles_f32s_block(const void* fin, void* fout, const BlockGrid& bg, uint32_t salt, bool pt,
+                            hipStream_t stream);
 // The FP64 block step (factored state in) that also writes the adjoint's tape, as
 // tiles_f64_tape does.
-hipError_t tiles_f64_block_tape(const void* fin, void* fout, const Instance* inst, const Tile* tiles, int ntiles,
-                                double* tape, hipStream_t stream);
-hipError_t launch_block(Prec prec, const void* fin, void* fout, const Instance* inst, const Tile* tiles,
-                        int ntiles, int64_t step, hipStream_t stream, bool pt = false,
-                        const int64_t* step_dev = nullptr);
+hipError_t tiles_f64_block_tape(const void* fin, void* fout, const BlockGrid& bg, double* tape, hipStream_t stream);
+hipError_t launch_block(Prec prec, const void* fin, void* fout, const BlockGrid& bg, int64_t step, hipStream_t stream,
+                        bool pt = false);
 
 // Host-side helpers (lbm3_api.hip).
 void set_error(const char* fmt, ...);

@@ -1509,9 +1509,8 @@ int tiles_occupancy(int threads)
 // Factored input and output only (a state in the 27-population format takes one step of
 // the march first).  With TAPE (FP64) the owned lanes also write the adjoint's tape as the
 // march does: densities, totals, concentration gradients and force, tape[20][ny][nx].
-constexpr int kBlockX = 32, kBlockY = 16;
-static_assert(kBlockX - 4 == kBlockCols && kBlockY - 4 == kBlockRows && kBlockX * kBlockY == kBlockThreads,
-              "block plan and kernel agree");
+constexpr int kBlockX = 32;
+static_assert(kBlockX - 4 == kBlockCols, "block plan and kernel agree");
 
 template <typename C, int BX, int BY>
 struct alignas(16) BlockLds {
@@ -1522,52 +1521,62 @@ struct alignas(16) BlockLds {
 
 template <typename S, typename C, int BX, int BY, bool PT, bool TAPE = false>
 __global__ __launch_bounds__(BX * BY) __attribute__((amdgpu_waves_per_eu(2))) void k_block(
-    const S* __restrict__ fin, S* __restrict__ fout, const Instance* __restrict__ inst,
-    const Tile* __restrict__ tiles, uint32_t salt, const int64_t* __restrict__ step_dev,
-    double* __restrict__ tape = nullptr)
+    const S* __restrict__ fin, S* __restrict__ fout, BlockGrid bg, uint32_t salt, double* __restrict__ tape = nullptr)
 {
     static_assert(BX % 64 == 0 || 64 % BX == 0, "waves are whole tile rows");
     __shared__ BlockLds<C, BX, BY> L;
-    const Tile tl = tiles[blockIdx.x];
-    const KParams kp = inst[tl.inst].kp;
-    const int64_t off = inst[tl.inst].offset;
-    fin += off;
-    fout += off;
-    if constexpr (kRounds<S, C>) {
-        if (step_dev) salt = step_salt(*step_dev);
-    }
-    const int nx = kp.nx, ny = kp.ny, cols = tl.cols, rows = tl.rows;
-    const int64_t plane = kp.plane, pitch = kp.fpitch;
+    const KParams& kp = bg.kp;
+    const int nx = kp.nx, ny = kp.ny;
     const int t = threadIdx.x, tx = t % BX, ty = t / BX;
+    int x0, y0, cols, rows;
+    bg.block((int)blockIdx.x, x0, y0, cols, rows);
     const bool in1 = tx <= cols + 3 && ty <= rows + 3;
     const bool in2 = tx >= 1 && tx <= cols + 2 && ty >= 1 && ty <= rows + 2;
     const bool in3 = tx >= 2 && tx <= cols + 1 && ty >= 2 && ty <= rows + 1;
-    const int x = wrapi(tl.x0 - 2 + tx, nx), y = wrapi(tl.y0 - 2 + ty, ny);
+    // indices at most BX (BY) beyond the lattice: one addition or subtraction wraps them unless
+    // the lattice is smaller than that (integer division takes tens of instructions)
+    const bool wide = nx >= BX && ny >= BX;
+    auto wrapx = [&](int a) { return wide ? (a < 0 ? a + nx : (a >= nx ? a - nx : a)) : wrapi(a, nx); };
+    auto wrapy = [&](int a) { return wide ? (a < 0 ? a + ny : (a >= ny ? a - ny : a)) : wrapi(a, ny); };
+    // byte offsets: a lattice of blocks has at most kBlockMaxNodes nodes, 27 planes of them (in
+    // rows padded to 64) lie within 32 bits
+    const uint32_t plane = (uint32_t)kp.plane * (uint32_t)sizeof(S), pitch = (uint32_t)kp.fpitch * (uint32_t)sizeof(S);
+    const int x = wrapx(x0 - 2 + tx), y = wrapy(y0 - 2 + ty);
+    // 1. all loads at once: the pull's f_dag_i, and the c_k, V_0, V_1 of the nodes of the block
+    // and its ring of three, node (x0 - 3 + u, y0 - 3 + w) at cv[w][.][u], taken in turn by the
+    // lanes (at most NE each)
+    constexpr int CWM = BX + 2, CHM = BY + 2, NE = (CWM * CHM + BX * BY - 1) / (BX * BY);
+    S fq[9], cq[NE][7];
+    const uint32_t xs[3] = {(uint32_t)(x + 1 == nx ? 0 : x + 1) * (uint32_t)sizeof(S), (uint32_t)x * (uint32_t)sizeof(S),
+                            (uint32_t)(x == 0 ? nx - 1 : x - 1) * (uint32_t)sizeof(S)};  // by e_x + 1
+    const uint32_t ys[3] = {(uint32_t)(y + 1 == ny ? 0 : y + 1) * pitch, (uint32_t)y * pitch,
+                            (uint32_t)(y == 0 ? ny - 1 : y - 1) * pitch};  // by e_y + 1
+    int wu[NE];
+#pragma unroll
+    for (int m = 0; m < NE; ++m) {
+        const int e = t + m * (BX * BY), w = e / CWM, u = e - w * CWM;
+        wu[m] = u <= cols + 5 && w <= rows + 5 ? w * (9 * CWM) + u : -1;
+        const uint32_t o = (uint32_t)wrapy(y0 - 3 + (w <= rows + 5 ? w : 0)) * pitch +
+                           (uint32_t)wrapx(x0 - 3 + (u <= cols + 5 ? u : 0)) * (uint32_t)sizeof(S);
+#pragma unroll
+        for (int q = 0; q < 7; ++q) cq[m][q] = ld_at(fin, o + (uint32_t)(9 + q) * plane);
+    }
+#pragma unroll
+    for (int i = 0; i < 9; ++i) fq[i] = ld_at(fin, ys[EY[i] + 1] + xs[EX[i] + 1] + (uint32_t)i * plane);
     const StepConsts<C> K(kp);
-    // 1. the pull's f_dag_i (in flight while the c_k, V_k are staged)
-    S fq[9];
 #pragma unroll
-    for (int i = 0; i < 9; ++i) fq[i] = S(0);
-    if (in1) {
-        const int xs[3] = {wrapi(x + 1, nx), x, wrapi(x - 1, nx)};  // by e_x + 1
-        const int64_t ys[3] = {(int64_t)wrapi(y + 1, ny) * pitch, (int64_t)y * pitch,
-                               (int64_t)wrapi(y - 1, ny) * pitch};  // by e_y + 1
+    for (int m = 0; m < NE; ++m)
+        if (wu[m] >= 0) {
+            C* c = &L.cv[0][0][0] + wu[m];
+            C v[7];
 #pragma unroll
-        for (int i = 0; i < 9; ++i) fq[i] = fin[(int64_t)i * plane + ys[EY[i] + 1] + xs[EX[i] + 1]];
-    }
-    // node (x0 - 3 + u, y0 - 3 + w) at cv[w][.][u]
-    const int CW = cols + 6, CH = rows + 6;
-    for (int e = t; e < CW * CH; e += BX * BY) {
-        const int w = e / CW, u = e - w * CW;
-        const int64_t o = (int64_t)wrapi(tl.y0 - 3 + w, ny) * pitch + wrapi(tl.x0 - 3 + u, nx);
-        C v[7];
-#pragma unroll
-        for (int q = 0; q < 7; ++q) v[q] = C(fin[(int64_t)(9 + q) * plane + o]);
-#pragma unroll
-        for (int q = 0; q < 7; ++q) L.cv[w][q][u] = v[q];
-        L.cv[w][7][u] = fac_v2<C>(v[3], v[5]);
-        L.cv[w][8][u] = fac_v2<C>(v[4], v[6]);
-    }
+            for (int q = 0; q < 7; ++q) {
+                v[q] = C(cq[m][q]);
+                c[q * CWM] = v[q];
+            }
+            c[7 * CWM] = fac_v2<C>(v[3], v[5]);
+            c[8 * CWM] = fac_v2<C>(v[4], v[6]);
+        }
     __syncthreads();
     // 2. densities and totals: the source rows' groups (e_y = +1, 0, -1) as pull_row adds them
     C r0[3] = {C(1), C(1), C(1)}, f0[9];
@@ -1646,38 +1655,40 @@ __global__ __launch_bounds__(BX * BY) __attribute__((amdgpu_waves_per_eu(2))) vo
         C fd[9], ck[3], V[6], ux, uy, mxh, myh;
         collide_recolour<C, PT>(f0, r0, n, Fx, Fy, K, fd, ck, V, ux, uy, mxh, myh, Tn);
         NodeBits bits(((uint32_t)y * (uint32_t)nx + (uint32_t)x) * 27u ^ salt);
-        S* o = fout + (int64_t)y * pitch + x;
+        const uint32_t o = ys[1] + xs[1];
 #pragma unroll
-        for (int i = 0; i < 9; ++i) o[(int64_t)i * plane] = to_storage<S, C>(fd[i], bits);
+        for (int i = 0; i < 9; ++i) st_plain(fout, o + (uint32_t)i * plane, to_storage<S, C>(fd[i], bits));
 #pragma unroll
-        for (int k = 0; k < 3; ++k) o[(int64_t)(9 + k) * plane] = to_storage<S, C>(ck[k], bits);
+        for (int k = 0; k < 3; ++k) st_plain(fout, o + (uint32_t)(9 + k) * plane, to_storage<S, C>(ck[k], bits));
 #pragma unroll
-        for (int q = 0; q < 4; ++q) o[(int64_t)(12 + q) * plane] = to_storage<S, C>(V[q], bits);
+        for (int q = 0; q < 4; ++q) st_plain(fout, o + (uint32_t)(12 + q) * plane, to_storage<S, C>(V[q], bits));
     }
 }
 
-// The FP64 block step writing the adjoint's tape (Guo forcing).
-inline hipError_t tiles_block_tape(const void* fin, void* fout, const Instance* inst, const Tile* tiles,
-                                   int ntiles, double* tape, hipStream_t st)
+template <typename S, typename C, int BY, bool PT, bool TAPE = false>
+hipError_t block_launch(const void* fin, void* fout, const BlockGrid& bg, uint32_t salt, double* tape, hipStream_t st)
 {
-    constexpr int BX = kBlockX, BY = kBlockY;
-    hipLaunchKernelGGL((k_block<double, double, BX, BY, false, true>), dim3(ntiles), dim3(BX * BY), 0, st,
-                       (const double*)fin, (double*)fout, inst, tiles, 0u, (const int64_t*)nullptr, tape);
+    hipLaunchKernelGGL((k_block<S, C, kBlockX, BY, PT, TAPE>), dim3(bg.count), dim3(kBlockX * BY), 0, st, (const S*)fin,
+                       (S*)fout, bg, salt, tape);
     return hipGetLastError();
 }
 
-template <typename S, typename C>
-hipError_t tiles_block_any(const void* fin, void* fout, const Instance* inst, const Tile* tiles, int ntiles,
-                           uint32_t salt, const int64_t* step_dev, bool pt, hipStream_t st)
+// The FP64 block step writing the adjoint's tape (Guo forcing).
+inline hipError_t tiles_block_tape(const void* fin, void* fout, const BlockGrid& bg, double* tape, hipStream_t st)
 {
-    constexpr int BX = kBlockX, BY = kBlockY;
-    if (pt)
-        hipLaunchKernelGGL((k_block<S, C, BX, BY, true>), dim3(ntiles), dim3(BX * BY), 0, st, (const S*)fin,
-                           (S*)fout, inst, tiles, salt, step_dev);
-    else
-        hipLaunchKernelGGL((k_block<S, C, BX, BY, false>), dim3(ntiles), dim3(BX * BY), 0, st, (const S*)fin,
-                           (S*)fout, inst, tiles, salt, step_dev);
-    return hipGetLastError();
+    if (bg.lanes_y == kBlockYSmall)
+        return block_launch<double, double, kBlockYSmall, false, true>(fin, fout, bg, 0u, tape, st);
+    return block_launch<double, double, kBlockY, false, true>(fin, fout, bg, 0u, tape, st);
+}
+
+template <typename S, typename C>
+hipError_t tiles_block_any(const void* fin, void* fout, const BlockGrid& bg, uint32_t salt, bool pt, hipStream_t st)
+{
+    if (bg.lanes_y == kBlockYSmall)
+        return pt ? block_launch<S, C, kBlockYSmall, true>(fin, fout, bg, salt, nullptr, st)
+                  : block_launch<S, C, kBlockYSmall, false>(fin, fout, bg, salt, nullptr, st);
+    return pt ? block_launch<S, C, kBlockY, true>(fin, fout, bg, salt, nullptr, st)
+              : block_launch<S, C, kBlockY, false>(fin, fout, bg, salt, nullptr, st);
 }
 
 }  // namespace

@@ -693,6 +693,24 @@ def test_block_step_equals_march_bitwise(shape, forcing, precision):
     assert np.array_equal(fa, fb)
 
 
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "fp32_storage"])
+@pytest.mark.parametrize("shape", [(28, 4), (29, 5), (31, 32), (32, 31), (33, 129), (448, 64), (449, 64), (448, 68), (700, 37),
+                                   (301, 263), (1021, 1027), (16, 65535)])
+def test_block_grids_cover_the_lattice_bitwise(shape, precision):
+    """The block step's own grid (blocks of 28 x 4 nodes while there is at most one per compute
+    unit, 448 x 64 being 16 x 16 of them, else 28 x 12) at the edges of both kinds and of the
+    sides below which indices wrap by division, against the march, bit for bit."""
+    nx, ny = shape
+    rho = inputs.random_mixture(nx, ny, 5, tiny_fraction=0.0)
+    A = lbm3.Lattice(nx, ny, precision=precision).init(rho).set_steps_per_launch(1)
+    B = lbm3.Lattice(nx, ny, precision=precision).init(rho).set_steps_per_launch(1).set_tile(64, 0)
+    fa, fb = A.step(4).state(), B.step(4).state()
+    A.close()
+    B.close()
+    assert np.isfinite(fa).all()
+    assert np.array_equal(fa, fb)
+
+
 def _factored_planes(L):
     """The 16 stored planes of a stepped lattice, as [16, ny, nx] in their storage type."""
     ptr, eb, pl, pitch, nq = lbm3.lbm3_state_buffer(L.h)
