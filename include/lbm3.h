@@ -340,6 +340,11 @@ int lbm3d_destroy(lbm3d_t *h);
  * roofline figures are compared with.  EINVAL for NULL pointers or a bad size. */
 int lbm3_device_copy(void *dst, const void *src, int64_t nbytes, void *hip_stream);
 
+/* Workspaces of released handles (adjoint sweeps, staging buffers) are kept on their device for
+ * the next handle, at most 1/32 of its memory, and given back when an allocation of the
+ * library needs them.  This gives them back at once.  Safe from any thread; always LBM3_OK. */
+int lbm3_release_cached(void);
+
 #ifdef __cplusplus
 }
 #endif

@@ -760,10 +760,10 @@ void adjoint_release(lbm3* h)
 {
     if (h->adj_stream) (void)hipStreamSynchronize(h->adj_stream);
     if (h->adj_stream2) (void)hipStreamSynchronize(h->adj_stream2);
-    for (void* p : h->ckpt)
-        if (p) (void)hipFree(p);
+    if (!h->ckpt.empty()) (void)hipStreamSynchronize(h->stream);
+    for (void* p : h->ckpt) pool_free(p);
     h->ckpt.clear();
-    if (h->adj_ws) (void)hipFree(h->adj_ws);
+    pool_free(h->adj_ws);
     h->adj_ws = nullptr;
     h->adj_ws_bytes = 0;
     h->tape_valid = false;
@@ -788,12 +788,12 @@ static int ensure_ws(lbm3* h, size_t bytes)
 {
     if (h->adj_ws_bytes >= bytes) return LBM3_OK;
     if (h->adj_ws) {
-        (void)hipStreamSynchronize(h->stream);
-        (void)hipFree(h->adj_ws);
+        // (the sweep that used it has waited for its streams)
+        pool_free(h->adj_ws);
         h->adj_ws = nullptr;
         h->adj_ws_bytes = 0;
     }
-    hipError_t e = hipMalloc(&h->adj_ws, bytes);
+    hipError_t e = pool_malloc(&h->adj_ws, bytes);
     if (e != hipSuccess) return hip_fail(e, "hipMalloc(adjoint workspace)");
     h->adj_ws_bytes = bytes;
     return LBM3_OK;
@@ -844,7 +844,7 @@ int lbm3_adjoint_record(lbm3_t* h, int64_t nsteps, int32_t ckpt_every)
     const size_t bytesfac = (size_t)h->kp.fpitch * h->kp.ny * sizeof(double);
     h->ckpt.assign(nseg, nullptr);
     for (int64_t c = 0; c < nseg; ++c) {
-        hipError_t e = hipMalloc(&h->ckpt[c], c == 0 ? bytes27 : bytesfac);
+        hipError_t e = pool_malloc(&h->ckpt[c], c == 0 ? bytes27 : bytesfac);
         if (e != hipSuccess) {
             int rc = hip_fail(e, "hipMalloc(checkpoint)");
             adjoint_release(h);
@@ -924,10 +924,11 @@ int lbm3_adjoint(lbm3_t* h, const double* drho1_T, double dsigma[3], double* drh
                (size_t)nsig * 6 * sizeof(double) + N * sizeof(double) + sf_tiles.size() * sizeof(Tile);
     };
     // Two pipeline slots (the recompute of the next segment beside the reverse steps of the
-    // current one) on small lattices where the second slot fits; else one.
+    // current one) on small lattices where the second slot fits; else one, and one for a
+    // single segment, which has nothing to overlap with.
     size_t free_b = 0, total_b = 0;
     if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) free_b = 0;
-    int nslots = lbm3_adjoint_pipeline_slots(N, need_of(2), h->adj_ws_bytes, free_b);
+    int nslots = nseg == 1 ? 1 : lbm3_adjoint_pipeline_slots(N, need_of(2), h->adj_ws_bytes, free_b + pool_kept());
     int rc = ensure_ws(h, need_of(nslots));
     if (rc == LBM3_ENOMEM && nslots == 2) {
         nslots = 1;  // the second slot did not fit after all: the one-slot sweep needs half the tape

@@ -390,11 +390,11 @@ static int ensure_staging(lbm3* h, size_t doubles)
     if (h->staging_cap >= doubles) return LBM3_OK;
     if (h->staging) {
         (void)hipStreamSynchronize(h->stream);
-        (void)hipFree(h->staging);
+        pool_free(h->staging);
         h->staging = nullptr;
         h->staging_cap = 0;
     }
-    hipError_t e = hipMalloc((void**)&h->staging, doubles * sizeof(double));
+    hipError_t e = pool_malloc((void**)&h->staging, doubles * sizeof(double));
     if (e != hipSuccess) return hip_fail(e, "hipMalloc(staging)");
     h->staging_cap = doubles;
     return LBM3_OK;
@@ -629,7 +629,7 @@ int lbm3_destroy(lbm3_t* h)
     if (!h) return LBM3_OK;
     (void)hipStreamSynchronize(h->stream);
     free_state_pair(h->buf);
-    if (h->staging) (void)hipFree(h->staging);
+    pool_free(h->staging);
     if (h->partials) (void)hipFree(h->partials);
     if (h->obs_dev) (void)hipFree(h->obs_dev);
     if (h->obs_host) (void)hipHostFree(h->obs_host);

@@ -54,6 +54,13 @@ Prec prec_of(int precision);
 void default_tile(const KParams& kp, Prec prec, int* threads, int* rows);
 int check_rho_fields(const double* rho, const double* u, int64_t n);
 int upload_plan(lbm3* h);
+// Device memory that outlives its owner for the next one (lbm3_pool.hip): pool_free may keep a
+// block, so its owner has waited for every stream that uses it.  device_malloc is hipMalloc,
+// tried again without the kept blocks when memory runs out.
+hipError_t pool_malloc(void** p, size_t bytes);
+void pool_free(void* p);
+void pool_trim();
+size_t pool_kept();  // bytes kept on the current device
 void adjoint_release(lbm3* h);
 void adjoint_destroy(lbm3* h);  // adjoint_release plus the adjoint stream and event
 // Enqueues n steps; factored = false keeps the 27-population format (the adjoint's tape).

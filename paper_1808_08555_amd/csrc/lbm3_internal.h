@@ -116,6 +116,7 @@ void plan_blocks(int inst, int nx, int ny, int cmax, int rmax, std::vector<Tile>
 // The two state buffers of a step (read one, write the other) in one allocation, the second
 // an odd number of MiB after the first (see lbm3_plan.hip); buf[1] is not freed on its own.
 hipError_t alloc_state_pair(size_t bytes, void* buf[2]);
+hipError_t device_malloc(void** p, size_t bytes);  // lbm3_pool.hip
 void free_state_pair(void* buf[2]);
 // Rows per segment that fit the tile count to the resident workgroup slots.
 int auto_rows(int nx, int ny, int threads, int slots, int elem_bytes, int halo = 3);

@@ -121,7 +121,7 @@ hipError_t alloc_state_pair(size_t bytes, void* buf[2])
     const size_t off = (bytes + 2 * MiB - 1) / (2 * MiB) * (2 * MiB) + MiB;
     buf[0] = buf[1] = nullptr;
     void* base = nullptr;
-    hipError_t e = hipMalloc(&base, off + bytes);
+    hipError_t e = device_malloc(&base, off + bytes);
     if (e != hipSuccess) return e;
     buf[0] = base;
     buf[1] = (char*)base + off;

@@ -112,6 +112,7 @@ def lib():
             "lbm3_adjoint_pipeline_slots": (I, [ctypes.c_int64, ctypes.c_uint64, ctypes.c_uint64,
                                                 ctypes.c_uint64]),
             "lbm3_device_copy": (I, [_VP, _VP, ctypes.c_int64, _VP]),
+            "lbm3_release_cached": (I, []),
             "lbm3d_create": (I, [P, ctypes.c_int32, _VP, ctypes.POINTER(H)]),
             "lbm3d_create_lattice": (I, [P, ctypes.c_int32, ctypes.c_int32, _VP, ctypes.POINTER(H)]),
             "lbm3d_init_fields": (I, [H, _DP]),
@@ -274,6 +275,11 @@ def lbm3_state_buffer(h):
 def lbm3_device_copy(dst_ptr: int, src_ptr: int, nbytes: int, stream=None):
     _check(lib().lbm3_device_copy(dst_ptr, src_ptr, int(nbytes), _stream_handle(stream)),
            "lbm3_device_copy")
+
+
+def lbm3_release_cached():
+    """Gives the device workspaces that the library keeps for its next handles back to the driver."""
+    _check(lib().lbm3_release_cached(), "lbm3_release_cached")
 
 
 # ----------------------------------------------------------------- batched form

@@ -75,3 +75,40 @@ def test_autograd_second_backward_raises():
     out.sum().backward(retain_graph=True)
     with pytest.raises(RuntimeError):
         out.sum().backward()
+
+
+def test_repeated_gradients_reuse_workspaces_and_stay_equal():
+    """Workspaces kept from one run for the next: gradients of different sizes and inputs in
+    turn, on two streams and from two threads at once, equal those of runs that had to
+    allocate (bit for bit), also after the kept memory was given back."""
+    import threading
+    sigma = torch.tensor([0.006, 0.010, 0.012], dtype=torch.float64)
+
+    def grad(n, seed, steps):
+        rho = torch.from_numpy(np.ascontiguousarray(_janus(n, n + 5, n / 6 + seed)[0]))
+        s, r = sigma.clone().requires_grad_(), rho.requires_grad_()
+        out = ternary_run(s, r, steps, ckpt_every=4, tau=(0.8, 0.8, 0.8))
+        return [x.clone() for x in torch.autograd.grad((out ** 2).sum(), (s, r))]
+
+    cases = [(96, 1, 12), (128, 2, 8), (96, 3, 12), (128, 2, 8)]
+    fresh = []
+    for c in cases:
+        lbm3.lbm3_release_cached()
+        fresh.append(grad(*c))
+    for got, want in zip([grad(*c) for c in cases], fresh):
+        assert all(torch.equal(a, b) for a, b in zip(got, want))
+    both = [None, None]
+
+    def work(k):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            both[k] = [grad(*c) for c in cases]
+
+    ts = [threading.Thread(target=work, args=(k,)) for k in (0, 1)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    for r in both:
+        for got, want in zip(r, fresh):
+            assert all(torch.equal(a, b) for a, b in zip(got, want))
+    lbm3.lbm3_release_cached()
