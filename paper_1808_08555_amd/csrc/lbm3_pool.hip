@@ -111,9 +111,9 @@ try {
             return hipSuccess;
         }
     }
-    size_t free_b = 0, total_b = 0;
-    (void)hipMemGetInfo(&free_b, &total_b);
-    std::list<Block> node(1, Block{dev, nullptr, bytes, total_b / 32, true});
+    size_t total = 0;  // (smaller blocks are not kept)
+    if (bytes >= kLeast && hipDeviceTotalMem(&total, dev) != hipSuccess) total = 0;
+    std::list<Block> node(1, Block{dev, nullptr, bytes, total / 32, true});
     e = device_malloc(p, bytes);
     if (e != hipSuccess) return e;
     node.front().p = *p;

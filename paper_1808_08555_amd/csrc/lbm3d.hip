@@ -286,32 +286,32 @@ __device__ __forceinline__ void collide3(C rho, C itau, const C (&ft)[Q], const 
 // A workgroup of TX x TY lanes (lane t at tile column t % TX, tile row t / TX; each wave is
 // two whole tile rows) owns the output nodes [x0, x0 + cols) x [y0, y0 + rows) x
 // [z0, z0 + depth), cols <= TX - 4 and rows <= TY - 4.  Lane (tx, ty) sits on node column
-// (x0 - 2 + tx, y0 - 2 + ty) (wrapped).  Iteration j takes source plane s = z0 - 3 + j, two
+// (x0 - sx + tx, y0 - 2 + ty) (wrapped), sx = 2 or 3.  Iteration j takes source plane s = z0 - 3 + j, two
 // barriers:
-//   stage 1 (lanes 0 .. cols + 3, 0 .. rows + 3): the densities that plane s streams to planes
+//   stage 1 (lanes within two columns and rows of the owned ones): the densities that plane s streams to planes
 //            s + 1, s and s - 1, from the lane's f_dag_i(x - e_i) of plane s and the c_k, V_k of
 //            plane s in LDS (one ring of nodes beyond the lanes').  sum_i w_i e_i . V_k(x - e_i)
 //            is plane_div of V_k.  Plane s - 1 is then complete; its c_k go into a
 //            three-plane LDS ring.
-//   stage 2, plane s - 2 (lanes 1 .. cols + 2, 1 .. rows + 2): grad c_k (Eq. 12) from the ring,
+//   stage 2, plane s - 2 (lanes within one): grad c_k (Eq. 12) from the ring,
 //            stress into LDS, V_k; the owned nodes store c_k, V_0, V_1.  The next plane's c_k,
 //            V_k go into LDS.
-//   stage 3, plane s - 3 (lanes 2 .. cols + 1, 2 .. rows + 1): the stress of plane s - 2 completes
+//   stage 3, plane s - 3 (the owned nodes' lanes): the stress of plane s - 2 completes
 //            F = div T; collision, f_dag_i stored.
-// The totals f_i = f_dag_i(x - e_i) (the c_k sum to 1 and the V_k to 0) are not kept from
-// stage 1 to stage 3, three iterations later: each owning lane loads its Q values again.
-// Holding them would take 4 Q values per node (three planes waiting and one arriving), more
-// than registers and LDS have.
+// The totals f_i = f_dag_i(x - e_i) (the c_k sum to 1 and the V_k to 0) are used in stage 3,
+// three iterations later.  Each owning lane keeps in LDS those of as many links as fit
+// (Hold3: 9 of 19 in FP64, 16 with FP32 storage, 14 in FP32) and loads the others again: all
+// would take 4 Q values per node (three planes waiting and one arriving), more than registers
+// and LDS have.  Loading all again cost, D3Q19 128^3: FP64 344 us a step against 325, FP32 storage
+// 242 against 226, FP32 199 against 180.
 // Global loads are issued up to an iteration before their use, into the registers that their
 // previous values have just left (D3Q27 in FP64 issues its f_dag_i after stage 2, so that
 // they are not in registers beside stage 2's: no spills, 735 -> 462 us at 128^3).
-// What bounds it: memory.  At 128^3 in FP64 a D3Q19 step moves 1.7 GB between L2 and the
-// memory behind it (2.5x the state's bytes in reads: the second read of the f_dag_i and the
-// halos that L2 misses; 1.03x in writes) at 4.8 TB/s; without its loads and stores it would
-// take 135 us.  Small boxes are bound by the loads' path through L1 (about 15 cycles per wave
-// instruction, whatever its width).  Measured against the march over 3 Q stored populations
-// that it replaced, us per step at 128^3 (FP64 / FP32 storage / FP32): D3Q19 723 / 413 / 338 ->
-// 345 / 242 / 198, D3Q27 1159 / 667 / 460 -> 462 / 301 / 263; D3Q19 48^3 FP64 63 -> 39.
+// What bounds it: memory.  A D3Q19 FP64 step at 128^3 takes 142 us without its loads and
+// stores; the stores alone add 109 us, the loads' path through L1 most of the rest (about 15
+// cycles per wave instruction, whatever its width).  Measured against the march over 3 Q stored
+// populations that it replaced, us per step at 128^3 (FP64 / FP32 storage / FP32): D3Q19 723 /
+// 413 / 338 -> 304 / 214 / 192, D3Q27 1159 / 667 / 460 -> 427 / 272 / 251; 48^3 D3Q19 FP64 63 -> 37.
 // Non-temporal stores made it 1-15% slower, non-temporal loads 10-20%.
 // The arithmetic of every node has a fixed order, so the result does not depend on the tile
 // shape.  With FP64 arithmetic two waves per SIMD fit in registers (512 lanes of 256), with
@@ -323,19 +323,54 @@ struct Tile3Shape {
     static constexpr int SX = TX - 2, SY = TY - 2;  // lanes that form the stress
 };
 
+// sx: columns from the tile's first lane to its first owned node, 2 or 3 (see plan3)
 struct Tile3 {
-    int32_t x0, y0, z0, cols, rows, depth;
+    int32_t x0, y0, z0, cols, rows, depth, sx;
+};
+
+// Links whose totals are kept in LDS from stage 1 to stage 3 (the others are loaded again): a
+// value of a link with e_z = -1 waits 2 iterations, with e_z = 0 three, with e_z = +1 four, so the
+// links are taken in that order while their slots (one storage-type value per owning lane
+// each) fit in what the 160 KB of LDS have left.
+template <typename S, typename C, int Q>
+struct Hold3 {
+    using Sh = Tile3Shape<sizeof(C)>;
+    static constexpr int lanes = (Sh::TX - 4) * (Sh::TY - 4);
+    static constexpr int base = (9 * Sh::CX * Sh::CY + 9 * Sh::T + 6 * Sh::SX * Sh::SY) * (int)sizeof(C);
+    static constexpr int slots = (160 * 1024 - 64 - base) / (lanes * (int)sizeof(S));
+    static constexpr int wait(int i) { return L3Z[i] + 3; }  // iterations
+    // first slot of link i, or -1
+    static constexpr int first(int i)
+    {
+        int n = 0;
+        for (int ez = -1; ez <= 1; ++ez)
+            for (int k = 0; k < Q; ++k) {
+                if (L3Z[k] != ez) continue;
+                const bool fits = n + ez + 3 <= slots;
+                if (k == i) return fits ? n : -1;
+                if (fits) n += ez + 3;
+            }
+        return -1;
+    }
+    static constexpr int used()
+    {
+        int n = 0;
+        for (int i = 0; i < Q; ++i) n += first(i) >= 0 ? wait(i) : 0;
+        return n;
+    }
 };
 
 // What a state holds: the three initial densities (FP64) or the factored values.
 enum class In3 : int { Rho = 0, Fac = 1 };
 
-template <typename C>
+template <typename S, typename C, int Q>
 struct alignas(16) March3Lds {
     using Sh = Tile3Shape<sizeof(C)>;
-    C cv[9][Sh::CX * Sh::CY];  // c_k, V_0, V_1 of the source plane
     C c[3][3][Sh::T];          // c_k of the new densities, by plane mod 3
+    C cv[9][Sh::CX * Sh::CY];  // c_k, V_0, V_1 of the source plane (lanes beyond the halo may read
+                               // one element before it)
     C T[6][Sh::SX * Sh::SY];   // stress of one plane
+    S held[Hold3<S, C, Q>::used()][Hold3<S, C, Q>::lanes];  // totals of the owned nodes
 };
 
 // The population of link i of a fluid at rest with density r, as a state in S holds it.
@@ -347,15 +382,17 @@ __device__ __forceinline__ C rest_pop(int i, double r)
 
 template <typename S, typename C, bool OBS, int Q, In3 IN, typename Off>
 __device__ __forceinline__ void march3(const void* __restrict__ in, const Geo3& g, const KParams& kp, const Tile3& tl,
-                                       S* __restrict__ out, March3Lds<C>& L, double (&acc)[8],
+                                       S* __restrict__ out, March3Lds<S, C, Q>& L, double (&acc)[8],
                                        double* __restrict__ rho_out, uint32_t salt)
 {
     using Sh = Tile3Shape<sizeof(C)>;
+    using Hold = Hold3<S, C, Q>;
     constexpr int TX = Sh::TX, T3 = Sh::T;
     const int t = threadIdx.x, tx = t % TX, ty = t / TX;
-    const bool in2 = tx >= 1 && tx <= tl.cols + 2 && ty >= 1 && ty <= tl.rows + 2;
-    const bool in3 = tx >= 2 && tx <= tl.cols + 1 && ty >= 2 && ty <= tl.rows + 1;
-    const int x = wrapi(tl.x0 - 2 + tx, g.nx), y = wrapi(tl.y0 - 2 + ty, g.ny);
+    const int sx = tl.sx;  // lane tx sits on column x0 - sx + tx
+    const bool in2 = tx >= sx - 1 && tx <= tl.cols + sx && ty >= 1 && ty <= tl.rows + 2;
+    const bool in3 = tx >= sx && tx < tl.cols + sx && ty >= 2 && ty <= tl.rows + 1;
+    const int x = wrapi(tl.x0 - sx + tx, g.nx), y = wrapi(tl.y0 - 2 + ty, g.ny);
     // byte offsets within a plane of the nine lateral neighbours, by 3 (e_y + 1) + e_x + 1
     Off lo[9];
     {
@@ -372,24 +409,30 @@ __device__ __forceinline__ void march3(const void* __restrict__ in, const Geo3& 
     // KiB past its address register, and the optimiser would otherwise take all three from
     // the start of LDS and hold the sums that do not fit in registers.
     typedef __attribute__((address_space(3))) C lds_t;
-    lds_t* cv = (lds_t*)&L.cv[0][0] + ((ty + 1) * Sh::CX + tx + 1);
+    lds_t* cv = (lds_t*)&L.cv[0][0] + ((ty + 1) * Sh::CX + tx + 3 - sx);
     lds_t* cl = (lds_t*)&L.c[0][0][0] + t;
     lds_t* Tl = (lds_t*)&L.T[0][0] + ((ty - 1) * Sh::SX + (tx - 1));
+    typedef __attribute__((address_space(3))) S held_t;
+    held_t* hl = (held_t*)&L.held[0][0] + ((ty - 2) * (Sh::TX - 4) + (tx - 2));
     constexpr int NC = Sh::CX * Sh::CY, NT = Sh::SX * Sh::SY;
     settle(cv);
     settle(cl);
     settle(Tl);
-    // The ring of nodes around the lanes': one more c_k, V_k for most lanes of the first and the
-    // last wave, which own no node (their tile rows are the halo's) and so load no totals.
+    settle(hl);
+    // The ring of nodes around the lanes': one more c_k, V_k for lanes of the first and, where it
+    // has sides, of the last wave, which own no node (their tile rows are the halo's) and so
+    // load no totals.
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const bool edge = wave == 0 || wave == T3 / 64 - 1;
+    const bool edge_cv = wave == 0 || (edge && sx == 2);
     const int e = wave == 0 ? t : t - (T3 - 128);  // 0 .. 127
+    const int cw = sx == 2 ? Sh::CX : TX;          // nodes of the ring's rows
     int ru, rw;
-    if (e < Sh::CX) ru = e, rw = 0;
-    else if (e < 2 * Sh::CX) ru = e - Sh::CX, rw = Sh::CY - 1;
-    else if (e < 2 * Sh::CX + Sh::TY) ru = 0, rw = e - 2 * Sh::CX + 1;
-    else ru = Sh::CX - 1, rw = e - 2 * Sh::CX - Sh::TY + 1;
-    const bool ring = edge && e < 2 * Sh::CX + 2 * Sh::TY && ru <= tl.cols + 5 && rw <= tl.rows + 5;
+    if (e < cw) ru = e, rw = 0;
+    else if (e < 2 * cw) ru = e - cw, rw = Sh::CY - 1;
+    else if (e < 2 * cw + Sh::TY) ru = 0, rw = e - 2 * cw + 1;
+    else ru = Sh::CX - 1, rw = e - 2 * cw - Sh::TY + 1;
+    const bool ring = edge_cv && e < 2 * cw + (sx == 2 ? 2 * Sh::TY : 0) && ru <= tl.cols + 5 && rw <= tl.rows + 5;
     Off ro = node_off3<S, Q, Off>((int64_t)wrapi(tl.y0 - 3 + rw, g.ny) * g.nx + wrapi(tl.x0 - 3 + ru, g.nx));
     lds_t* cr = (lds_t*)&L.cv[0][0] + rw * Sh::CX + ru;
     settle(cr);
@@ -416,7 +459,8 @@ __device__ __forceinline__ void march3(const void* __restrict__ in, const Geo3& 
 #pragma unroll
         for (int a = 0; a < 9; ++a) refresh(lo[a]);
 #pragma unroll
-        for (int i = 0; i < Q; ++i) v[i] = ld_value<S>(base[1 - L3Z[i]], lo[at(i)], i);
+        for (int i = 0; i < Q; ++i)
+            if (Hold::first(i) < 0) v[i] = ld_value<S>(base[1 - L3Z[i]], lo[at(i)], i);
     };
 
     C D0[3], D1[3], rA[3], rB[3], Fa[3], Fb[3], rhoA = C(1), itauA = C(1);
@@ -446,7 +490,7 @@ __device__ __forceinline__ void march3(const void* __restrict__ in, const Geo3& 
     auto load_next_cv = [&]() {
         const int s = sc.next();
         load_cv(s, lo[4], vc);
-        if (edge) load_cv(s, ro, vx);
+        if (edge_cv) load_cv(s, ro, vx);
     };
     if constexpr (IN == In3::Fac) {
         load_next_cv();
@@ -455,7 +499,8 @@ __device__ __forceinline__ void march3(const void* __restrict__ in, const Geo3& 
         load_next_cv();
     }
     __syncthreads();
-    int slot = 0;  // ring slot of plane s - 1
+    int slot = 0;        // ring slot of plane s - 1
+    int h2 = 0, h3 = 0, h4 = 0;  // j mod 2, 3, 4
 #pragma unroll 1
     for (int j = 0; j < J; ++j) {
         // the ring's planes s - 1, s - 2, s - 3
@@ -496,6 +541,20 @@ __device__ __forceinline__ void march3(const void* __restrict__ in, const Geo3& 
                 settle(P0[k]);
                 settle(D1[k]);
             }
+            if (in3) {
+                // the totals that waited come out, those of this plane go in
+                held_t* const h[3] = {hl + h2 * Hold::lanes, hl + h3 * Hold::lanes, hl + h4 * Hold::lanes};
+#pragma unroll
+                for (int i = 0; i < Q; ++i)
+                    if (Hold::first(i) >= 0) {
+                        held_t* const a = h[L3Z[i] + 1] + Hold::first(i) * Hold::lanes;
+                        vx[i] = *a;
+                        *a = vf[i];
+                    }
+            }
+            h2 ^= 1;
+            h3 = h3 == 2 ? 0 : h3 + 1;
+            h4 = (h4 + 1) & 3;
             if constexpr (!kLate) load_f(sf.next(), vf);
             __builtin_amdgcn_sched_barrier(0);
             C m[2], p[2], z[2];
@@ -658,7 +717,7 @@ __global__ __launch_bounds__((Tile3Shape<sizeof(C)>::T)) __attribute__((amdgpu_w
     static_assert(T3 % 64 == 0 && (2 * Sh::TX) % 64 == 0, "each wave is whole tile rows");
     static_assert(2 * Sh::CX + 2 * Sh::TY <= 128, "one lane of two waves per node of the outer ring");
     static_assert(sizeof(double) * 8 * (T3 / 64) <= sizeof(C) * 3 * 3 * T3, "c ring too small for the reduction");
-    __shared__ March3Lds<C> L;
+    __shared__ March3Lds<S, C, Q> L;
     const Tile3 tl = tiles[blockIdx.x];
     const int t = threadIdx.x;
     double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -814,6 +873,12 @@ static std::vector<Tile3> plan3(const Geo3& g, int slots, Prec prec)
             nseg = s;
         }
     }
+    // Where no tile has more than TX - 6 columns the lanes start one column earlier: they then
+    // cover every column whose c_k, V_k stage 1 reads, and the ring of nodes around the lanes'
+    // has no sides, whose nodes lie in a cache line each (D3Q19 FP64 128^3 325 -> 304 us, FP32
+    // storage 226 -> 214, 127^3 231 -> 216; FP32 127^3 188 -> 175, 96^3 78 -> 75, but 128^3 180 ->
+    // 192).  Tiles of both kinds side by side were slower (160^3, 27 and 26 columns: 384 -> 400).
+    const int sx = (g.nx + ntx - 1) / ntx <= TX - 6 ? 3 : 2;
     std::vector<Tile3> L;
     L.reserve((size_t)per_seg * nseg);
     for (int zs = 0; zs < nseg; ++zs)
@@ -823,6 +888,7 @@ static std::vector<Tile3> plan3(const Geo3& g, int slots, Prec prec)
                 split_even(g.nx, ntx, tx, t.x0, t.cols);
                 split_even(g.ny, nty, ty, t.y0, t.rows);
                 split_even(g.nz, nseg, zs, t.z0, t.depth);
+                t.sx = sx;
                 L.push_back(t);
             }
     const int T = (int)L.size(), nxcd = 8;
