@@ -178,20 +178,21 @@ int lbm3_derived(const lbm3_params *p, double X[3], double g[3], double nu[3]);
  * 256 or 512; each workgroup owns a strip of at most threads-6 columns) and rows
  * marched per workgroup (>= 1; 0 = chosen so that the number of workgroups fits
  * the device's resident slots).  Setting a shape keeps one-step launches on the
- * march (a lattice of at most 2^20 nodes otherwise takes them on blocks, see
+ * march (a small lattice otherwise takes them on blocks, see
  * lbm3_set_steps_per_launch).  Results do not depend on the shape (bitwise).
  * get_tile returns the march's shape, with the rows actually used. */
 int lbm3_set_tile(lbm3_t *h, int32_t threads, int32_t rows);
 int lbm3_get_tile(const lbm3_t *h, int32_t *threads, int32_t *rows);
 
 /* How many steps one launch advances in lbm3_step: 0 = chosen by size (two on
- * lattices of 2^19 nodes or more in FP64, of more than 2^20 in FP32 and FP32
- * storage), 1 = one, 2 = two where possible.  A two-step launch keeps the
+ * lattices of 13 x 2^16 nodes or more in FP64, of 2^19 or more with the perturbation
+ * operator, of 7 x 2^18 or more in FP32 and FP32 storage), 1 = one, 2 = two where possible.  A two-step launch keeps the
  * intermediate state on chip (in every precision; the first step of a state loaded
  * in 27-population form runs alone) and needs a tile width (lbm3_set_tile's
  * threads) of at most 256; otherwise, and for the odd last step, a one-step launch
- * runs.  One-step launches on lattices of at most 2^20 nodes take two-dimensional
- * blocks of 28 x 12 nodes (no row march) unless lbm3_set_tile chose a shape.
+ * runs.  One-step launches on lattices of at most 2^20 nodes (7 x 2^18 in FP32 and
+ * FP32 storage) take two-dimensional blocks of 28 x 12 nodes, 28 x 4 on the smallest
+ * (no row march), unless lbm3_set_tile chose a shape.
  * Results do not depend on the mode or the kernel (bitwise).  EINVAL for another
  * mode. */
 int lbm3_set_steps_per_launch(lbm3_t *h, int32_t mode);

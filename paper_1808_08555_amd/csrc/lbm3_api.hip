@@ -239,11 +239,13 @@ int check_rho_fields(const double* rho, const double* u, int64_t n)
 // two-step pass exists, its own with the wider halo) and uploads them with the one-entry
 // instance table.  The two-step pass exists for every precision (64 to 256 threads); rows
 // requested explicitly apply to both lists.
-// Lattices up to this many nodes take their single steps on the block kernel (measured
-// against the row march's single step: 1.7-1.9x faster at 128^2 and 256^2, 1.4-1.5x at
-// 512^2 in FP32 and FP32 storage; at 1448^2 the march, 15.2k / 20.6k / 29.4k MLUPS in
-// FP64 / FP32 storage / FP32, runs below the two-step pass anyway).
-constexpr int64_t kBlockMaxNodes = (int64_t)1 << 20;
+// Lattices up to this many nodes take their single steps on the block kernel, and in FP32 and
+// FP32 storage all of them.  The line is where the two state buffers outgrow the 256 MB
+// last-level cache: 2^20 nodes in FP64 (2^21 with the factored state in floats).  Below it the
+// block step reads what the step before left in that cache; beyond, its time per node rises by
+// half (FP64: 58.7 us at 1024^2, 82.3 us at 1200 x 1000, where the two-step pass takes 55.3 and
+// 55.0; FP32: 37.7 us at 1300 x 1200, 66.3 us at 1448^2, the pass 50.1 and 57.6).
+static int64_t block_max_nodes(Prec prec) { return prec == Prec::F64 ? (int64_t)1 << 20 : (int64_t)7 << 18; }
 
 int upload_plan(lbm3* h)
 {
@@ -253,15 +255,18 @@ int upload_plan(lbm3* h)
         rows = auto_rows(h->kp.nx, h->kp.ny, h->threads, device_slots(h->prec, h->threads), eb);
     std::vector<Tile> L, L2;
     plan_lattice(0, h->kp.nx, h->kp.ny, h->threads, rows, eb, L);
-    // The two-step pass halves the traffic per step but needs a 12-row warm-up per tile:
-    // it wins on large lattices.  Below, single steps on the block kernel win (measured,
-    // square compound droplets, block step vs two-step pass: FP64 12.0k vs 10.2k MLUPS at
-    // 512^2, 15.8k vs 16.5k at 768^2, 17.3k vs 20.8k at 1024^2; FP32 storage 17.7k vs 17.3k
-    // and FP32 31.2k vs 26.7k at 1024^2).  So pairs from 2^19 nodes in FP64 and above 2^20
-    // in FP32 and FP32 storage.  The pass's own default width: 64 columns below 768 (512^2
-    // FP64: +6% over 256), else 256 (FP64: 512 lanes, one step per wave group);
-    // lbm3_set_tile's width applies to both passes.
-    const int64_t min2 = h->prec == Prec::F64 ? (int64_t)1 << 19 : ((int64_t)1 << 20) + 1;
+    // The two-step pass halves the traffic per step but needs a 12-row warm-up per tile: it wins
+    // on large lattices.  Below, single steps on the block kernel win (us per step, block step
+    // and two-step pass: FP64 800^2 36.0 and 40.6, 880 x 900 42.5 and 44.4, 960^2 48.0 and 45.9;
+    // FP32 storage 1024^2 47.8 and 58.0, 1300 x 1200 69.1 and 74.1, 1448^2 95.0 and 87.9; FP32
+    // 1024^2 27.2 and 40.7, 1300 x 1200 37.7 and 50.1, 1448^2 66.3 and 57.6).  So pairs from
+    // 13 x 2^16 nodes in FP64 and from 7 x 2^18 in FP32 and FP32 storage.  In FP64 with the
+    // perturbation operator they stay from 2^19, the line that callers of that operator know
+    // (1024 x 512: 35.8 us, blocks 32.4; 960^2: 44.9 and 48.5).  The pass's own default width:
+    // 64 columns below 768 (512^2 FP64: +6% over 256), else 256 (FP64: 512 lanes, one step per wave group); lbm3_set_tile's width applies
+    // to both passes.
+    const bool pt = h->p.forcing == LBM3_FORCING_PERTURBATION;
+    const int64_t min2 = h->prec != Prec::F64 ? (int64_t)7 << 18 : (pt ? (int64_t)1 << 19 : (int64_t)13 << 16);
     const bool big = (int64_t)h->kp.nx * h->kp.ny >= min2;
     const bool want2 = h->pass_mode == 2 || (h->pass_mode == 0 && big);
     int t2 = h->tile_set ? h->threads : (h->kp.nx < 768 ? 64 : 256);
@@ -274,7 +279,7 @@ int upload_plan(lbm3* h)
     h->threads2 = t2;
     // Single steps of a small lattice go to the block kernel (no march warm-up), unless
     // lbm3_set_tile chose a march shape or steps-per-launch mode 2 asks for pairs.
-    h->blocks = !h->tile_set && h->pass_mode != 2 && (int64_t)h->kp.nx * h->kp.ny <= kBlockMaxNodes;
+    h->blocks = !h->tile_set && h->pass_mode != 2 && (int64_t)h->kp.nx * h->kp.ny <= block_max_nodes(h->prec);
     h->bgrid = block_grid(h->kp, device_cus());
     std::vector<Tile> T = xcd_order(L, 8), T2 = xcd_order(L2, 8);
     (void)hipStreamSynchronize(h->stream);

@@ -1538,8 +1538,8 @@ __global__ __launch_bounds__(BX * BY) __attribute__((amdgpu_waves_per_eu(2))) vo
     const bool wide = nx >= BX && ny >= BX;
     auto wrapx = [&](int a) { return wide ? (a < 0 ? a + nx : (a >= nx ? a - nx : a)) : wrapi(a, nx); };
     auto wrapy = [&](int a) { return wide ? (a < 0 ? a + ny : (a >= ny ? a - ny : a)) : wrapi(a, ny); };
-    // byte offsets: a lattice of blocks has at most kBlockMaxNodes nodes, 27 planes of them (in
-    // rows padded to 64) lie within 32 bits
+    // byte offsets: a lattice of blocks has at most 7 x 2^18 nodes and 65535 rows, whose 16 planes
+    // (in rows padded to 64) lie within 32 bits
     const uint32_t plane = (uint32_t)kp.plane * (uint32_t)sizeof(S), pitch = (uint32_t)kp.fpitch * (uint32_t)sizeof(S);
     const int x = wrapx(x0 - 2 + tx), y = wrapy(y0 - 2 + ty);
     // 1. all loads at once: the pull's f_dag_i, and the c_k, V_0, V_1 of the nodes of the block

@@ -711,6 +711,25 @@ def test_block_grids_cover_the_lattice_bitwise(shape, precision):
     assert np.array_equal(fa, fb)
 
 
+@pytest.mark.parametrize("precision,shape,steps", [("fp64", (851, 1001), 1), ("fp64", (852, 1000), 2), ("fp32", (1311, 1399), 1),
+                                                   ("fp32", (1312, 1400), 2), ("fp32_storage", (1311, 1399), 1),
+                                                   ("fp32_storage", (1312, 1400), 2), ("fp32_storage", (28, 65535), 1)])
+def test_default_launch_at_its_size_limits_equals_the_march(precision, shape, steps):
+    """On either side of the node counts from which two steps go into a launch by default
+    (13 x 2^16 in FP64, 7 x 2^18 otherwise): the chosen launch, and its state against the
+    one-step march, bit for bit."""
+    nx, ny = shape
+    rho = inputs.random_mixture(nx, ny, 6, tiny_fraction=0.0)
+    A = lbm3.Lattice(nx, ny, precision=precision).init(rho)
+    B = lbm3.Lattice(nx, ny, precision=precision).init(rho).set_steps_per_launch(1).set_tile(64, 0)
+    assert lbm3.lbm3_get_pair_launch(A.h)[0] == steps
+    fa, fb = A.step(5).state(), B.step(5).state()
+    A.close()
+    B.close()
+    assert np.isfinite(fa).all()
+    assert np.array_equal(fa, fb)
+
+
 def _factored_planes(L):
     """The 16 stored planes of a stepped lattice, as [16, ny, nx] in their storage type."""
     ptr, eb, pl, pitch, nq = lbm3.lbm3_state_buffer(L.h)
