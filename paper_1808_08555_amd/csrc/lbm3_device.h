@@ -70,6 +70,30 @@ __device__ __forceinline__ void st_plain(T* base, unsigned byte_off, T v)
     *(gT*)(b + byte_off) = v;
 }
 
+// A per-lane byte offset the optimiser must take as new: left alone, it widens the offset to 64
+// bits outside the loop and every access takes a 64-bit vector addition.
+__device__ __forceinline__ void refresh(uint32_t& o) { asm volatile("" : "+v"(o)); }
+
+// Access at a scalar base address (pinned there: plane offsets hoisted out of a loop end up in
+// vector registers, at four instructions per access) plus a 32-bit lane offset.  Stores are
+// non-temporal, as st_at's.
+template <typename T>
+__device__ __forceinline__ T ld_sbase(uint64_t& base, uint32_t byte_off)
+{
+    typedef const __attribute__((address_space(1))) char gchar;
+    typedef const __attribute__((address_space(1))) T gT;
+    asm volatile("" : "+s"(base));
+    return *(gT*)((gchar*)base + byte_off);
+}
+template <typename T>
+__device__ __forceinline__ void st_sbase(uint64_t& base, uint32_t byte_off, T v)
+{
+    typedef __attribute__((address_space(1))) char gchar;
+    typedef __attribute__((address_space(1))) T gT;
+    asm volatile("" : "+s"(base));
+    __builtin_nontemporal_store(v, (gT*)((gchar*)base + byte_off));
+}
+
 // The plane stride as a value the optimiser must take afresh at each row: left alone, it
 // hoists the 18 or 27 plane offsets of a row out of the march loop and keeps them all live
 // in scalar registers, which then spill to vector lanes (FP32 storage: 91 spilled scalars,

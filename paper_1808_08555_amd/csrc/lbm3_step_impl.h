@@ -40,6 +40,8 @@
 // gradients and stress never leave the chip.
 #pragma once
 
+#include <type_traits>
+
 #include "lbm3_device.h"
 #include "lbm3_internal.h"
 #include "lbm3_rounding.h"
@@ -704,25 +706,195 @@ __device__ __forceinline__ void march(const S* __restrict__ fin, S* __restrict__
 // pulls that row in iteration j + 1 and outputs row y0 - 11 + j.
 template <typename C, int NT>
 struct alignas(16) PairLds {
-    C cA[3][3][NT];  // A: concentration ring (by row mod 3)
-    C tA[3][3][NT];  // A: stress ring
-    C xA[2][9][NT];  // A: c_k, V_k of the source row, double-buffered
+    C before[16 / sizeof(C)];  // lane 0's column - 1 of the first row lies here
+    C xA[9][NT];               // A: c_k, V_k of the source row
+    C cA[3][3][NT];            // A: concentration ring (by iteration mod 3)
+    C tA[3][3][NT];            // A: stress ring
     C cB[3][3][NT];
     C tB[3][3][NT];
-    C xB[18][NT];    // A's recoloured row: f_dag (0-8), c_k (9-11), V_k (12-17)
+    C xB[18][NT];              // A's recoloured row: f_dag (0-8), c_k (9-11), V_k (12-17)
 };
+
+// A lane's own views of the workgroup's LDS: three pointers at its column - 1 (kAt is its own
+// column), one for A's rows, one for B's, one for the exchange row.  Every access of a march is
+// one of them plus a constant within the 64 KB that an LDS instruction's offset reaches; they
+// are made anew at each use because the optimiser otherwise forms all the addresses before the
+// loop and holds them in registers (45 of 256 in FP64).
+template <typename C, int NT>
+struct PairLanes {
+    typedef __attribute__((address_space(3))) C lds_t;
+    static constexpr int kAt = 1;
+    static_assert(27 * NT * sizeof(C) <= 65536, "views within the reach of an offset");
+    lds_t *a, *b, *x;
+    __device__ PairLanes(PairLds<C, NT>& L, int t)
+        : a((lds_t*)&L.xA[0][0] + (t - kAt)), b((lds_t*)&L.cB[0][0][0] + (t - kAt)), x((lds_t*)&L.xB[0][0] + (t - kAt))
+    {
+    }
+    __device__ __forceinline__ static C* fresh(lds_t*& p)
+    {
+        asm volatile("" : "+v"(p));
+        return (C*)p;
+    }
+    struct Rows {
+        C (*x)[NT], (*c)[3][NT], (*T)[3][NT];
+    };
+    __device__ __forceinline__ static Rows rows_at(C* x, C* c)
+    {
+        return {reinterpret_cast<C (*)[NT]>(x), reinterpret_cast<C (*)[3][NT]>(c),
+                reinterpret_cast<C (*)[3][NT]>(c + 9 * NT)};
+    }
+    __device__ __forceinline__ Rows A()
+    {
+        C* p = fresh(a);
+        return rows_at(p, p + 9 * NT);
+    }
+    __device__ __forceinline__ Rows B()
+    {
+        C* p = fresh(b);
+        return rows_at(nullptr, p);
+    }
+    __device__ __forceinline__ C (*xB())[NT] { return reinterpret_cast<C (*)[NT]>(fresh(x)); }
+};
+
+// The rows a step holds between its stages: totals and densities of the three rows between its
+// pull and its output, their pair normals, and the partial sums of the rows above.  The march
+// loops are unrolled by three, so that a row stays in the registers it was formed in and every
+// ring slot is a constant (slot of row j is j % 3); rotating the rows instead took 40 moves of
+// the some 600 vector instructions per row and step.
+template <typename C>
+struct PairRows {
+    C f[3][9], r[3][3], n[3][6];
+    C d0r[3], d0f[6], d1r[3], d1f[3];
+    __device__ PairRows()
+    {
+#pragma unroll
+        for (int s = 0; s < 3; ++s) {
+#pragma unroll
+            for (int i = 0; i < 9; ++i) f[s][i] = C(0);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) r[s][k] = C(1);
+#pragma unroll
+            for (int q = 0; q < 6; ++q) n[s][q] = C(0);
+        }
+#pragma unroll
+        for (int k = 0; k < 3; ++k) d0r[k] = d1r[k] = d1f[k] = C(0);
+#pragma unroll
+        for (int q = 0; q < 6; ++q) d0f[q] = C(0);
+    }
+    // a source row's pulls, completing the row of slot P
+    template <int P, int NT, typename FD>
+    __device__ __forceinline__ void pull(FD f_dag, const C (*X)[NT], int t)
+    {
+        pull_row<C, NT>(f_dag, X, t, d0r, d0f, d1r, d1f, r[P], f[P]);
+    }
+    template <int P, int NT>
+    __device__ __forceinline__ void concentrations(C (*ring)[3][NT], int t) const
+    {
+        const C irho = recip((r[P][0] + r[P][1]) + r[P][2]);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) ring[P][k][t] = r[P][k] * irho;
+    }
+    // stress of the row before
+    template <int P, int NT>
+    __device__ __forceinline__ void stress(typename PairLanes<C, NT>::Rows L, int t, const StepConsts<C>& K)
+    {
+        constexpr int s1 = (P + 2) % 3, s2 = (P + 1) % 3;
+        C Txx, Txy, Tyy;
+#pragma unroll
+        for (int q = 0; q < 6; ++q) n[s1][q] = C(0);
+        stress_at_lane<C, NT>(L.c, P, s1, s2, t, r[s1], K, n[s1], Txx, Txy, Tyy);
+        L.T[s1][0][t] = Txx;
+        L.T[s1][1][t] = Txy;
+        L.T[s1][2][t] = Tyy;
+    }
+    // collision and recolouring of the row before that
+    template <int P, int NT, bool PT>
+    __device__ __forceinline__ void collide(const C (*tring)[3][NT], int t, const StepConsts<C>& K, C (&fd)[9],
+                                            C (&ck)[3], C (&V)[6]) const
+    {
+        constexpr int s1 = (P + 2) % 3, s2 = (P + 1) % 3;
+        C Fx, Fy, Tn[3], ux, uy, mxh, myh;
+        force_or_stress<C, NT, PT>(tring, P, s1, s2, t, Fx, Fy, Tn);
+        collide_recolour<C, PT>(f[s2], r[s2], n[s2], Fx, Fy, K, fd, ck, V, ux, uy, mxh, myh, Tn);
+    }
+};
+
+// iter(slot, j) for j = 0 .. J - 1, slot = j % 3 as a constant
+template <typename F>
+__device__ __forceinline__ void march_by_three(int J, F iter)
+{
+#pragma unroll 1
+    for (int j = 0; j < J;) {
+        iter(std::integral_constant<int, 0>(), j);
+        if (++j == J) break;
+        iter(std::integral_constant<int, 1>(), j);
+        if (++j == J) break;
+        iter(std::integral_constant<int, 2>(), j);
+        ++j;
+    }
+}
+
+// One source row read in two parts: its f_dag_i at this lane's pull columns, and its c_k, V_0,
+// V_1 at this lane's own column.
+template <typename S>
+struct SourceRows {
+    const S* fin;
+    int64_t pitch, plane;
+    uint32_t scol[3], xoff;  // byte offsets of the source columns for e_x = -1, 0, +1; own column
+    __device__ SourceRows(const S* f, const KParams& kp, int x)
+        : fin(f), pitch(kp.fpitch * (int64_t)sizeof(S)), plane(kp.plane * (int64_t)sizeof(S)),
+          scol{(uint32_t)wrapi(x + 1, kp.nx) * (uint32_t)sizeof(S), (uint32_t)x * (uint32_t)sizeof(S),
+               (uint32_t)wrapi(x - 1, kp.nx) * (uint32_t)sizeof(S)},
+          xoff((uint32_t)x * (uint32_t)sizeof(S))
+    {
+    }
+    __device__ __forceinline__ void f_dag(int s, S (&v)[9])
+    {
+        uint64_t b = uniform_u64(reinterpret_cast<uint64_t>(fin) + (uint64_t)(s * pitch));
+#pragma unroll
+        for (int e = 0; e < 3; ++e) refresh(scol[e]);
+#pragma unroll
+        for (int i = 0; i < 9; ++i, b += plane) v[i] = ld_sbase<S>(b, scol[EX[i] + 1]);
+    }
+    __device__ __forceinline__ void c_v(int s, S (&v)[kFacPlanes - 9])
+    {
+        uint64_t b = uniform_u64(reinterpret_cast<uint64_t>(fin) + (uint64_t)(s * pitch + 9 * plane));
+        refresh(xoff);
+#pragma unroll
+        for (int q = 0; q < kFacPlanes - 9; ++q, b += plane) v[q] = ld_sbase<S>(b, xoff);
+    }
+};
+
+// c_k, V_k of this lane's column of a source row to the neighbouring lanes
+template <typename S, typename C, int NT>
+__device__ __forceinline__ void publish_row(const S (&v)[kFacPlanes - 9], C (*X)[NT], int t)
+{
+#pragma unroll
+    for (int q = 0; q < kFacPlanes - 9; ++q) X[q][t] = C(v[q]);
+    X[7][t] = fac_v2<C>(C(v[3]), C(v[5]));
+    X[8][t] = fac_v2<C>(C(v[4]), C(v[6]));
+}
+
+// Values FIRST .. FIRST + N - 1 of an output row
+template <int FIRST, int N, typename S>
+__device__ __forceinline__ void store_row(S* fout, const KParams& kp, int y, uint32_t& xoff, const S (&v)[N])
+{
+    const int64_t plane = kp.plane * (int64_t)sizeof(S);
+    uint64_t b =
+        uniform_u64(reinterpret_cast<uint64_t>(fout) + (uint64_t)(y * (kp.fpitch * (int64_t)sizeof(S)) + FIRST * plane));
+    refresh(xoff);
+#pragma unroll
+    for (int q = 0; q < N; ++q, b += plane) st_sbase<S>(b, xoff, v[q]);
+}
 
 template <typename S, typename C, int NT, bool PT = false>
 __device__ __forceinline__ void pair_step_a(const S* __restrict__ fin, const KParams& kp, int x0, int y0,
-                                            int rows, int cols, PairLds<C, NT>& L, int t, uint32_t salt)
+                                            int rows, int cols, PairLds<C, NT>& lds, int t, uint32_t salt)
 {
+    PairLanes<C, NT> L(lds, t);
+    constexpr int at = L.kAt;
     const int nx = kp.nx, ny = kp.ny;
-    const int64_t plane = kp.plane;
     const int x = wrapi(x0 - 6 + t, nx);
-    const unsigned scol[3] = {(unsigned)wrapi(x + 1, nx) * (unsigned)sizeof(S),
-                              (unsigned)x * (unsigned)sizeof(S),
-                              (unsigned)wrapi(x - 1, nx) * (unsigned)sizeof(S)};
-    const unsigned xoff = (unsigned)x * (unsigned)sizeof(S);
     const bool a0 = t <= cols + 11;
     const bool a1 = (t >= 1) && (t <= cols + 10);
     const bool a2 = (t >= 2) && (t <= cols + 9);
@@ -730,10 +902,8 @@ __device__ __forceinline__ void pair_step_a(const S* __restrict__ fin, const KPa
     const StepConsts<C> K(kp);
     const int JA = rows + 10;
     const int J = rows + 11;  // one more iteration for B's last row
-    // A source row is loaded in two parts: its f_dag_i at this lane's pull columns (pulled by
-    // this lane in the next phase 0) and its c_k, V_0, V_1 at this lane's own column (published
-    // to the neighbouring lanes in phase 1).  Each part goes into its registers once their
-    // previous contents were used, so no copy of a prefetched row is kept (the registers freed
+    // Each part of a source row goes into its registers once their previous contents were
+    // used, so no copy of a prefetched row is kept (the registers freed
     // hold the 27 exchange fields pull_row reads once): the f_dag_i at the end of phase 0,
     // after the pull, and the c_k, V_k of the row after next at the start of phase 2, after
     // the publish, a whole iteration before they are published.  Loads issued at the start
@@ -742,97 +912,55 @@ __device__ __forceinline__ void pair_step_a(const S* __restrict__ fin, const KPa
     // V_k loads there against B's 2.2k, and B waited that difference at every iteration).
     // The prefetched values stay in the storage type until used.
     constexpr int NC = kFacPlanes - 9;
-    auto load_fd = [&](int s, S (&v)[9]) {
-        const int64_t rowo = (int64_t)s * kp.fpitch;
-#pragma unroll
-        for (int i = 0; i < 9; ++i) v[i] = ld_at(fin + ((int64_t)i * plane + rowo), scol[EX[i] + 1]);
-    };
-    auto load_cv = [&](int s, S (&v)[NC]) {
-        const int64_t rowo = (int64_t)s * kp.fpitch;
-#pragma unroll
-        for (int q = 0; q < NC; ++q) v[q] = ld_at(fin + ((int64_t)(9 + q) * plane + rowo), xoff);
-    };
-    auto publish = [&](const S (&v)[NC], int slot) {
-        if (a0) {
-#pragma unroll
-            for (int q = 0; q < 7; ++q) L.xA[slot][q][t] = C(v[q]);
-            L.xA[slot][7][t] = fac_v2<C>(C(v[3]), C(v[5]));
-            L.xA[slot][8][t] = fac_v2<C>(C(v[4]), C(v[6]));
-        }
-    };
-    C fA[9], fB[9], rA[3], rB[3], nB[6], d0r[3], d0f[6], d1r[3], d1f[3];
+    SourceRows<S> in(fin, kp, x);
+    PairRows<C> R;
     S vf[9], vc[NC];
 #pragma unroll
-    for (int i = 0; i < 9; ++i) {
-        fA[i] = fB[i] = C(0);
-        vf[i] = S(0);
-    }
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        rA[k] = rB[k] = C(1);
-        d0r[k] = d1r[k] = d1f[k] = C(0);
-    }
-#pragma unroll
-    for (int q = 0; q < 6; ++q) nB[q] = d0f[q] = C(0);
+    for (int i = 0; i < 9; ++i) vf[i] = S(0);
 #pragma unroll
     for (int q = 0; q < NC; ++q) vc[q] = S(1);
     RowCursor src(y0 - 6, ny);
     {
         const int r = src.next();
         if (a0) {
-            load_cv(r, vc);
-            load_fd(r, vf);
+            in.c_v(r, vc);
+            in.f_dag(r, vf);
         }
     }
 #pragma unroll 1
     for (int p = 0; p < 2; ++p) {
-        publish(vc, p);
+        if (a0) publish_row<S, C, NT>(vc, L.A().x, at);
         const int r = src.next();
-        if (a0) load_cv(r, vc);
+        if (a0) in.c_v(r, vc);
         __syncthreads();
-        C r_[3], f_[9];
-        if (a1) pull_row<C, NT>([&](int i) { return C(vf[i]); }, L.xA[p], t, d0r, d0f, d1r, d1f, r_, f_);
-        if (a0) load_fd(r, vf);
+        if (a1) R.template pull<0, NT>([&](int i) { return C(vf[i]); }, L.A().x, at);
+        if (a0) in.f_dag(r, vf);
+        __syncthreads();
     }
-    publish(vc, 0);
-    if (a0) load_cv(src.r, vc);  // for the loop's first publish
+    if (a0) {
+        publish_row<S, C, NT>(vc, L.A().x, at);
+        in.c_v(src.r, vc);  // for the loop's first publish
+    }
     __syncthreads();
-#pragma unroll 1
-    for (int j = 0; j < J; ++j) {
+    march_by_three(J, [&](auto slot, int j) {
+        constexpr int P = decltype(slot)::value;
         const bool live = j < JA;
-        const int s0 = j % 3, s1 = (j + 2) % 3, s2 = (j + 1) % 3;
-        C f0[9], r0[3];
-#pragma unroll
-        for (int i = 0; i < 9; ++i) f0[i] = C(0);
-#pragma unroll
-        for (int k = 0; k < 3; ++k) r0[k] = C(1);
         if (live) {
             const int r = src.next();
-            const bool more = a0 && j + 1 < JA;
-            if (a1) pull_row<C, NT>([&](int i) { return C(vf[i]); }, L.xA[j & 1], t, d0r, d0f, d1r, d1f, r0, f0);
-            if (more) load_fd(r, vf);
-            const C irho = recip((r0[0] + r0[1]) + r0[2]);
-#pragma unroll
-            for (int k = 0; k < 3; ++k) L.cA[s0][k][t] = r0[k] * irho;
+            if (a1) R.template pull<P, NT>([&](int i) { return C(vf[i]); }, L.A().x, at);
+            if (a0 && j + 1 < JA) in.f_dag(r, vf);
+            R.template concentrations<P, NT>(L.A().c, at);
         }
         __syncthreads();
-        C nA[6] = {C(0), C(0), C(0), C(0), C(0), C(0)};
-        if (live && j >= 2 && a2) {
-            C Txx, Txy, Tyy;
-            stress_at_lane<C, NT>(L.cA, s0, s1, s2, t, rA, K, nA, Txx, Txy, Tyy);
-            L.tA[s1][0][t] = Txx;
-            L.tA[s1][1][t] = Txy;
-            L.tA[s1][2][t] = Tyy;
-        }
-        if (j + 1 < JA) publish(vc, (j + 1) & 1);
+        if (live && j >= 2 && a2) R.template stress<P, NT>(L.A(), at, K);
+        if (a0 && j + 1 < JA) publish_row<S, C, NT>(vc, L.A().x, at);
         __syncthreads();
         // the c_k, V_k of the row src.next() returns in the next iteration
-        if (a0 && j + 2 < JA) load_cv(src.r, vc);
+        if (a0 && j + 2 < JA) in.c_v(src.r, vc);
         if (live && j >= 4 && a3) {
-            C Fx, Fy, fd[9], ck[3], V[6], ux, uy, mxh, myh;
-            C Tn[3];
-            force_or_stress<C, NT, PT>(L.tA, s0, s1, s2, t, Fx, Fy, Tn);
-            collide_recolour<C, PT>(fB, rB, nB, Fx, Fy, K, fd, ck, V, ux, uy, mxh, myh, Tn);
+            C fd[9], ck[3], V[6];
+            R.template collide<P, NT, PT>(L.A().T, at, K, fd, ck, V);
+            C(*xB)[NT] = L.xB();
             if constexpr (kRounds<S, C>) {
                 // the row as a single step would store it: each value rounded with the key of
                 // its node (row y0 - 7 + j, wrapped) and in store order, V_2 formed from the
@@ -840,40 +968,28 @@ __device__ __forceinline__ void pair_step_a(const S* __restrict__ fin, const KPa
                 const uint32_t yo = (uint32_t)wrapi(y0 - 7 + j, ny);
                 NodeBits bits((yo * (uint32_t)nx + (uint32_t)x) * 27u ^ salt);
 #pragma unroll
-                for (int i = 0; i < 9; ++i) L.xB[i][t] = C(to_storage<S, C>(fd[i], bits));
+                for (int i = 0; i < 9; ++i) xB[i][at] = C(to_storage<S, C>(fd[i], bits));
 #pragma unroll
-                for (int k = 0; k < 3; ++k) L.xB[9 + k][t] = C(to_storage<S, C>(ck[k], bits));
+                for (int k = 0; k < 3; ++k) xB[9 + k][at] = C(to_storage<S, C>(ck[k], bits));
                 C v4[4];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     v4[q] = C(to_storage<S, C>(V[q], bits));
-                    L.xB[12 + q][t] = v4[q];
+                    xB[12 + q][at] = v4[q];
                 }
-                L.xB[16][t] = fac_v2<C>(v4[0], v4[2]);
-                L.xB[17][t] = fac_v2<C>(v4[1], v4[3]);
+                xB[16][at] = fac_v2<C>(v4[0], v4[2]);
+                xB[17][at] = fac_v2<C>(v4[1], v4[3]);
             } else {
 #pragma unroll
-                for (int i = 0; i < 9; ++i) L.xB[i][t] = fd[i];
+                for (int i = 0; i < 9; ++i) xB[i][at] = fd[i];
 #pragma unroll
-                for (int k = 0; k < 3; ++k) L.xB[9 + k][t] = ck[k];
+                for (int k = 0; k < 3; ++k) xB[9 + k][at] = ck[k];
 #pragma unroll
-                for (int q = 0; q < 6; ++q) L.xB[12 + q][t] = V[q];
+                for (int q = 0; q < 6; ++q) xB[12 + q][at] = V[q];
             }
         }
-#pragma unroll
-        for (int i = 0; i < 9; ++i) {
-            fB[i] = fA[i];
-            fA[i] = f0[i];
-        }
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            rB[k] = rA[k];
-            rA[k] = r0[k];
-        }
-#pragma unroll
-        for (int q = 0; q < 6; ++q) nB[q] = nA[q];
         __syncthreads();
-    }
+    });
 }
 
 // B's rows are numbered by m: its stage 1 pulls source row y0 - 1 + m (from xB) and
@@ -882,116 +998,66 @@ __device__ __forceinline__ void pair_step_a(const S* __restrict__ fin, const KPa
 // iteration m + 7, one iteration after A recoloured its source row into xB.
 template <typename S, typename C, int NT, bool PT = false>
 __device__ __forceinline__ void pair_step_b(S* __restrict__ fout, const KParams& kp, int x0, int y0,
-                                            int rows, int cols, PairLds<C, NT>& L, int t, uint32_t salt)
+                                            int rows, int cols, PairLds<C, NT>& lds, int t, uint32_t salt)
 {
+    PairLanes<C, NT> L(lds, t);
+    constexpr int at = L.kAt;
     const int nx = kp.nx;
-    const int64_t plane = kp.plane;
     const int x = wrapi(x0 - 6 + t, nx);
-    const unsigned xoff = (unsigned)x * (unsigned)sizeof(S);
+    uint32_t xoff = (uint32_t)x * (uint32_t)sizeof(S);
     const bool b1 = (t >= 4) && (t <= cols + 7);
     const bool b2 = (t >= 5) && (t <= cols + 6);
     const bool b3 = (t >= 6) && (t <= cols + 5);
     const StepConsts<C> K(kp);
-    const int MB = rows + 3;  // last row index m
     const int J = rows + 11;
 
     // The f_dag_i of an output row are stored at the end of the next iteration's phase 1, its
     // c_k, V_k at once: B's phase 2 (collision and 16 stores) is the longest phase of the pair
     // and A waits for it at every iteration (measured 3.5k cycles against A's 2.1-2.5k).
     S fdp[9];
-    int64_t prow = -1;  // row offset of the f_dag_i held in fdp, or -1
-    auto store_fd = [&]() {
-        if (prow >= 0) {
 #pragma unroll
-            for (int i = 0; i < 9; ++i) st_at(fout + ((int64_t)i * plane + prow), xoff, fdp[i]);
-            prow = -1;
-        }
-    };
-    C fA[9], fB[9], rA[3], rB[3], nB[6], d0r[3], d0f[6], d1r[3], d1f[3];
-#pragma unroll
-    for (int i = 0; i < 9; ++i) fA[i] = fB[i] = C(0);
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        rA[k] = rB[k] = C(1);
-        d0r[k] = d1r[k] = d1f[k] = C(0);
-    }
-#pragma unroll
-    for (int q = 0; q < 6; ++q) nB[q] = d0f[q] = C(0);
+    for (int i = 0; i < 9; ++i) fdp[i] = S(0);
+    PairRows<C> R;
 
-    // A's three pre-roll barriers
+    // A's five pre-roll barriers
 #pragma unroll 1
-    for (int p = 0; p < 3; ++p) __syncthreads();
+    for (int p = 0; p < 5; ++p) __syncthreads();
 
-#pragma unroll 1
-    for (int j = 0; j < J; ++j) {
+    march_by_three(J, [&](auto slot, int j) {
+        constexpr int P = decltype(slot)::value;
         const int m = j - 7;
-        const bool live = m >= -2 && m <= MB;
-        const int s0 = (m + 6) % 3, s1 = (m + 8) % 3, s2 = (m + 7) % 3;
         // phase 0: stage 1 of row m from A's row in xB
-        C f0[9], r0[3];
-#pragma unroll
-        for (int i = 0; i < 9; ++i) f0[i] = C(0);
-#pragma unroll
-        for (int k = 0; k < 3; ++k) r0[k] = C(1);
-        if (live) {
-            if (b1)
-                pull_row<C, NT>([&](int i) { return L.xB[i][t - EX[i]]; }, L.xB + 9, t, d0r, d0f, d1r, d1f,
-                                r0, f0);
-            if (m >= 0) {
-                const C irho = recip((r0[0] + r0[1]) + r0[2]);
-#pragma unroll
-                for (int k = 0; k < 3; ++k) L.cB[s0][k][t] = r0[k] * irho;
+        if (m >= -2) {
+            if (b1) {
+                const C(*xB)[NT] = L.xB();
+                R.template pull<P, NT>([&](int i) { return xB[i][at - EX[i]]; }, xB + 9, at);
             }
+            if (m >= 0) R.template concentrations<P, NT>(L.B().c, at);
         }
         __syncthreads();
         // phase 1: stage 2
-        C nA[6] = {C(0), C(0), C(0), C(0), C(0), C(0)};
-        if (live && m >= 2 && b2) {
-            C Txx, Txy, Tyy;
-            stress_at_lane<C, NT>(L.cB, s0, s1, s2, t, rA, K, nA, Txx, Txy, Tyy);
-            L.tB[s1][0][t] = Txx;
-            L.tB[s1][1][t] = Txy;
-            L.tB[s1][2][t] = Tyy;
-        }
-        store_fd();
+        if (m >= 2 && b2) R.template stress<P, NT>(L.B(), at, K);
+        if (m >= 5 && b3) store_row<0, 9, S>(fout, kp, y0 - 5 + m, xoff, fdp);
         __syncthreads();
-        // phase 2: stage 3, then row m enters the pipeline
-        if (live && m >= 4 && b3) {
+        // phase 2: stage 3
+        if (m >= 4 && b3) {
             const int yo = y0 - 4 + m;
-            C Fx, Fy, fd[9], ck[3], V[6], ux, uy, mxh, myh;
-            C Tn[3];
-            force_or_stress<C, NT, PT>(L.tB, s0, s1, s2, t, Fx, Fy, Tn);
-            collide_recolour<C, PT>(fB, rB, nB, Fx, Fy, K, fd, ck, V, ux, uy, mxh, myh, Tn);
-            const int64_t orow = (int64_t)yo * kp.fpitch;
+            C fd[9], ck[3], V[6];
+            R.template collide<P, NT, PT>(L.B().T, at, K, fd, ck, V);
             NodeBits bits(((uint32_t)yo * (uint32_t)nx + (uint32_t)x) * 27u ^ salt);
             // rounded in store order, the f_dag_i first
 #pragma unroll
             for (int i = 0; i < 9; ++i) fdp[i] = to_storage<S, C>(fd[i], bits);
-            prow = orow;
+            S cv[kFacPlanes - 9];
 #pragma unroll
-            for (int k = 0; k < 3; ++k)
-                st_at(fout + ((int64_t)(9 + k) * plane + orow), xoff, to_storage<S, C>(ck[k], bits));
+            for (int k = 0; k < 3; ++k) cv[k] = to_storage<S, C>(ck[k], bits);
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                st_at(fout + ((int64_t)(12 + q) * plane + orow), xoff, to_storage<S, C>(V[q], bits));
-        }
-        if (live && m >= 0) {
-#pragma unroll
-            for (int i = 0; i < 9; ++i) {
-                fB[i] = fA[i];
-                fA[i] = f0[i];
-            }
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                rB[k] = rA[k];
-                rA[k] = r0[k];
-            }
-#pragma unroll
-            for (int q = 0; q < 6; ++q) nB[q] = nA[q];
+            for (int q = 0; q < 4; ++q) cv[3 + q] = to_storage<S, C>(V[q], bits);
+            store_row<9, kFacPlanes - 9, S>(fout, kp, yo, xoff, cv);
         }
         __syncthreads();
-    }
-    store_fd();
+    });
+    if (b3) store_row<0, 9, S>(fout, kp, y0 + rows - 1, xoff, fdp);
 }
 
 // The same two-step pass with each thread carrying both steps (used for FP32, whose two
@@ -1003,18 +1069,13 @@ __device__ __forceinline__ void pair_step_b(S* __restrict__ fout, const KParams&
 // A recolours row y0 - 7 + j, B consumes that row at once and outputs row y0 - 10 + j.
 template <typename C, int NT, bool PT = false>
 __device__ __forceinline__ void march2(const C* __restrict__ fin, C* __restrict__ fout,
-                                       const KParams& kp, int x0, int y0, int rows, int cols,
-                                       C (*cA)[3][NT], C (*tA)[3][NT], C (*xA)[9][NT],
-                                       C (*cB)[3][NT], C (*tB)[3][NT], C (*xB)[NT])
+                                       const KParams& kp, int x0, int y0, int rows, int cols, PairLds<C, NT>& lds)
 {
     const int nx = kp.nx, ny = kp.ny;
-    const int64_t plane = kp.plane;
     const int t = threadIdx.x;
+    PairLanes<C, NT> L(lds, t);
+    constexpr int at = L.kAt;
     const int x = wrapi(x0 - 6 + t, nx);
-    const unsigned scol[3] = {(unsigned)wrapi(x + 1, nx) * (unsigned)sizeof(C),
-                              (unsigned)x * (unsigned)sizeof(C),
-                              (unsigned)wrapi(x - 1, nx) * (unsigned)sizeof(C)};
-    const unsigned xoff = (unsigned)x * (unsigned)sizeof(C);
     const bool a0 = t <= cols + 11;
     const bool a1 = (t >= 1) && (t <= cols + 10);
     const bool a2 = (t >= 2) && (t <= cols + 9);
@@ -1024,181 +1085,95 @@ __device__ __forceinline__ void march2(const C* __restrict__ fin, C* __restrict_
     const bool b3 = (t >= 6) && (t <= cols + 5);
     const StepConsts<C> K(kp);
     const int JA = rows + 10;
+    constexpr int NC = kFacPlanes - 9;
 
-    auto load_fac = [&](int s, C (&v)[kFacPlanes]) {
-        const int64_t rowo = (int64_t)s * kp.fpitch;
-        const int64_t pl = fresh_stride(plane);
+    // A and the prefetched next source row (in two parts, each loaded once its registers are
+    // free, as in pair_step_a); B
+    SourceRows<C> in(fin, kp, x);
+    PairRows<C> A, B;
+    C vf[9], vc[NC];
 #pragma unroll
-        for (int i = 0; i < 9; ++i) v[i] = ld_at(fin + ((int64_t)i * pl + rowo), scol[EX[i] + 1]);
+    for (int i = 0; i < 9; ++i) vf[i] = C(0);
 #pragma unroll
-        for (int q = 9; q < kFacPlanes; ++q) v[q] = ld_at(fin + ((int64_t)q * pl + rowo), xoff);
-    };
-    auto publish_a = [&](const C (&v)[kFacPlanes], int slot) {
-        if (a0) {
-#pragma unroll
-            for (int q = 0; q < 7; ++q) xA[slot][q][t] = v[9 + q];
-            xA[slot][7][t] = fac_v2<C>(v[12], v[14]);
-            xA[slot][8][t] = fac_v2<C>(v[13], v[15]);
-        }
-    };
-
-    // A: pipeline, partial sums and the prefetched next source row
-    C fA_a[9], fB_a[9], rA_a[3], rB_a[3], nB_a[6], d0r_a[3], d0f_a[6], d1r_a[3], d1f_a[3], vn[kFacPlanes];
-    // B: pipeline and partial sums
-    C fA_b[9], fB_b[9], rA_b[3], rB_b[3], nB_b[6], d0r_b[3], d0f_b[6], d1r_b[3], d1f_b[3];
-#pragma unroll
-    for (int i = 0; i < 9; ++i) fA_a[i] = fB_a[i] = fA_b[i] = fB_b[i] = C(0);
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        rA_a[k] = rB_a[k] = rA_b[k] = rB_b[k] = C(1);
-        d0r_a[k] = d1r_a[k] = d0r_b[k] = d1r_b[k] = C(0);
-        d1f_a[k] = d1f_b[k] = C(0);
-    }
-#pragma unroll
-    for (int q = 0; q < 6; ++q) nB_a[q] = nB_b[q] = d0f_a[q] = d0f_b[q] = C(0);
-#pragma unroll
-    for (int q = 0; q < kFacPlanes; ++q) vn[q] = C(1);
+    for (int q = 0; q < NC; ++q) vc[q] = C(1);
 
     // A's pre-roll (as march() with first output row y0 - 3): source rows y0 - 6 and y0 - 5,
     // then row y0 - 4 published for the first iteration
     RowCursor src(y0 - 6, ny);  // source rows in load order: y0 - 6, y0 - 5, ...
     {
         const int r = src.next();
-        if (a0) load_fac(r, vn);
+        if (a0) {
+            in.c_v(r, vc);
+            in.f_dag(r, vf);
+        }
     }
 #pragma unroll 1
     for (int p = 0; p < 2; ++p) {
-        C v[kFacPlanes], r_[3], f_[9];
-#pragma unroll
-        for (int q = 0; q < kFacPlanes; ++q) v[q] = vn[q];
-        publish_a(v, p);
+        if (a0) publish_row<C, C, NT>(vc, L.A().x, at);
         const int r = src.next();
-        if (a0) load_fac(r, vn);
+        if (a0) in.c_v(r, vc);
         __syncthreads();
-        if (a1)
-            pull_row<C, NT>([&](int i) { return v[i]; }, xA[p], t, d0r_a, d0f_a, d1r_a, d1f_a, r_, f_);
+        if (a1) A.template pull<0, NT>([&](int i) { return vf[i]; }, L.A().x, at);
+        if (a0) in.f_dag(r, vf);
+        __syncthreads();
     }
-    publish_a(vn, 0);
+    if (a0) {
+        publish_row<C, C, NT>(vc, L.A().x, at);
+        in.c_v(src.r, vc);
+    }
     __syncthreads();
 
-#pragma unroll 1
-    for (int j = 0; j < JA; ++j) {
-        const int sa0 = j % 3, sa1 = (j + 2) % 3, sa2 = (j + 1) % 3;
+    march_by_three(JA, [&](auto slot, int j) {
+        constexpr int P = decltype(slot)::value;
         const int jb = j - 6;
-        const int sb0 = (jb + 6) % 3, sb1 = (jb + 8) % 3, sb2 = (jb + 7) % 3;
         // ---- A stage 1: densities of row y0 - 5 + j from source row y0 - 4 + j
-        C f0a[9], r0a[3];
-        {
-#pragma unroll
-            for (int i = 0; i < 9; ++i) f0a[i] = C(0);
-#pragma unroll
-            for (int k = 0; k < 3; ++k) r0a[k] = C(1);
-            C v[kFacPlanes];
-#pragma unroll
-            for (int q = 0; q < kFacPlanes; ++q) v[q] = vn[q];
-            const int r = src.next();  // row y0 - 3 + j
-            if (a0 && j + 1 < JA) load_fac(r, vn);
-            if (a1)
-                pull_row<C, NT>([&](int i) { return v[i]; }, xA[j & 1], t, d0r_a, d0f_a, d1r_a, d1f_a,
-                                r0a, f0a);
-            const C irho = recip((r0a[0] + r0a[1]) + r0a[2]);
-#pragma unroll
-            for (int k = 0; k < 3; ++k) cA[sa0][k][t] = r0a[k] * irho;
-        }
+        const int r = src.next();  // row y0 - 3 + j
+        if (a1) A.template pull<P, NT>([&](int i) { return vf[i]; }, L.A().x, at);
+        if (a0 && j + 1 < JA) in.f_dag(r, vf);
+        A.template concentrations<P, NT>(L.A().c, at);
         __syncthreads();
         // ---- A stage 2: stress of row y0 - 6 + j; publish the next source row
-        C nA_a[6] = {C(0), C(0), C(0), C(0), C(0), C(0)};
-        if (j >= 2 && a2) {
-            C Txx, Txy, Tyy;
-            stress_at_lane<C, NT>(cA, sa0, sa1, sa2, t, rA_a, K, nA_a, Txx, Txy, Tyy);
-            tA[sa1][0][t] = Txx;
-            tA[sa1][1][t] = Txy;
-            tA[sa1][2][t] = Tyy;
-        }
-        if (j + 1 < JA) publish_a(vn, (j + 1) & 1);
+        if (j >= 2 && a2) A.template stress<P, NT>(L.A(), at, K);
+        if (a0 && j + 1 < JA) publish_row<C, C, NT>(vc, L.A().x, at);
         __syncthreads();
+        if (a0 && j + 2 < JA) in.c_v(src.r, vc);
         // ---- A stage 3: recolour row y0 - 7 + j into B's exchange row
         if (j >= 4 && a3) {
-            C Fx, Fy, fd[9], ck[3], V[6], ux, uy, mxh, myh;
-            C Tn[3];
-            force_or_stress<C, NT, PT>(tA, sa0, sa1, sa2, t, Fx, Fy, Tn);
-            collide_recolour<C, PT>(fB_a, rB_a, nB_a, Fx, Fy, K, fd, ck, V, ux, uy, mxh, myh, Tn);
+            C fd[9], ck[3], V[6];
+            A.template collide<P, NT, PT>(L.A().T, at, K, fd, ck, V);
+            C(*xB)[NT] = L.xB();
 #pragma unroll
-            for (int i = 0; i < 9; ++i) xB[i][t] = fd[i];
+            for (int i = 0; i < 9; ++i) xB[i][at] = fd[i];
 #pragma unroll
-            for (int k = 0; k < 3; ++k) xB[9 + k][t] = ck[k];
+            for (int k = 0; k < 3; ++k) xB[9 + k][at] = ck[k];
 #pragma unroll
-            for (int q = 0; q < 6; ++q) xB[12 + q][t] = V[q];
+            for (int q = 0; q < 6; ++q) xB[12 + q][at] = V[q];
         }
-#pragma unroll
-        for (int i = 0; i < 9; ++i) {
-            fB_a[i] = fA_a[i];
-            fA_a[i] = f0a[i];
-        }
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            rB_a[k] = rA_a[k];
-            rA_a[k] = r0a[k];
-        }
-#pragma unroll
-        for (int q = 0; q < 6; ++q) nB_a[q] = nA_a[q];
         __syncthreads();
         // ---- B stage 1: pulls of source row y0 - 7 + j (the pre-roll for j = 4, 5)
-        C f0b[9], r0b[3];
-#pragma unroll
-        for (int i = 0; i < 9; ++i) f0b[i] = C(0);
-#pragma unroll
-        for (int k = 0; k < 3; ++k) r0b[k] = C(1);
-        if (j >= 4 && b1)
-            pull_row<C, NT>([&](int i) { return xB[i][t - EX[i]]; }, xB + 9, t, d0r_b, d0f_b, d1r_b, d1f_b,
-                            r0b, f0b);
-        if (jb >= 0) {
-            const C irho = recip((r0b[0] + r0b[1]) + r0b[2]);
-#pragma unroll
-            for (int k = 0; k < 3; ++k) cB[sb0][k][t] = r0b[k] * irho;
+        if (j >= 4 && b1) {
+            const C(*xB)[NT] = L.xB();
+            B.template pull<P, NT>([&](int i) { return xB[i][at - EX[i]]; }, xB + 9, at);
         }
+        if (jb >= 0) B.template concentrations<P, NT>(L.B().c, at);
         __syncthreads();
         // ---- B stage 2
-        C nA_b[6] = {C(0), C(0), C(0), C(0), C(0), C(0)};
-        if (jb >= 2 && b2) {
-            C Txx, Txy, Tyy;
-            stress_at_lane<C, NT>(cB, sb0, sb1, sb2, t, rA_b, K, nA_b, Txx, Txy, Tyy);
-            tB[sb1][0][t] = Txx;
-            tB[sb1][1][t] = Txy;
-            tB[sb1][2][t] = Tyy;
-        }
+        if (jb >= 2 && b2) B.template stress<P, NT>(L.B(), at, K);
         __syncthreads();
         // ---- B stage 3: recolour and store row y0 - 4 + jb
         if (jb >= 4 && b3) {
-            const int yo = y0 - 4 + jb;
-            C Fx, Fy, fd[9], ck[3], V[6], ux, uy, mxh, myh;
-            C Tn[3];
-            force_or_stress<C, NT, PT>(tB, sb0, sb1, sb2, t, Fx, Fy, Tn);
-            collide_recolour<C, PT>(fB_b, rB_b, nB_b, Fx, Fy, K, fd, ck, V, ux, uy, mxh, myh, Tn);
-            const int64_t orow = (int64_t)yo * kp.fpitch;
-            const int64_t pl = fresh_stride(plane);
+            C fd[9], ck[3], V[6];
+            B.template collide<P, NT, PT>(L.B().T, at, K, fd, ck, V);
+            C out[kFacPlanes];
 #pragma unroll
-            for (int i = 0; i < 9; ++i) st_at(fout + ((int64_t)i * pl + orow), xoff, fd[i]);
+            for (int i = 0; i < 9; ++i) out[i] = fd[i];
 #pragma unroll
-            for (int k = 0; k < 3; ++k) st_at(fout + ((int64_t)(9 + k) * pl + orow), xoff, ck[k]);
+            for (int k = 0; k < 3; ++k) out[9 + k] = ck[k];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) st_at(fout + ((int64_t)(12 + q) * pl + orow), xoff, V[q]);
+            for (int q = 0; q < 4; ++q) out[12 + q] = V[q];
+            store_row<0, kFacPlanes, C>(fout, kp, y0 - 4 + jb, in.xoff, out);
         }
-        if (jb >= 0) {
-#pragma unroll
-            for (int i = 0; i < 9; ++i) {
-                fB_b[i] = fA_b[i];
-                fA_b[i] = f0b[i];
-            }
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                rB_b[k] = rA_b[k];
-                rA_b[k] = r0b[k];
-            }
-#pragma unroll
-            for (int q = 0; q < 6; ++q) nB_b[q] = nA_b[q];
-        }
-    }
+    });
 }
 
 // Combination of two partials of observable field a: sums for the masses, momenta and kinetic
@@ -1397,15 +1372,11 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1))) void k_
     const C* __restrict__ fin, C* __restrict__ fout, const Instance* __restrict__ inst,
     const Tile* __restrict__ tiles)
 {
-    __shared__ alignas(16) C ringsA[2][3][3][NT];
-    __shared__ alignas(16) C xA[2][9][NT];
-    __shared__ alignas(16) C ringsB[2][3][3][NT];
-    __shared__ alignas(16) C xB[18][NT];
+    __shared__ PairLds<C, NT> lds;
     const Tile tl = tiles[blockIdx.x];
     const KParams kp = inst[tl.inst].kp;
     const int64_t off = inst[tl.inst].offset;
-    march2<C, NT, PT>(fin + off, fout + off, kp, tl.x0, tl.y0, tl.rows, tl.cols, ringsA[0], ringsA[1], xA,
-                  ringsB[0], ringsB[1], xB);
+    march2<C, NT, PT>(fin + off, fout + off, kp, tl.x0, tl.y0, tl.rows, tl.cols, lds);
 }
 
 // The two-step pass: FP64 arithmetic (FP64 or FP32 storage) wave-specialised (k_tiles2w,

@@ -87,7 +87,6 @@ int64_t zbytes3(int nx, int ny, int q)
 // Makes a lane's 32-bit offset a value the optimiser must take afresh from here: left alone, it
 // widens the offsets to 64 bits outside the march's loop, which doubles their registers and
 // replaces the scalar-base form of every access by a 64-bit vector address.
-__device__ __forceinline__ void refresh(uint32_t& o) { asm volatile("" : "+v"(o)); }
 __device__ __forceinline__ void refresh(uint64_t&) {}
 // Has x computed here: a sum that only the next iteration reads would be moved to the end of
 // this one, with everything that it is made of kept in registers till then.
