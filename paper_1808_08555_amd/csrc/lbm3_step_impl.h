@@ -1494,6 +1494,22 @@ int tiles_occupancy(int threads)
 // the march first).  With TAPE (FP64) the owned lanes also write the adjoint's tape as the
 // march does: densities, totals, concentration gradients and force, tape[20][ny][nx].
 constexpr int kBlockX = 32;
+// The tape of a step: none, stored as usual, or past the caches.  On a lattice whose two state
+// buffers and a step's tape (416 bytes per node) outgrow the 256 MB last-level cache, a tape left
+// in it drives out the state that the next step reads; below, the reverse steps find the last
+// tapes there (us per taped step and reverse step, as usual and past the caches: 512^2 24.1 + 41.4
+// and 26.2 + 40.5, 720^2 43.7 + 72.5 and 42.9 + 71.4, 1100 x 900 112 + 141 and 77.4 + 139).  The
+// march, of larger lattices, is 4 % slower with it.
+enum class Tape { None, Plain, Stream };
+constexpr int64_t kTapeStreamNodes = (int64_t)1 << 19;
+template <Tape TAPE>
+__device__ __forceinline__ void tape_store(double* p, double v)
+{
+    if constexpr (TAPE == Tape::Stream)
+        __builtin_nontemporal_store(v, p);
+    else
+        *p = v;
+}
 static_assert(kBlockX - 4 == kBlockCols, "block plan and kernel agree");
 
 template <typename C, int BX, int BY>
@@ -1503,7 +1519,7 @@ struct alignas(16) BlockLds {
     C T[BY][3][BX];           // stress of the lanes' nodes
 };
 
-template <typename S, typename C, int BX, int BY, bool PT, bool TAPE = false>
+template <typename S, typename C, int BX, int BY, bool PT, Tape TAPE = Tape::None>
 __global__ __launch_bounds__(BX * BY) __attribute__((amdgpu_waves_per_eu(2))) void k_block(
     const S* __restrict__ fin, S* __restrict__ fout, BlockGrid bg, uint32_t salt, double* __restrict__ tape = nullptr)
 {
@@ -1596,12 +1612,12 @@ __global__ __launch_bounds__(BX * BY) __attribute__((amdgpu_waves_per_eu(2))) vo
         for (int k = 0; k < 3; ++k) L.c[ty][k][tx] = r0[k] * irho;
     }
     const int64_t NN = (int64_t)nx * ny, on = (int64_t)y * nx + x;  // tape index
-    if constexpr (TAPE) {
+    if constexpr (TAPE != Tape::None) {
         if (in3) {
 #pragma unroll
-            for (int k = 0; k < 3; ++k) tape[k * NN + on] = double(r0[k]);
+            for (int k = 0; k < 3; ++k) tape_store<TAPE>(&tape[k * NN + on], double(r0[k]));
 #pragma unroll
-            for (int i = 0; i < 9; ++i) tape[(3 + i) * NN + on] = double(f0[i]);
+            for (int i = 0; i < 9; ++i) tape_store<TAPE>(&tape[(3 + i) * NN + on], double(f0[i]));
         }
     }
     __syncthreads();
@@ -1609,14 +1625,14 @@ __global__ __launch_bounds__(BX * BY) __attribute__((amdgpu_waves_per_eu(2))) vo
     C n[6] = {C(0), C(0), C(0), C(0), C(0), C(0)};
     if (in2) {
         C Txx, Txy, Tyy;
-        if constexpr (TAPE) {
+        if constexpr (TAPE != Tape::None) {
             stress_at_lane<C, BX>(L.c, ty + 1, ty, ty - 1, tx, r0, K, n, Txx, Txy, Tyy,
                                   [&](const C (&gx)[3], const C (&gy)[3]) {
                                       if (in3) {
 #pragma unroll
                                           for (int k = 0; k < 3; ++k) {
-                                              tape[(12 + 2 * k) * NN + on] = double(gx[k]);
-                                              tape[(13 + 2 * k) * NN + on] = double(gy[k]);
+                                              tape_store<TAPE>(&tape[(12 + 2 * k) * NN + on], double(gx[k]));
+                                              tape_store<TAPE>(&tape[(13 + 2 * k) * NN + on], double(gy[k]));
                                           }
                                       }
                                   });
@@ -1632,9 +1648,9 @@ __global__ __launch_bounds__(BX * BY) __attribute__((amdgpu_waves_per_eu(2))) vo
     if (in3) {
         C Fx, Fy, Tn[3];
         force_or_stress<C, BX, PT>(L.T, ty - 1, ty + 1, ty, tx, Fx, Fy, Tn);
-        if constexpr (TAPE) {
-            tape[18 * NN + on] = double(Fx);
-            tape[19 * NN + on] = double(Fy);
+        if constexpr (TAPE != Tape::None) {
+            tape_store<TAPE>(&tape[18 * NN + on], double(Fx));
+            tape_store<TAPE>(&tape[19 * NN + on], double(Fy));
         }
         C fd[9], ck[3], V[6], ux, uy, mxh, myh;
         collide_recolour<C, PT>(f0, r0, irho, n, Fx, Fy, K, fd, ck, V, ux, uy, mxh, myh, Tn);
@@ -1649,7 +1665,7 @@ __global__ __launch_bounds__(BX * BY) __attribute__((amdgpu_waves_per_eu(2))) vo
     }
 }
 
-template <typename S, typename C, int BY, bool PT, bool TAPE = false>
+template <typename S, typename C, int BY, bool PT, Tape TAPE = Tape::None>
 hipError_t block_launch(const void* fin, void* fout, const BlockGrid& bg, uint32_t salt, double* tape, hipStream_t st)
 {
     hipLaunchKernelGGL((k_block<S, C, kBlockX, BY, PT, TAPE>), dim3(bg.count), dim3(kBlockX * BY), 0, st, (const S*)fin,
@@ -1661,8 +1677,10 @@ hipError_t block_launch(const void* fin, void* fout, const BlockGrid& bg, uint32
 inline hipError_t tiles_block_tape(const void* fin, void* fout, const BlockGrid& bg, double* tape, hipStream_t st)
 {
     if (bg.lanes_y == kBlockYSmall)
-        return block_launch<double, double, kBlockYSmall, false, true>(fin, fout, bg, 0u, tape, st);
-    return block_launch<double, double, kBlockY, false, true>(fin, fout, bg, 0u, tape, st);
+        return block_launch<double, double, kBlockYSmall, false, Tape::Plain>(fin, fout, bg, 0u, tape, st);
+    if ((int64_t)bg.kp.nx * bg.kp.ny >= kTapeStreamNodes)
+        return block_launch<double, double, kBlockY, false, Tape::Stream>(fin, fout, bg, 0u, tape, st);
+    return block_launch<double, double, kBlockY, false, Tape::Plain>(fin, fout, bg, 0u, tape, st);
 }
 
 template <typename S, typename C>

@@ -169,6 +169,23 @@ def test_adjoint_block_pass_against_march_and_gpu_finite_differences(n):
         assert abs(ds[q] - fd) <= 1e-5 * abs(fd) + noise
 
 
+@pytest.mark.parametrize("shape", [(749, 699), (752, 700), (723, 725)])
+def test_adjoint_block_pass_equals_march_around_the_streamed_tape(shape):
+    """Lattices on both sides of 2^19 nodes, from which a taped block step writes its tape past
+    the caches, and one of odd sides just above it: the gradients against the march's, to the
+    rounding of the two passes (1e-12 of the largest for rho0, 1e-10 for sigma)."""
+    nx, ny = shape
+    y, x = np.mgrid[0:ny, 0:nx]
+    rho0 = inputs.rho_from_labels(((x // 37) + 2 * (y // 29)) % 3)
+    target = inputs.loss_target(rho0[0], seed=nx)
+    loss, ds, dr = gpu_gradient(rho0, target, SIGMA, (0.7, 0.8, 0.9), 4, 4)
+    loss_m, ds_m, dr_m = gpu_gradient(rho0, target, SIGMA, (0.7, 0.8, 0.9), 4, 4, tile=(256, 0))
+    assert loss == loss_m
+    assert np.isfinite(dr).all()
+    assert np.allclose(ds, ds_m, rtol=1e-10, atol=0)
+    assert np.abs(dr - dr_m).max() <= 1e-12 * np.abs(dr_m).max()
+
+
 def test_adjoint_above_the_overlap_size_against_gpu_finite_differences():
     """2048^2 (2^22 nodes: the sweep runs its segments one after the other in one slot,
     where smaller lattices overlap the next segment's recompute with the reverse steps),
