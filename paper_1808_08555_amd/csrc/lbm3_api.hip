@@ -239,12 +239,11 @@ int check_rho_fields(const double* rho, const double* u, int64_t n)
 // two-step pass exists, its own with the wider halo) and uploads them with the one-entry
 // instance table.  The two-step pass exists for every precision (64 to 256 threads); rows
 // requested explicitly apply to both lists.
-// Lattices up to this many nodes take their single steps on the block kernel, and in FP32 and
-// FP32 storage all of them.  The line is where the two state buffers outgrow the 256 MB
-// last-level cache: 2^20 nodes in FP64 (2^21 with the factored state in floats).  Below it the
-// block step reads what the step before left in that cache; beyond, its time per node rises by
-// half (FP64: 58.7 us at 1024^2, 82.3 us at 1200 x 1000, where the two-step pass takes 55.3 and
-// 55.0; FP32: 37.7 us at 1300 x 1200, 66.3 us at 1448^2, the pass 50.1 and 57.6).
+// Lattices up to this many nodes take their single steps on the block kernel.  The line is where
+// the two state buffers outgrow the 256 MB last-level cache: 2^20 nodes in FP64, 2^21 with the
+// factored state in floats.  Below it the block step reads what the step before left in that
+// cache; beyond, its time per node rises by half (FP64: 57.6 us at 1024^2, 75.9 us at 1200 x
+// 1000; FP32: 34.9 us at 1300 x 1200, 70.8 us at 1448^2).
 static int64_t block_max_nodes(Prec prec) { return prec == Prec::F64 ? (int64_t)1 << 20 : (int64_t)7 << 18; }
 
 int upload_plan(lbm3* h)
@@ -257,19 +256,22 @@ int upload_plan(lbm3* h)
     plan_lattice(0, h->kp.nx, h->kp.ny, h->threads, rows, eb, L);
     // The two-step pass halves the traffic per step but needs a 12-row warm-up per tile: it wins
     // on large lattices.  Below, single steps on the block kernel win (us per step, block step
-    // and two-step pass: FP64 800^2 36.0 and 40.6, 880 x 900 42.5 and 44.4, 960^2 48.0 and 45.9;
-    // FP32 storage 1024^2 47.8 and 58.0, 1300 x 1200 69.1 and 74.1, 1448^2 95.0 and 87.9; FP32
-    // 1024^2 27.2 and 40.7, 1300 x 1200 37.7 and 50.1, 1448^2 66.3 and 57.6).  So pairs from
-    // 13 x 2^16 nodes in FP64 and from 7 x 2^18 in FP32 and FP32 storage.  In FP64 with the
-    // perturbation operator they stay from 2^19, the line that callers of that operator know
-    // (1024 x 512: 35.8 us, blocks 32.4; 960^2: 44.9 and 48.5).  The pass's own default width:
-    // 64 columns below 768 (512^2 FP64: +6% over 256), else 256 (FP64: 512 lanes, one step per wave group); lbm3_set_tile's width applies
-    // to both passes.
-    const bool pt = h->p.forcing == LBM3_FORCING_PERTURBATION;
-    const int64_t min2 = h->prec != Prec::F64 ? (int64_t)7 << 18 : (pt ? (int64_t)1 << 19 : (int64_t)13 << 16);
-    const bool big = (int64_t)h->kp.nx * h->kp.ny >= min2;
+    // and two-step pass: FP64 640^2 25.2 and 27.8, 720 x 730 31.7 and 29.9, 1024^2 57.6 and 44.6;
+    // FP32 storage 1024^2 45.1 and 46.9, 1200 x 1000 50.8 and 47.9, 1448^2 98.2 and 71.3; FP32
+    // 1024^2 26.0 and 32.8, 1300 x 1200 34.9 and 40.7, 1448^2 70.8 and 50.2).  So pairs from
+    // 2^19 nodes in FP64, beyond 2^20 in FP32 storage and from 7 x 2^18 in FP32.  The pass's own
+    // default width: 64 columns below 768 of them, and below 1536 up to 2^20 nodes, where 256
+    // leave too few tiles or too short ones (FP64, 64 and 256: 800^2 33.5 and 35.1, 1024^2 44.6
+    // and 46.9, 2048 x 500 43.5 and 42.9, 4096 x 200 38.9 and 35.9, 1200 x 1000 51.1 and 47.8,
+    // 1448^2 86.1 and 75.2), else 256 (FP64: 512 lanes, one step per wave group);
+    // lbm3_set_tile's width applies to both passes.
+    const int64_t nodes = (int64_t)h->kp.nx * h->kp.ny;
+    const int64_t min2 = h->prec == Prec::F64    ? (int64_t)1 << 19
+                         : h->prec == Prec::F32S ? ((int64_t)1 << 20) + 1
+                                                 : (int64_t)7 << 18;
+    const bool big = nodes >= min2;
     const bool want2 = h->pass_mode == 2 || (h->pass_mode == 0 && big);
-    int t2 = h->tile_set ? h->threads : (h->kp.nx < 768 ? 64 : 256);
+    int t2 = h->tile_set ? h->threads : (h->kp.nx < 768 || (h->kp.nx < 1536 && nodes <= (int64_t)1 << 20) ? 64 : 256);
     const int slots2 = want2 ? device_slots_pair(h->prec, t2) : 0;
     if (slots2 > 0) {
         int rows2 = h->rows_request;
@@ -279,7 +281,7 @@ int upload_plan(lbm3* h)
     h->threads2 = t2;
     // Single steps of a small lattice go to the block kernel (no march warm-up), unless
     // lbm3_set_tile chose a march shape or steps-per-launch mode 2 asks for pairs.
-    h->blocks = !h->tile_set && h->pass_mode != 2 && (int64_t)h->kp.nx * h->kp.ny <= block_max_nodes(h->prec);
+    h->blocks = !h->tile_set && h->pass_mode != 2 && nodes <= block_max_nodes(h->prec);
     h->bgrid = block_grid(h->kp, device_cus());
     std::vector<Tile> T = xcd_order(L, 8), T2 = xcd_order(L2, 8);
     (void)hipStreamSynchronize(h->stream);

@@ -711,13 +711,14 @@ def test_block_grids_cover_the_lattice_bitwise(shape, precision):
     assert np.array_equal(fa, fb)
 
 
-@pytest.mark.parametrize("precision,shape,steps", [("fp64", (851, 1001), 1), ("fp64", (852, 1000), 2), ("fp32", (1311, 1399), 1),
-                                                   ("fp32", (1312, 1400), 2), ("fp32_storage", (1311, 1399), 1),
-                                                   ("fp32_storage", (1312, 1400), 2), ("fp32_storage", (28, 65535), 1)])
+@pytest.mark.parametrize("precision,shape,steps", [("fp64", (733, 715), 1), ("fp64", (733, 716), 2), ("fp64", (1001, 1048), 2),
+                                                   ("fp32", (1311, 1399), 1), ("fp32", (1312, 1400), 2),
+                                                   ("fp32_storage", (1023, 1025), 1), ("fp32_storage", (1025, 1024), 2),
+                                                   ("fp32", (28, 65535), 1)])
 def test_default_launch_at_its_size_limits_equals_the_march(precision, shape, steps):
     """On either side of the node counts from which two steps go into a launch by default
-    (13 x 2^16 in FP64, 7 x 2^18 otherwise): the chosen launch, and its state against the
-    one-step march, bit for bit."""
+    (2^19 in FP64, 2^20 in FP32 storage, 7 x 2^18 in FP32) and beyond the FP64 block step's: the
+    chosen launch, and its state against the one-step march, bit for bit."""
     nx, ny = shape
     rho = inputs.random_mixture(nx, ny, 6, tiny_fraction=0.0)
     A = lbm3.Lattice(nx, ny, precision=precision).init(rho)
