@@ -186,7 +186,8 @@ int lbm3_get_tile(const lbm3_t *h, int32_t *threads, int32_t *rows);
 
 /* How many steps one launch advances in lbm3_step: 0 = chosen by size (two on
  * lattices of 2^19 nodes or more in FP64, of more than 2^20 in FP32 storage, of
- * 7 x 2^18 or more in FP32), 1 = one, 2 = two where possible.  A two-step launch keeps the
+ * 7 x 2^18 or more in FP32, and on blocks of at most 22 x 22 nodes where those are at
+ * most one per compute unit), 1 = one, 2 = two where possible.  A two-step launch keeps the
  * intermediate state on chip (in every precision; the first step of a state loaded
  * in 27-population form runs alone) and needs a tile width (lbm3_set_tile's
  * threads) of at most 256; otherwise, and for the odd last step, a one-step launch

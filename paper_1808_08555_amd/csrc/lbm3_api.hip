@@ -283,6 +283,8 @@ int upload_plan(lbm3* h)
     // lbm3_set_tile chose a march shape or steps-per-launch mode 2 asks for pairs.
     h->blocks = !h->tile_set && h->pass_mode != 2 && nodes <= block_max_nodes(h->prec);
     h->bgrid = block_grid(h->kp, device_cus());
+    h->bgrid2 = block_grid2(h->kp, device_cus());
+    h->blocks2 = h->blocks && h->pass_mode == 0 && h->bgrid2.count > 0;
     std::vector<Tile> T = xcd_order(L, 8), T2 = xcd_order(L2, 8);
     (void)hipStreamSynchronize(h->stream);
     if (h->dtiles) (void)hipFree(h->dtiles);
@@ -308,7 +310,8 @@ int upload_plan(lbm3* h)
 
 // Enqueues n fused steps.  A state in the 27-population format (after init_fields or
 // set_state) is converted to the factored format by its first step; from the factored
-// format, pairs of steps go through the two-step pass where the plan has one.
+// format, pairs of steps go through the two-step pass where the plan has one, or the two-step
+// blocks of a small lattice.
 int step_handle(lbm3* h, int64_t n)
 {
     while (n > 0) {
@@ -318,6 +321,9 @@ int step_handle(lbm3* h, int64_t n)
         if (h->fmt == Fmt::FAC && n >= 2 && h->ntiles2 > 0) {
             e = launch_pair(h->prec, h->buf[h->cur], h->buf[h->cur ^ 1], h->dinst, h->dtiles2, h->ntiles2,
                             h->threads2, h->step, h->stream, pt);
+            done = 2;
+        } else if (h->fmt == Fmt::FAC && n >= 2 && h->blocks2) {
+            e = launch_block2(h->prec, h->buf[h->cur], h->buf[h->cur ^ 1], h->bgrid2, h->step, h->stream, pt);
             done = 2;
         } else if (h->fmt == Fmt::FAC && h->blocks) {
             e = launch_block(h->prec, h->buf[h->cur], h->buf[h->cur ^ 1], h->bgrid, h->step, h->stream, pt);
@@ -679,10 +685,11 @@ int lbm3_get_pair_launch(const lbm3_t* h, int32_t* steps, int32_t* threads, int3
         set_error("handle is NULL");
         return LBM3_EINVAL;
     }
-    const bool two = h->ntiles2 > 0;
-    if (steps) *steps = two ? 2 : 1;
-    if (threads) *threads = two ? (h->prec == Prec::F32 ? 1 : 2) * h->threads2 : 0;
-    if (workgroups) *workgroups = two ? h->ntiles2 : 0;
+    const bool two = h->ntiles2 > 0, blocks = !two && h->blocks2;
+    const int march_threads = (h->prec == Prec::F32 ? 1 : 2) * h->threads2;
+    if (steps) *steps = two || blocks ? 2 : 1;
+    if (threads) *threads = two ? march_threads : (blocks ? h->bgrid2.lanes_x * h->bgrid2.lanes_y : 0);
+    if (workgroups) *workgroups = two ? h->ntiles2 : (blocks ? h->bgrid2.count : 0);
     return LBM3_OK;
 }
 

@@ -27,6 +27,8 @@ struct lbm3 {
     int threads2 = 0;                   // its threads per workgroup
     bool blocks = false;                // single steps run on the block kernel, with this grid
     tcg::BlockGrid bgrid{};
+    bool blocks2 = false;               // pairs of steps run on the two-step block kernel, with this grid
+    tcg::BlockGrid bgrid2{};
     int pass_mode = 0;                  // steps per launch: 0 automatic, 1 one, 2 two
     bool tile_set = false;              // launch shape chosen by lbm3_set_tile
     double* staging = nullptr;          // device FP64 staging for host transfers

@@ -183,7 +183,8 @@ constexpr int kBlockY = 16, kBlockYSmall = 8;  // rows of lanes
 constexpr int kBlockCols = 28, kBlockRows = kBlockY - 4;
 struct BlockGrid {
     KParams kp;
-    int32_t lanes_y;     // kBlockY or kBlockYSmall
+    int32_t lanes_x;     // lanes of a workgroup
+    int32_t lanes_y;     // one step: kBlockY or kBlockYSmall
     int32_t count;       // blocks
     int32_t nbx;         // blocks per row of blocks
     uint32_t inv;        // ceil(2^32 / nbx): b / nbx = (b inv) >> 32 for b nbx < 2^32
@@ -204,17 +205,28 @@ struct BlockGrid {
 };
 // cus: compute units of the device
 BlockGrid block_grid(const KParams& kp, int cus);
+// Two steps per launch: the grid of the smallest blocks that are at most one per compute unit, or
+// none (count 0).
+BlockGrid block_grid2(const KParams& kp, int cus);
 hipError_t tiles_f64_block(const void* fin, void* fout, const BlockGrid& bg, uint32_t salt, bool pt,
                            hipStream_t stream);
 hipError_t tiles_f32_block(const void* fin, void* fout, const BlockGrid& bg, uint32_t salt, bool pt,
                            hipStream_t stream);
 hipError_t tiles_f32s_block(const void* fin, void* fout, const BlockGrid& bg, uint32_t salt, bool pt,
                             hipStream_t stream);
+hipError_t tiles_f64_block2(const void* fin, void* fout, const BlockGrid& bg, uint32_t salt_a, uint32_t salt_b, bool pt,
+                            hipStream_t stream);
+hipError_t tiles_f32_block2(const void* fin, void* fout, const BlockGrid& bg, uint32_t salt_a, uint32_t salt_b, bool pt,
+                            hipStream_t stream);
+hipError_t tiles_f32s_block2(const void* fin, void* fout, const BlockGrid& bg, uint32_t salt_a, uint32_t salt_b, bool pt,
+                            hipStream_t stream);
 // The FP64 block step (factored state in) that also writes the adjoint's tape, as
 // tiles_f64_tape does.
 hipError_t tiles_f64_block_tape(const void* fin, void* fout, const BlockGrid& bg, double* tape, hipStream_t stream);
 hipError_t launch_block(Prec prec, const void* fin, void* fout, const BlockGrid& bg, int64_t step, hipStream_t stream,
                         bool pt = false);
+hipError_t launch_block2(Prec prec, const void* fin, void* fout, const BlockGrid& bg, int64_t step, hipStream_t stream,
+                         bool pt = false);
 
 // Host-side helpers (lbm3_api.hip).
 void set_error(const char* fmt, ...);

@@ -79,14 +79,15 @@ void plan_blocks(int inst, int nx, int ny, int cmax, int rmax, std::vector<Tile>
 // then that of one workgroup, whose four waves have a SIMD each (64^2 FP64: 5.0 us a step
 // against 6.8 us with 16 rows, 128^2 5.3 against 7.0, FP32 4.4 against 5.3).  Beyond, 16 rows,
 // which compute fewer halo nodes (256^2 FP64: 8.0 us against 8.9, 1024^2 FP32 26.7 against 31.5).
-BlockGrid block_grid(const KParams& kp, int cus)
+static BlockGrid grid_of(const KParams& kp, int lanes_x, int lanes_y, int halo)
 {
+    const int cmax = lanes_x - 2 * halo, rmax = lanes_y - 2 * halo;
     BlockGrid g{};
     g.kp = kp;
-    g.nbx = (kp.nx + kBlockCols - 1) / kBlockCols;
-    auto rows_of = [&](int lanes_y) { return (kp.ny + lanes_y - 5) / (lanes_y - 4); };
-    g.lanes_y = (int64_t)g.nbx * rows_of(kBlockYSmall) <= cus ? kBlockYSmall : kBlockY;
-    const int nby = rows_of(g.lanes_y);
+    g.lanes_x = lanes_x;
+    g.lanes_y = lanes_y;
+    g.nbx = (kp.nx + cmax - 1) / cmax;
+    const int nby = (kp.ny + rmax - 1) / rmax;
     g.count = g.nbx * nby;
     g.inv = (uint32_t)((((uint64_t)1 << 32) + g.nbx - 1) / g.nbx);
     g.bw = kp.nx / g.nbx;
@@ -94,6 +95,29 @@ BlockGrid block_grid(const KParams& kp, int cus)
     g.bh = kp.ny / nby;
     g.rh = kp.ny % nby;
     return g;
+}
+
+BlockGrid block_grid(const KParams& kp, int cus)
+{
+    const BlockGrid g = grid_of(kp, kBlockCols + 4, kBlockYSmall, 2);
+    return g.count <= cus ? g : grid_of(kp, kBlockCols + 4, kBlockY, 2);
+}
+
+// A pass's time is that of one workgroup while there is at most one per compute unit, and grows
+// with the workgroup's lanes (us per step, blocks of 16 x 16, 32 x 16, 32 x 24 and 32 x 32 lanes
+// and single steps: FP64 96^2 3.8, 4.7, 6.5, 7.7 and 5.0; 160^2 6.5, 5.1, 6.7, 8.2 and 5.3; 256^2
+// 13.0, 9.6, 7.1, 8.7 and 7.9; 320^2 18.3, 11.9, 12.3, 9.0 and 10.8; FP32 96^2 3.2, 3.6, 4.3, 5.1
+// and 4.6; 256^2 8.2, 5.7, 5.1, 6.1 and 5.9; 320^2 11.1, 7.4, 6.6, 6.2 and 7.4).  More blocks than
+// compute units, and single steps, whose blocks hold fewer halo nodes, are faster: 384^2 FP64 12.9
+// at best and 11.7.
+BlockGrid block_grid2(const KParams& kp, int cus)
+{
+    const int shapes[4][2] = {{16, 16}, {32, 16}, {32, 24}, {32, 32}};
+    for (const auto& s : shapes) {
+        const BlockGrid g = grid_of(kp, s[0], s[1], 5);
+        if (g.count <= cus) return g;
+    }
+    return BlockGrid{};
 }
 
 std::vector<Tile> xcd_order(const std::vector<Tile>& L, int nxcd)

@@ -179,6 +179,18 @@ hipError_t launch_block(Prec prec, const void* fin, void* fout, const BlockGrid&
     return hipErrorInvalidValue;
 }
 
+hipError_t launch_block2(Prec prec, const void* fin, void* fout, const BlockGrid& bg, int64_t step, hipStream_t st,
+                         bool pt)
+{
+    const uint32_t sa = step_salt(step), sb = step_salt(step + 1);
+    switch (prec) {
+        case Prec::F64: return tiles_f64_block2(fin, fout, bg, sa, sb, pt, st);
+        case Prec::F32S: return tiles_f32s_block2(fin, fout, bg, sa, sb, pt, st);
+        case Prec::F32: return tiles_f32_block2(fin, fout, bg, sa, sb, pt, st);
+    }
+    return hipErrorInvalidValue;
+}
+
 hipError_t launch_advance_step(int64_t* step_dev, int64_t n, hipStream_t st)
 {
     hipLaunchKernelGGL(k_advance_step, dim3(1), dim3(64), 0, st, step_dev, n);

@@ -1519,6 +1519,112 @@ struct alignas(16) BlockLds {
     C T[BY][3][BX];           // stress of the lanes' nodes
 };
 
+// The geometry of a lane's loads.  Indices reach at most BX (BY) beyond the lattice: one addition
+// or subtraction wraps them unless the lattice is smaller than that (integer division takes tens
+// of instructions).  Byte offsets fit 32 bits: a lattice of blocks has at most 7 x 2^18 nodes and
+// 65535 rows, 16 planes each (in rows padded to 64).
+template <typename S, int REACH>
+struct BlockGeo {
+    int nx, ny;
+    bool wide;
+    uint32_t plane, pitch;
+    __device__ explicit BlockGeo(const KParams& kp)
+        : nx(kp.nx), ny(kp.ny), wide(kp.nx >= REACH && kp.ny >= REACH),
+          plane((uint32_t)kp.plane * (uint32_t)sizeof(S)), pitch((uint32_t)kp.fpitch * (uint32_t)sizeof(S))
+    {
+    }
+    __device__ __forceinline__ int wrapx(int a) const
+    {
+        return wide ? (a < 0 ? a + nx : (a >= nx ? a - nx : a)) : wrapi(a, nx);
+    }
+    __device__ __forceinline__ int wrapy(int a) const
+    {
+        return wide ? (a < 0 ? a + ny : (a >= ny ? a - ny : a)) : wrapi(a, ny);
+    }
+    // by e_x + 1, e_y + 1: the node at x - e_x (y - e_y)
+    __device__ __forceinline__ void columns(int x, uint32_t (&xs)[3]) const
+    {
+        xs[0] = (uint32_t)(x + 1 == nx ? 0 : x + 1) * (uint32_t)sizeof(S);
+        xs[1] = (uint32_t)x * (uint32_t)sizeof(S);
+        xs[2] = (uint32_t)(x == 0 ? nx - 1 : x - 1) * (uint32_t)sizeof(S);
+    }
+    __device__ __forceinline__ void rows(int y, uint32_t (&ys)[3]) const
+    {
+        ys[0] = (uint32_t)(y + 1 == ny ? 0 : y + 1) * pitch;
+        ys[1] = (uint32_t)y * pitch;
+        ys[2] = (uint32_t)(y == 0 ? ny - 1 : y - 1) * pitch;
+    }
+};
+
+// The c_k, V_0, V_1 of the nodes of a block of lanes and the ring around it, node (xl - 1 + u,
+// yl - 1 + w) at cv[w][.][u] for u < cw, w < ch (xl, yl: lane 0's node), taken in turn by the
+// lanes (at most NE each): loaded at once, then put into LDS with V_2.
+template <typename S, typename C, int BX, int BY>
+struct BlockStage {
+    static constexpr int CWM = BX + 2, CHM = BY + 2, NE = (CWM * CHM + BX * BY - 1) / (BX * BY);
+    S v[NE][7];
+    int at[NE];
+    __device__ __forceinline__ void load(const S* fin, const BlockGeo<S, (BX > BY ? BX : BY)>& g, int xl, int yl, int cw,
+                                         int ch, int t)
+    {
+#pragma unroll
+        for (int m = 0; m < NE; ++m) {
+            const int e = t + m * (BX * BY), w = e / CWM, u = e - w * CWM;
+            at[m] = u < cw && w < ch ? w * (9 * CWM) + u : -1;
+            const uint32_t o = (uint32_t)g.wrapy(yl - 1 + (w < ch ? w : 0)) * g.pitch +
+                               (uint32_t)g.wrapx(xl - 1 + (u < cw ? u : 0)) * (uint32_t)sizeof(S);
+#pragma unroll
+            for (int q = 0; q < 7; ++q) v[m][q] = ld_at(fin, o + (uint32_t)(9 + q) * g.plane);
+        }
+    }
+    __device__ __forceinline__ void publish(C* cv) const
+    {
+#pragma unroll
+        for (int m = 0; m < NE; ++m)
+            if (at[m] >= 0) {
+                C* c = cv + at[m];
+                C x[7];
+#pragma unroll
+                for (int q = 0; q < 7; ++q) {
+                    x[q] = C(v[m][q]);
+                    c[q * CWM] = x[q];
+                }
+                c[7 * CWM] = fac_v2<C>(x[3], x[5]);
+                c[8 * CWM] = fac_v2<C>(x[4], x[6]);
+            }
+    }
+};
+
+// Densities and totals of lane (tx, ty)'s node: the source rows' groups (e_y = +1, 0, -1) as
+// pull_row adds them, f_dag(i) the pulled f_dag_i.
+template <typename C, int CWM, typename FD>
+__device__ __forceinline__ void block_pull(FD f_dag, const C (*cv)[9][CWM], int tx, int ty, C (&r0)[3], C (&f0)[9])
+{
+    auto pull = [&](int i, C (&fk)[3]) {
+        const int u = tx + 1 - EX[i], w = ty + 1 - EY[i];
+        const C fdi = f_dag(i);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) fk[k] = recon<C>(cv[w][k][u], fdi, cv[w][3 + 2 * k][u], cv[w][4 + 2 * k][u], i);
+    };
+    auto group = [&](int a, int b, int c, C (&g)[3]) {
+        C fa[3], fb[3], fc[3];
+        pull(a, fa);
+        pull(b, fb);
+        pull(c, fc);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) g[k] = group_sum<C>(fa[k], fb[k], fc[k]);
+        f0[a] = (fa[0] + fa[1]) + fa[2];
+        f0[b] = (fb[0] + fb[1]) + fb[2];
+        f0[c] = (fc[0] + fc[1]) + fc[2];
+    };
+    C gp[3], gz[3], gm[3];
+    group(2, 5, 6, gp);
+    group(0, 1, 3, gz);
+    group(4, 7, 8, gm);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) r0[k] = (gp[k] + gz[k]) + gm[k];
+}
+
 template <typename S, typename C, int BX, int BY, bool PT, Tape TAPE = Tape::None>
 __global__ __launch_bounds__(BX * BY) __attribute__((amdgpu_waves_per_eu(2))) void k_block(
     const S* __restrict__ fin, S* __restrict__ fout, BlockGrid bg, uint32_t salt, double* __restrict__ tape = nullptr)
@@ -1533,80 +1639,28 @@ __global__ __launch_bounds__(BX * BY) __attribute__((amdgpu_waves_per_eu(2))) vo
     const bool in1 = tx <= cols + 3 && ty <= rows + 3;
     const bool in2 = tx >= 1 && tx <= cols + 2 && ty >= 1 && ty <= rows + 2;
     const bool in3 = tx >= 2 && tx <= cols + 1 && ty >= 2 && ty <= rows + 1;
-    // indices at most BX (BY) beyond the lattice: one addition or subtraction wraps them unless
-    // the lattice is smaller than that (integer division takes tens of instructions)
-    const bool wide = nx >= BX && ny >= BX;
-    auto wrapx = [&](int a) { return wide ? (a < 0 ? a + nx : (a >= nx ? a - nx : a)) : wrapi(a, nx); };
-    auto wrapy = [&](int a) { return wide ? (a < 0 ? a + ny : (a >= ny ? a - ny : a)) : wrapi(a, ny); };
-    // byte offsets: a lattice of blocks has at most 7 x 2^18 nodes and 65535 rows, whose 16 planes
-    // (in rows padded to 64) lie within 32 bits
-    const uint32_t plane = (uint32_t)kp.plane * (uint32_t)sizeof(S), pitch = (uint32_t)kp.fpitch * (uint32_t)sizeof(S);
-    const int x = wrapx(x0 - 2 + tx), y = wrapy(y0 - 2 + ty);
-    // 1. all loads at once: the pull's f_dag_i, and the c_k, V_0, V_1 of the nodes of the block
-    // and its ring of three, node (x0 - 3 + u, y0 - 3 + w) at cv[w][.][u], taken in turn by the
-    // lanes (at most NE each)
-    constexpr int CWM = BX + 2, CHM = BY + 2, NE = (CWM * CHM + BX * BY - 1) / (BX * BY);
-    S fq[9], cq[NE][7];
-    const uint32_t xs[3] = {(uint32_t)(x + 1 == nx ? 0 : x + 1) * (uint32_t)sizeof(S), (uint32_t)x * (uint32_t)sizeof(S),
-                            (uint32_t)(x == 0 ? nx - 1 : x - 1) * (uint32_t)sizeof(S)};  // by e_x + 1
-    const uint32_t ys[3] = {(uint32_t)(y + 1 == ny ? 0 : y + 1) * pitch, (uint32_t)y * pitch,
-                            (uint32_t)(y == 0 ? ny - 1 : y - 1) * pitch};  // by e_y + 1
-    int wu[NE];
-#pragma unroll
-    for (int m = 0; m < NE; ++m) {
-        const int e = t + m * (BX * BY), w = e / CWM, u = e - w * CWM;
-        wu[m] = u <= cols + 5 && w <= rows + 5 ? w * (9 * CWM) + u : -1;
-        const uint32_t o = (uint32_t)wrapy(y0 - 3 + (w <= rows + 5 ? w : 0)) * pitch +
-                           (uint32_t)wrapx(x0 - 3 + (u <= cols + 5 ? u : 0)) * (uint32_t)sizeof(S);
-#pragma unroll
-        for (int q = 0; q < 7; ++q) cq[m][q] = ld_at(fin, o + (uint32_t)(9 + q) * plane);
-    }
+    const BlockGeo<S, BX> geo(kp);
+    const uint32_t plane = geo.plane;
+    const int x = geo.wrapx(x0 - 2 + tx), y = geo.wrapy(y0 - 2 + ty);
+    uint32_t xs[3], ys[3];
+    geo.columns(x, xs);
+    geo.rows(y, ys);
+    // 1. all loads at once: the c_k, V_0, V_1 of the nodes of the block and its ring of three, and
+    // the pull's f_dag_i
+    BlockStage<S, C, BX, BY> stage;
+    S fq[9];
+    stage.load(fin, geo, x0 - 2, y0 - 2, cols + 6, rows + 6, t);
 #pragma unroll
     for (int i = 0; i < 9; ++i) fq[i] = ld_at(fin, ys[EY[i] + 1] + xs[EX[i] + 1] + (uint32_t)i * plane);
     const StepConsts<C> K(kp);
-#pragma unroll
-    for (int m = 0; m < NE; ++m)
-        if (wu[m] >= 0) {
-            C* c = &L.cv[0][0][0] + wu[m];
-            C v[7];
-#pragma unroll
-            for (int q = 0; q < 7; ++q) {
-                v[q] = C(cq[m][q]);
-                c[q * CWM] = v[q];
-            }
-            c[7 * CWM] = fac_v2<C>(v[3], v[5]);
-            c[8 * CWM] = fac_v2<C>(v[4], v[6]);
-        }
+    stage.publish(&L.cv[0][0][0]);
     __syncthreads();
-    // 2. densities and totals: the source rows' groups (e_y = +1, 0, -1) as pull_row adds them
+    // 2. densities and totals
     C r0[3] = {C(1), C(1), C(1)}, f0[9], irho = C(1);
 #pragma unroll
     for (int i = 0; i < 9; ++i) f0[i] = C(0);
     if (in1) {
-        auto pull = [&](int i, C (&fk)[3]) {
-            const int u = tx + 1 - EX[i], w = ty + 1 - EY[i];
-            const C fdi = C(fq[i]);
-#pragma unroll
-            for (int k = 0; k < 3; ++k)
-                fk[k] = recon<C>(L.cv[w][k][u], fdi, L.cv[w][3 + 2 * k][u], L.cv[w][4 + 2 * k][u], i);
-        };
-        auto group = [&](int a, int b, int c, C (&g)[3]) {
-            C fa[3], fb[3], fc[3];
-            pull(a, fa);
-            pull(b, fb);
-            pull(c, fc);
-#pragma unroll
-            for (int k = 0; k < 3; ++k) g[k] = group_sum<C>(fa[k], fb[k], fc[k]);
-            f0[a] = (fa[0] + fa[1]) + fa[2];
-            f0[b] = (fb[0] + fb[1]) + fb[2];
-            f0[c] = (fc[0] + fc[1]) + fc[2];
-        };
-        C gp[3], gz[3], gm[3];
-        group(2, 5, 6, gp);
-        group(0, 1, 3, gz);
-        group(4, 7, 8, gm);
-#pragma unroll
-        for (int k = 0; k < 3; ++k) r0[k] = (gp[k] + gz[k]) + gm[k];
+        block_pull<C, BX + 2>([&](int i) { return C(fq[i]); }, L.cv, tx, ty, r0, f0);
         irho = recip((r0[0] + r0[1]) + r0[2]);
 #pragma unroll
         for (int k = 0; k < 3; ++k) L.c[ty][k][tx] = r0[k] * irho;
@@ -1665,6 +1719,125 @@ __global__ __launch_bounds__(BX * BY) __attribute__((amdgpu_waves_per_eu(2))) vo
     }
 }
 
+// Two steps on two-dimensional blocks.  A single step of a small lattice is mostly its launch,
+// the round trip of its loads and its three barriers (64^2 FP64: 4.9 us, of which 0.8 us are
+// arithmetic); a second step on the same lanes adds arithmetic and barriers only (3.6 us per
+// step).  Lane (tx, ty) sits on node (x0 - 5 + tx, y0 - 5 + ty) and cols <= BX - 10, rows <= BY - 10.  Step A does
+// what k_block does and leaves its recoloured state, rounded as a store rounds it, in LDS: c_k
+// and V_k where its own input lay, the f_dag_i over its concentrations and stress.  Step B
+// pulls those three rings further in and stores.  The lanes' arithmetic is k_block's, so two
+// steps equal two launches bit for bit.
+template <typename C, int BX, int BY>
+struct alignas(16) Block2Lds {
+    C cv[BY + 2][9][BX + 2];
+    union {
+        C fd[9][BY][BX];
+        struct {
+            C c[BY][3][BX];
+            C T[BY][3][BX];
+        };
+    };
+};
+
+template <typename S, typename C, int BX, int BY, bool PT>
+__global__ __launch_bounds__(BX * BY) void k_block2(const S* __restrict__ fin, S* __restrict__ fout, BlockGrid bg,
+                                                    uint32_t salt_a, uint32_t salt_b)
+{
+    static_assert(BX % 64 == 0 || 64 % BX == 0, "waves are whole tile rows");
+    static_assert(BX >= BY, "the wrap's reach is BX");
+    __shared__ Block2Lds<C, BX, BY> L;
+    const KParams& kp = bg.kp;
+    const int nx = kp.nx;
+    const int t = threadIdx.x, tx = t % BX, ty = t / BX;
+    int x0, y0, cols, rows;
+    bg.block((int)blockIdx.x, x0, y0, cols, rows);
+    // lanes at least d within the lanes of the block
+    auto within = [&](int d) { return tx >= d && tx <= cols + 9 - d && ty >= d && ty <= rows + 9 - d; };
+    const BlockGeo<S, BX> geo(kp);
+    const int x = geo.wrapx(x0 - 5 + tx), y = geo.wrapy(y0 - 5 + ty);
+    uint32_t xs[3], ys[3];
+    geo.columns(x, xs);
+    geo.rows(y, ys);
+    const StepConsts<C> K(kp);
+    const uint32_t key = ((uint32_t)y * (uint32_t)nx + (uint32_t)x) * 27u;
+    C r0[3] = {C(1), C(1), C(1)}, f0[9], irho = C(1), n[6], fd[9], ck[3], V[6];
+#pragma unroll
+    for (int i = 0; i < 9; ++i) f0[i] = C(0);
+    // concentrations, then the stress of the lanes within d + 1 (rows: ty + 1 above, ty, ty - 1
+    // below), then the collision of the lanes within d + 2
+    auto concentrations = [&]() {
+        irho = recip((r0[0] + r0[1]) + r0[2]);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) L.c[ty][k][tx] = r0[k] * irho;
+    };
+    auto finish = [&](int d) {
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 6; ++q) n[q] = C(0);
+        if (within(d + 1)) {
+            C Txx, Txy, Tyy;
+            stress_at_lane<C, BX>(L.c, ty + 1, ty, ty - 1, tx, r0, K, n, Txx, Txy, Tyy);
+            L.T[ty][0][tx] = Txx;
+            L.T[ty][1][tx] = Txy;
+            L.T[ty][2][tx] = Tyy;
+        }
+        __syncthreads();
+        if (within(d + 2)) {
+            C Fx, Fy, Tn[3], ux, uy, mxh, myh;
+            force_or_stress<C, BX, PT>(L.T, ty - 1, ty + 1, ty, tx, Fx, Fy, Tn);
+            collide_recolour<C, PT>(f0, r0, irho, n, Fx, Fy, K, fd, ck, V, ux, uy, mxh, myh, Tn);
+        }
+    };
+    // ---- step A
+    {
+        BlockStage<S, C, BX, BY> stage;
+        S fq[9];
+        stage.load(fin, geo, x0 - 5, y0 - 5, cols + 12, rows + 12, t);
+#pragma unroll
+        for (int i = 0; i < 9; ++i) fq[i] = ld_at(fin, ys[EY[i] + 1] + xs[EX[i] + 1] + (uint32_t)i * geo.plane);
+        stage.publish(&L.cv[0][0][0]);
+        __syncthreads();
+        if (within(0)) {
+            block_pull<C, BX + 2>([&](int i) { return C(fq[i]); }, L.cv, tx, ty, r0, f0);
+            concentrations();
+        }
+    }
+    finish(0);
+    __syncthreads();  // the stress is read: the f_dag_i may take its place
+    if (within(2)) {
+        NodeBits bits(key ^ salt_a);
+#pragma unroll
+        for (int i = 0; i < 9; ++i) L.fd[i][ty][tx] = C(to_storage<S, C>(fd[i], bits));
+        C(*w)[BX + 2] = L.cv[ty + 1];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) w[k][tx + 1] = C(to_storage<S, C>(ck[k], bits));
+        C v4[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            v4[q] = C(to_storage<S, C>(V[q], bits));
+            w[3 + q][tx + 1] = v4[q];
+        }
+        w[7][tx + 1] = fac_v2<C>(v4[0], v4[2]);
+        w[8][tx + 1] = fac_v2<C>(v4[1], v4[3]);
+    }
+    __syncthreads();
+    // ---- step B
+    if (within(3)) block_pull<C, BX + 2>([&](int i) { return L.fd[i][ty - EY[i]][tx - EX[i]]; }, L.cv, tx, ty, r0, f0);
+    __syncthreads();  // the f_dag_i are read: the concentrations may take their place
+    if (within(3)) concentrations();
+    finish(3);
+    if (within(5)) {
+        NodeBits bits(key ^ salt_b);
+        const uint32_t o = ys[1] + xs[1];
+#pragma unroll
+        for (int i = 0; i < 9; ++i) st_plain(fout, o + (uint32_t)i * geo.plane, to_storage<S, C>(fd[i], bits));
+#pragma unroll
+        for (int k = 0; k < 3; ++k) st_plain(fout, o + (uint32_t)(9 + k) * geo.plane, to_storage<S, C>(ck[k], bits));
+#pragma unroll
+        for (int q = 0; q < 4; ++q) st_plain(fout, o + (uint32_t)(12 + q) * geo.plane, to_storage<S, C>(V[q], bits));
+    }
+}
+
 template <typename S, typename C, int BY, bool PT, Tape TAPE = Tape::None>
 hipError_t block_launch(const void* fin, void* fout, const BlockGrid& bg, uint32_t salt, double* tape, hipStream_t st)
 {
@@ -1691,6 +1864,33 @@ hipError_t tiles_block_any(const void* fin, void* fout, const BlockGrid& bg, uin
                   : block_launch<S, C, kBlockYSmall, false>(fin, fout, bg, salt, nullptr, st);
     return pt ? block_launch<S, C, kBlockY, true>(fin, fout, bg, salt, nullptr, st)
               : block_launch<S, C, kBlockY, false>(fin, fout, bg, salt, nullptr, st);
+}
+
+template <typename S, typename C, int BX, int BY>
+hipError_t block2_launch(const void* fin, void* fout, const BlockGrid& bg, uint32_t salt_a, uint32_t salt_b, bool pt,
+                         hipStream_t st)
+{
+    if (pt)
+        hipLaunchKernelGGL((k_block2<S, C, BX, BY, true>), dim3(bg.count), dim3(BX * BY), 0, st, (const S*)fin, (S*)fout,
+                           bg, salt_a, salt_b);
+    else
+        hipLaunchKernelGGL((k_block2<S, C, BX, BY, false>), dim3(bg.count), dim3(BX * BY), 0, st, (const S*)fin,
+                           (S*)fout, bg, salt_a, salt_b);
+    return hipGetLastError();
+}
+
+template <typename S, typename C>
+hipError_t tiles_block2_any(const void* fin, void* fout, const BlockGrid& bg, uint32_t salt_a, uint32_t salt_b, bool pt,
+                            hipStream_t st)
+{
+    if (bg.lanes_x == 16 && bg.lanes_y == 16) return block2_launch<S, C, 16, 16>(fin, fout, bg, salt_a, salt_b, pt, st);
+    if (bg.lanes_x != 32) return hipErrorInvalidValue;
+    switch (bg.lanes_y) {
+        case 16: return block2_launch<S, C, 32, 16>(fin, fout, bg, salt_a, salt_b, pt, st);
+        case 24: return block2_launch<S, C, 32, 24>(fin, fout, bg, salt_a, salt_b, pt, st);
+        case 32: return block2_launch<S, C, 32, 32>(fin, fout, bg, salt_a, salt_b, pt, st);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 }  // namespace

@@ -27,4 +27,10 @@ hipError_t tiles_f32_block(const void* fin, void* fout, const BlockGrid& bg, uin
     return tiles_block_any<float, float>(fin, fout, bg, salt, pt, stream);
 }
 
+hipError_t tiles_f32_block2(const void* fin, void* fout, const BlockGrid& bg, uint32_t salt_a, uint32_t salt_b, bool pt,
+                            hipStream_t stream)
+{
+    return tiles_block2_any<float, float>(fin, fout, bg, salt_a, salt_b, pt, stream);
+}
+
 }  // namespace tcg

@@ -731,6 +731,29 @@ def test_default_launch_at_its_size_limits_equals_the_march(precision, shape, st
     assert np.array_equal(fa, fb)
 
 
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "fp32_storage"])
+@pytest.mark.parametrize("forcing", ["guo", "perturbation"])
+@pytest.mark.parametrize("shape,threads", [((1, 1), 256), ((7, 5), 256), ((13, 37), 256), ((96, 96), 256), ((97, 96), 512),
+                                           ((6, 1536), 256), ((176, 191), 512), ((177, 193), 768), ((265, 279), 1024),
+                                           ((352, 350), 1024), ((352, 353), 0)])
+def test_two_step_blocks_equal_single_steps_bitwise(shape, threads, forcing, precision):
+    """Two steps per launch on blocks of each of their four sizes (6 x 6, 22 x 6, 22 x 14 and
+    22 x 22 nodes) at the counts where the next size takes over on 256 compute units, on lattices
+    smaller than a block's halo and just past the last: against one step per launch, an odd number
+    of steps, bit for bit."""
+    nx, ny = shape
+    rho = inputs.random_mixture(nx, ny, 7, tiny_fraction=0.0)
+    A = lbm3.Lattice(nx, ny, precision=precision, forcing=forcing).init(rho)
+    B = lbm3.Lattice(nx, ny, precision=precision, forcing=forcing).init(rho).set_steps_per_launch(1)
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert lbm3.lbm3_get_pair_launch(A.h)[:2] == ((2, threads) if threads else (1, 0))
+    fa, fb = A.step(6).state(), B.step(6).state()
+    A.close()
+    B.close()
+    assert np.isfinite(fa).all()
+    assert np.array_equal(fa, fb)
+
+
 def _factored_planes(L):
     """The 16 stored planes of a stepped lattice, as [16, ny, nx] in their storage type."""
     ptr, eb, pl, pitch, nq = lbm3.lbm3_state_buffer(L.h)
