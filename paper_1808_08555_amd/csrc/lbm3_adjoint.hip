@@ -915,9 +915,8 @@ int lbm3_adjoint(lbm3_t* h, const double* drho1_T, double dsigma[3], double* drh
     w.sig = tbase + (size_t)nslots * K * kTapeFields * N;
     double* gT = w.sig + nsig * 6;
     Tile* dsf = (Tile*)(gT + N);
-    // The reverse steps run on the handle's own adjoint stream (graph capture needs a stream
-    // other than the null stream) and the segment recomputes on a second one, both ordered
-    // after the work already on the handle's stream.
+    // The reverse steps run on the handle's own adjoint stream and the segment recomputes on a
+    // second one, both ordered after the work already on the handle's stream.
     hipError_t e = hipSuccess;
     if (!h->adj_stream) e = hipStreamCreateWithFlags(&h->adj_stream, hipStreamNonBlocking);
     if (e == hipSuccess && !h->adj_stream2) e = hipStreamCreateWithFlags(&h->adj_stream2, hipStreamNonBlocking);
@@ -938,9 +937,10 @@ int lbm3_adjoint(lbm3_t* h, const double* drho1_T, double dsigma[3], double* drh
     // checkpoint into pipeline slot s & 1 (K forward steps recording the tape) on the second
     // stream, while the reverse steps of segment s + 1 run from the other slot; events order
     // a slot's tape before its reverse steps, and its reverse steps before the slot is
-    // recomputed again.  The launch arguments depend only on the slot and the adjoint
-    // buffer's parity, so after the first use each sequence is captured once and replayed
-    // (segment 0 starts from the 27-population state and runs eagerly).
+    // recomputed again.  Every launch is enqueued directly: captured and replayed, the same
+    // sequences took longer (64^2, 2000 steps, a checkpoint every 100: 22.8 ms against 21.7;
+    // 256^2, 1000 steps: 20.0 against 19.0; the host enqueues faster than a step runs), and a
+    // blocking copy in any other thread fails while a capture is open.
     auto recompute = [&](hipStream_t q, Fmt in, int b) -> hipError_t {
         hipError_t r = hipSuccess;
         for (int j = 0; j < K && r == hipSuccess; ++j) {
@@ -975,14 +975,8 @@ int lbm3_adjoint(lbm3_t* h, const double* drho1_T, double dsigma[3], double* drh
         }
         return r;
     };
-    hipGraphExec_t gF[2] = {nullptr, nullptr}, gR[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};
     hipEvent_t ready[2] = {nullptr, nullptr}, freed[2] = {nullptr, nullptr};
     auto drop = [&]() {
-        for (auto& x : gF)
-            if (x) (void)hipGraphExecDestroy(x);
-        for (auto& row : gR)
-            for (auto& x : row)
-                if (x) (void)hipGraphExecDestroy(x);
         for (auto* ev : {&ready[0], &ready[1], &freed[0], &freed[1]})
             if (*ev) (void)hipEventDestroy(*ev);
     };
@@ -990,23 +984,6 @@ int lbm3_adjoint(lbm3_t* h, const double* drho1_T, double dsigma[3], double* drh
         e = hipEventCreateWithFlags(&ready[b], hipEventDisableTiming);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&freed[b], hipEventDisableTiming);
     }
-    // runs `body` on stream q, from a graph captured on its first use when replays pay off
-    auto run = [&](hipStream_t q, hipGraphExec_t& gx, bool graph, auto body) -> hipError_t {
-        if (!graph) return body(q);
-        if (!gx) {
-            hipGraph_t gr = nullptr;
-            hipError_t r = hipStreamBeginCapture(q, hipStreamCaptureModeThreadLocal);
-            if (r != hipSuccess) return r;
-            const hipError_t le = body(q);
-            r = hipStreamEndCapture(q, &gr);
-            if (r == hipSuccess) r = le;
-            if (r == hipSuccess) r = hipGraphInstantiate(&gx, gr, nullptr, nullptr, 0);
-            if (gr) (void)hipGraphDestroy(gr);
-            if (r != hipSuccess) return r;
-        }
-        return hipGraphLaunch(gx, q);
-    };
-    const bool graphs = nseg >= 3;
     bool slot_used[2] = {false, false};
     hipStream_t rq = overlap ? sf2 : st;  // the recompute's stream
     // recompute segment s into its slot
@@ -1016,8 +993,7 @@ int lbm3_adjoint(lbm3_t* h, const double* drho1_T, double dsigma[3], double* drh
         hipError_t r = slot_used[b] ? hipStreamWaitEvent(rq, freed[b], 0) : hipSuccess;
         if (r == hipSuccess)
             r = hipMemcpyAsync(fwd[b][0], h->ckpt[s], in == Fmt::F27 ? sbytes : fbytes, hipMemcpyDeviceToDevice, rq);
-        if (r == hipSuccess)
-            r = run(rq, gF[b], graphs && s > 0, [&](hipStream_t q) { return recompute(q, in, b); });
+        if (r == hipSuccess) r = recompute(rq, in, b);
         if (r == hipSuccess) r = hipEventRecord(ready[b], rq);
         slot_used[b] = true;
         return r;
@@ -1028,7 +1004,7 @@ int lbm3_adjoint(lbm3_t* h, const double* drho1_T, double dsigma[3], double* drh
         if (!overlap) e = start_segment(s);
         else if (s > 0) e = start_segment(s - 1);
         if (e == hipSuccess) e = hipStreamWaitEvent(st, ready[b], 0);
-        if (e == hipSuccess) e = run(st, gR[b][cl], graphs, [&](hipStream_t q) { return reverse(q, b, cl); });
+        if (e == hipSuccess) e = reverse(st, b, cl);
         if (e == hipSuccess) e = hipEventRecord(freed[b], st);
         cl ^= K & 1;
     }
