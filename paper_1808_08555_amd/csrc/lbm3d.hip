@@ -315,12 +315,17 @@ __device__ __forceinline__ void collide3(C rho, C itau, const C (&ft)[Q], const 
 // The arithmetic of every node has a fixed order, so the result does not depend on the tile
 // shape.  With FP64 arithmetic two waves per SIMD fit in registers (512 lanes of 256), with
 // FP32 three (768 lanes): 336 owned columns of 512 lanes, 560 of 768.
-template <int CB>
+// Small boxes take tiles of 8 rows of lanes (see plan3).
+template <int ROWS>
 struct Tile3Shape {
-    static constexpr int TX = 32, TY = CB == 4 ? 24 : 16, T = TX * TY;
+    static constexpr int TX = 32, TY = ROWS, T = TX * TY;
     static constexpr int CX = TX + 2, CY = TY + 2;  // nodes whose c_k, V_k the lanes need
     static constexpr int SX = TX - 2, SY = TY - 2;  // lanes that form the stress
 };
+
+constexpr int kSmallRows3 = 8;
+template <typename C>
+constexpr int kRows3 = sizeof(C) == 4 ? 24 : 16;
 
 // sx: columns from the tile's first lane to its first owned node, 2 or 3 (see plan3)
 struct Tile3 {
@@ -331,9 +336,9 @@ struct Tile3 {
 // value of a link with e_z = -1 waits 2 iterations, with e_z = 0 three, with e_z = +1 four, so the
 // links are taken in that order while their slots (one storage-type value per owning lane
 // each) fit in what the 160 KB of LDS have left.
-template <typename S, typename C, int Q>
+template <typename S, typename C, int Q, int ROWS>
 struct Hold3 {
-    using Sh = Tile3Shape<sizeof(C)>;
+    using Sh = Tile3Shape<ROWS>;
     static constexpr int lanes = (Sh::TX - 4) * (Sh::TY - 4);
     static constexpr int base = (9 * Sh::CX * Sh::CY + 9 * Sh::T + 6 * Sh::SX * Sh::SY) * (int)sizeof(C);
     static constexpr int slots = (160 * 1024 - 64 - base) / (lanes * (int)sizeof(S));
@@ -362,14 +367,15 @@ struct Hold3 {
 // What a state holds: the three initial densities (FP64) or the factored values.
 enum class In3 : int { Rho = 0, Fac = 1 };
 
-template <typename S, typename C, int Q>
+template <typename S, typename C, int Q, int ROWS>
 struct alignas(16) March3Lds {
-    using Sh = Tile3Shape<sizeof(C)>;
+    using Sh = Tile3Shape<ROWS>;
+    using Hold = Hold3<S, C, Q, ROWS>;
     C c[3][3][Sh::T];          // c_k of the new densities, by plane mod 3
     C cv[9][Sh::CX * Sh::CY];  // c_k, V_0, V_1 of the source plane (lanes beyond the halo may read
                                // one element before it)
     C T[6][Sh::SX * Sh::SY];   // stress of one plane
-    S held[Hold3<S, C, Q>::used()][Hold3<S, C, Q>::lanes];  // totals of the owned nodes
+    S held[Hold::used()][Hold::lanes];  // totals of the owned nodes
 };
 
 // The population of link i of a fluid at rest with density r, as a state in S holds it.
@@ -379,13 +385,13 @@ __device__ __forceinline__ C rest_pop(int i, double r)
     return C(S(w3<C, Q>(i) * C(r)));
 }
 
-template <typename S, typename C, bool OBS, int Q, In3 IN, typename Off>
+template <typename S, typename C, bool OBS, int Q, In3 IN, typename Off, int ROWS>
 __device__ __forceinline__ void march3(const void* __restrict__ in, const Geo3& g, const KParams& kp, const Tile3& tl,
-                                       S* __restrict__ out, March3Lds<S, C, Q>& L, double (&acc)[8],
+                                       S* __restrict__ out, March3Lds<S, C, Q, ROWS>& L, double (&acc)[8],
                                        double* __restrict__ rho_out, uint32_t salt)
 {
-    using Sh = Tile3Shape<sizeof(C)>;
-    using Hold = Hold3<S, C, Q>;
+    using Sh = Tile3Shape<ROWS>;
+    using Hold = Hold3<S, C, Q, ROWS>;
     constexpr int TX = Sh::TX, T3 = Sh::T;
     const int t = threadIdx.x, tx = t % TX, ty = t / TX;
     const int sx = tl.sx;  // lane tx sits on column x0 - sx + tx
@@ -706,21 +712,21 @@ __device__ __forceinline__ void march3(const void* __restrict__ in, const Geo3& 
 // is rounded stochastically with the random bits of its node (key: node index and the step's
 // salt; f_dag_i first, then c_k, V_0, V_1).  OBS: the observables of the state instead of its
 // next step, and with rho_out the densities.
-template <typename S, typename C, bool OBS, int Q, In3 IN, typename Off>
-__global__ __launch_bounds__((Tile3Shape<sizeof(C)>::T)) __attribute__((amdgpu_waves_per_eu(Tile3Shape<sizeof(C)>::T / 256))) void k3_march(
+template <typename S, typename C, bool OBS, int Q, In3 IN, typename Off, int ROWS>
+__global__ __launch_bounds__(Tile3Shape<ROWS>::T) __attribute__((amdgpu_waves_per_eu(Tile3Shape<ROWS>::T / 256))) void k3_march(
     const void* __restrict__ in, Geo3 g, KParams kp, const Tile3* __restrict__ tiles, S* __restrict__ out,
     double* __restrict__ partials, double* __restrict__ rho_out, uint32_t salt)
 {
-    using Sh = Tile3Shape<sizeof(C)>;
+    using Sh = Tile3Shape<ROWS>;
     constexpr int T3 = Sh::T;
     static_assert(T3 % 64 == 0 && (2 * Sh::TX) % 64 == 0, "each wave is whole tile rows");
     static_assert(2 * Sh::CX + 2 * Sh::TY <= 128, "one lane of two waves per node of the outer ring");
     static_assert(sizeof(double) * 8 * (T3 / 64) <= sizeof(C) * 3 * 3 * T3, "c ring too small for the reduction");
-    __shared__ March3Lds<S, C, Q> L;
+    __shared__ March3Lds<S, C, Q, ROWS> L;
     const Tile3 tl = tiles[blockIdx.x];
     const int t = threadIdx.x;
     double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    march3<S, C, OBS, Q, IN, Off>(in, g, kp, tl, out, L, acc, rho_out, salt);
+    march3<S, C, OBS, Q, IN, Off, ROWS>(in, g, kp, tl, out, L, acc, rho_out, salt);
     if constexpr (OBS) {
         // wavefront reductions, then the waves' results in order (the c ring is free once
         // every lane has passed the last barrier of the march)
@@ -825,6 +831,7 @@ struct lbm3d {
     double* partials = nullptr;  // [ntiles][8]
     double* staging = nullptr;   // [3q][N] for exports
     double* rho = nullptr;       // [3][N] densities for exports
+    int rows = 0;  // rows of lanes of its tiles
     int cur = 0;
     int64_t step = 0;
     bool ready = false;
@@ -855,21 +862,36 @@ static void split_even(int n, int parts, int q, int& start, int& len)
 // (48^3 D3Q19 FP64: 12 segments of 4 planes 56 us, 24 of 2 planes 48 us).  Workgroups go to the
 // XCDs in turn, so the list is permuted for each XCD to take a contiguous run of it
 // (neighbouring blocks, whose halos it then finds in its own L2).
-static std::vector<Tile3> plan3(const Geo3& g, int slots, Prec prec)
+//
+// Tiles of 8 rows of lanes (28 x 4 nodes) take less time per plane, their four waves having a
+// SIMD each, but own a third of the nodes: a plane's time is 0.72 of the large tile's with FP64
+// arithmetic, 0.9 in FP32, where three of the small ones share a compute unit, and the plan with
+// the least of rounds x planes x that time is taken (us per step, large and small tiles: D3Q19
+// FP64 32^3 31.8 and 26.6, 48^3 36.8 and 34.7, 64^3 56.0 and 60.8, 96^3 134 and 187; FP32 32^3 24.4
+// and 19.9, 64^3 40.9 and 37.4, 80^3 53.1 and 68.3; D3Q27 FP64 32^3 39.4 and 32.9, 48^3 50.7 and
+// 46.7, FP32 64^3 49.9 and 45.0).
+static std::vector<Tile3> plan3(const Geo3& g, const int (&slots)[2], Prec prec, int& rows)
 {
-    const int TX = Tile3Shape<8>::TX, TY = prec == Prec::F32 ? Tile3Shape<4>::TY : Tile3Shape<8>::TY;
-    const int ntx = (g.nx + TX - 5) / (TX - 4), nty = (g.ny + TY - 5) / (TY - 4);
-    const int64_t per_seg = (int64_t)ntx * nty;
-    if (slots < 1) slots = 1;
-    int nseg = 1;
+    constexpr int TX = Tile3Shape<kSmallRows3>::TX;
+    const int shapes[2] = {prec == Prec::F32 ? kRows3<float> : kRows3<double>, kSmallRows3};
+    const double plane[2] = {1.0, prec == Prec::F32 ? 0.9 : 0.72};
+    int ntx = 1, nty = 1, nseg = 1;
     double best = 1e300;
-    for (int s = 1; s <= g.nz; ++s) {
-        const int depth = (g.nz + s - 1) / s;
-        const int64_t rounds = (per_seg * s + slots - 1) / slots;
-        const double cost = (double)rounds * (depth + 6) * (1.0 + 1e-9 * s);
-        if (cost < best) {
-            best = cost;
-            nseg = s;
+    for (int k = 0; k < 2; ++k) {
+        const int TY = shapes[k], nx = (g.nx + TX - 5) / (TX - 4), ny = (g.ny + TY - 5) / (TY - 4);
+        const int64_t per_seg = (int64_t)nx * ny, n = std::max(slots[k], 1);
+        if (k == 1 && g.zbytes >= ((int64_t)1 << 32)) break;
+        for (int s = 1; s <= g.nz; ++s) {
+            const int depth = (g.nz + s - 1) / s;
+            const int64_t rounds = (per_seg * s + n - 1) / n;
+            const double cost = (double)rounds * (depth + 6) * plane[k] * (1.0 + 1e-9 * s);
+            if (cost < best) {
+                best = cost;
+                nseg = s;
+                ntx = nx;
+                nty = ny;
+                rows = TY;
+            }
         }
     }
     // Where no tile has more than TX - 6 columns the lanes start one column earlier: they then
@@ -879,7 +901,7 @@ static std::vector<Tile3> plan3(const Geo3& g, int slots, Prec prec)
     // 192).  Tiles of both kinds side by side were slower (160^3, 27 and 26 columns: 384 -> 400).
     const int sx = (g.nx + ntx - 1) / ntx <= TX - 6 ? 3 : 2;
     std::vector<Tile3> L;
-    L.reserve((size_t)per_seg * nseg);
+    L.reserve((size_t)ntx * nty * nseg);
     for (int zs = 0; zs < nseg; ++zs)
         for (int ty = 0; ty < nty; ++ty)
             for (int tx = 0; tx < ntx; ++tx) {
@@ -898,28 +920,35 @@ static std::vector<Tile3> plan3(const Geo3& g, int slots, Prec prec)
     return out;
 }
 
-template <typename S, typename C, int Q, In3 IN, typename Off>
-static hipError_t launch_march_f(lbm3d* h, bool obs, double* rho_out)
+template <typename S, typename C, int Q, In3 IN, typename Off, int ROWS>
+static hipError_t launch_march_r(lbm3d* h, bool obs, double* rho_out)
 {
     const void* in = h->buf[h->cur];
-    const dim3 grid(h->ntiles), block(Tile3Shape<sizeof(C)>::T);
+    const dim3 grid(h->ntiles), block(Tile3Shape<ROWS>::T);
     if (obs)
-        hipLaunchKernelGGL((k3_march<S, C, true, Q, IN, Off>), grid, block, 0, h->stream, in, h->g, h->kp,
+        hipLaunchKernelGGL((k3_march<S, C, true, Q, IN, Off, ROWS>), grid, block, 0, h->stream, in, h->g, h->kp,
                            (const Tile3*)h->dtiles, (S*)nullptr, h->partials, rho_out, 0u);
     else
-        hipLaunchKernelGGL((k3_march<S, C, false, Q, IN, Off>), grid, block, 0, h->stream, in, h->g, h->kp,
+        hipLaunchKernelGGL((k3_march<S, C, false, Q, IN, Off, ROWS>), grid, block, 0, h->stream, in, h->g, h->kp,
                            (const Tile3*)h->dtiles, (S*)h->buf[h->cur ^ 1], (double*)nullptr, (double*)nullptr,
                            step_salt(h->step));
     return hipGetLastError();
 }
 
+template <typename S, typename C, int Q, In3 IN, typename Off>
+static hipError_t launch_march_f(lbm3d* h, bool obs, double* rho_out)
+{
+    return h->rows == kSmallRows3 ? launch_march_r<S, C, Q, IN, Off, kSmallRows3>(h, obs, rho_out)
+                                  : launch_march_r<S, C, Q, IN, Off, kRows3<C>>(h, obs, rho_out);
+}
+
 // Offsets within a z plane fit 32 bits below 4 GiB a plane (15 to 38 million nodes); larger
-// planes, and every first step, take the 64-bit instantiation.
+// planes (never with small tiles), and every first step, take the 64-bit instantiation.
 template <typename S, typename C, int Q>
 static hipError_t launch_march_q(lbm3d* h, bool obs, double* rho_out)
 {
     if (h->fmt == In3::Rho) return launch_march_f<S, C, Q, In3::Rho, uint64_t>(h, obs, rho_out);
-    if (h->g.zbytes >= ((int64_t)1 << 32)) return launch_march_f<S, C, Q, In3::Fac, uint64_t>(h, obs, rho_out);
+    if (h->g.zbytes >= ((int64_t)1 << 32)) return launch_march_r<S, C, Q, In3::Fac, uint64_t, kRows3<C>>(h, obs, rho_out);
     return launch_march_f<S, C, Q, In3::Fac, uint32_t>(h, obs, rho_out);
 }
 
@@ -941,24 +970,31 @@ static hipError_t launch_march(lbm3d* h, bool obs, double* rho_out = nullptr)
     return hipErrorInvalidValue;
 }
 
-template <int Q>
-static hipError_t march_occupancy_q(Prec prec, int* per_cu)
+template <typename S, typename C, int ROWS>
+static hipError_t march_occupancy_t(int q, int* per_cu)
 {
-    constexpr int T8 = Tile3Shape<8>::T, T4 = Tile3Shape<4>::T;
-    switch (prec) {
-        case Prec::F64:
-            return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, k3_march<double, double, false, Q, In3::Fac, uint32_t>, T8, 0);
-        case Prec::F32S:
-            return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, k3_march<float, double, false, Q, In3::Fac, uint32_t>, T8, 0);
-        case Prec::F32:
-            return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, k3_march<float, float, false, Q, In3::Fac, uint32_t>, T4, 0);
-    }
-    return hipErrorInvalidValue;
+    constexpr int T = Tile3Shape<ROWS>::T;
+    return q == 27 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(
+                         per_cu, k3_march<S, C, false, 27, In3::Fac, uint32_t, ROWS>, T, 0)
+                   : hipOccupancyMaxActiveBlocksPerMultiprocessor(
+                         per_cu, k3_march<S, C, false, 19, In3::Fac, uint32_t, ROWS>, T, 0);
 }
 
-static hipError_t march_occupancy(Prec prec, int q, int* per_cu)
+// workgroups per compute unit, of either tile
+static hipError_t march_occupancy(Prec prec, int q, bool small, int* per_cu)
 {
-    return q == 27 ? march_occupancy_q<27>(prec, per_cu) : march_occupancy_q<19>(prec, per_cu);
+    switch (prec) {
+        case Prec::F64:
+            return small ? march_occupancy_t<double, double, kSmallRows3>(q, per_cu)
+                         : march_occupancy_t<double, double, kRows3<double>>(q, per_cu);
+        case Prec::F32S:
+            return small ? march_occupancy_t<float, double, kSmallRows3>(q, per_cu)
+                         : march_occupancy_t<float, double, kRows3<double>>(q, per_cu);
+        case Prec::F32:
+            return small ? march_occupancy_t<float, float, kSmallRows3>(q, per_cu)
+                         : march_occupancy_t<float, float, kRows3<float>>(q, per_cu);
+    }
+    return hipErrorInvalidValue;
 }
 
 template <int Q>
@@ -1021,13 +1057,16 @@ int lbm3d_create_lattice(const lbm3_params* p, int32_t nz, int32_t q, void* hip_
     h->stream = (hipStream_t)hip_stream;
     const int64_t N = h->g.N;
     hipError_t e = hipSuccess;
-    int dev = 0, cus = 0, per_cu = 0;
+    int dev = 0, cus = 0, slots[2] = {0, 0};
     e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e == hipSuccess) e = march_occupancy(h->prec, q, &per_cu);
+    for (int k = 0; k < 2 && e == hipSuccess; ++k) {
+        e = march_occupancy(h->prec, q, k == 1, &slots[k]);
+        slots[k] *= cus;
+    }
     std::vector<Tile3> tiles;
     if (e == hipSuccess) {
-        tiles = plan3(h->g, per_cu * cus, h->prec);
+        tiles = plan3(h->g, slots, h->prec, h->rows);
         h->ntiles = (int)tiles.size();
     }
     if (e == hipSuccess) e = alloc_state_pair((size_t)h->g.zbytes * nz, h->buf);

@@ -216,6 +216,25 @@ def test_factored_march_at_the_edges_of_its_tiles(shape, q, precision, rtol):
         assert err <= rtol
 
 
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("q", QS)
+@pytest.mark.parametrize("cell,times", [((45, 19, 8), (5, 5, 1)), ((28, 24, 9), (8, 4, 1)), ((31, 5, 60), (3, 7, 3))])
+def test_large_and_small_tiles_agree_bitwise(cell, times, q, precision):
+    """A box small enough for tiles of 28 x 4 nodes, and the periodic repetition of it that takes
+    the large tiles: node by node the same populations, bit for bit."""
+    nx, ny, nz = cell
+    rho = inputs.random_mixture_3d(nx, ny, nz, 22, tiny_fraction=0.0)
+    reps = times[::-1]
+    A = lbm3.Lattice3D(nx, ny, nz, SIG, TAU, q=q, precision=precision).init(rho)
+    B = lbm3.Lattice3D(nx * times[0], ny * times[1], nz * times[2], SIG, TAU, q=q, precision=precision)
+    B.init(np.ascontiguousarray(np.tile(rho, (1,) + reps)))
+    fa, fb = A.step(3).state(), B.step(3).state()
+    A.close()
+    B.close()
+    assert np.isfinite(fa).all()
+    assert np.array_equal(np.tile(fa, (1,) * (fa.ndim - 3) + reps), fb)
+
+
 def test_plane_beyond_32_bit_offsets_equals_the_2d_step():
     """A plane of 4.1 GiB (5000 x 3840 nodes, D3Q19, FP64) takes the march with 64-bit offsets;
     one plane deep, the lattice is uniform along z and its densities follow the two-dimensional
