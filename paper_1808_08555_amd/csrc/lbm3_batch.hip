@@ -17,6 +17,7 @@
 #include "lbm3_handle.h"
 
 namespace {
+constexpr int64_t kBatchBlockNodes = (int64_t)1 << 21;  // single steps on blocks up to this many
 constexpr int kGraphSteps = 20;  // steps per captured graph (a multiple of 4: parity kept with pairs)
 }
 
@@ -41,6 +42,9 @@ struct lbm3_batch {
     int ntiles2 = 0;
     int threads2 = 0;
     int rows2 = 0;
+    tcg::Tile* dblocks = nullptr;     // blocks of the one-step launch on small batches
+    int nblocks = 0;                  // 0: the march
+    int block_lanes_y = 0;
     tcg::Tile* dobs = nullptr;        // observation list, instance by instance
     std::vector<int> obs_first, obs_count;
     hipGraphExec_t exec[2] = {nullptr, nullptr};  // one graph per starting buffer parity
@@ -111,13 +115,20 @@ static int batch_plan(lbm3_batch* b)
     b->rows2 = 0;
     int64_t nodes = 0;
     for (int i = 0; i < b->count; ++i) nodes += (int64_t)b->inst[i].kp.nx * b->inst[i].kp.ny;
-    const bool want2 = b->pair_mode == 2 || (b->pair_mode == 0 && nodes >= ((int64_t)1 << 20));
-    // two-step width: 128 columns unless the instances are wide (a 256-wide workgroup leaves
-    // half its lanes idle on a 128-wide instance; measured on the 64-instance sweep with sides
-    // 128-512: 27.7k MLUPS at 128 against 26.2k at 256, and never slower per size class)
+    // Pairs of steps from 2^19 nodes in FP64 and 5 x 2^18 in FP32 and FP32 storage, single steps on
+    // blocks below (us per step of a batch, blocks and pairs, and in brackets the march's single
+    // steps: FP64 52 k nodes 7.5 and 13.6 (18.2), 503 k 30.7 and 29.5 (37.6), 930 k 60.2 and 44.8
+    // (69.8); FP32 storage 930 k 42.8 and 48.0 (61.5), 1.46 M 62.6 and 58.4 (79.5); FP32 52 k 5.6 and
+    // 12.8 (13.3), 930 k 27.0 and 31.8 (39.2), 1.46 M 42.8 and 40.1 (58.2)).
+    const int64_t min2 = b->prec == Prec::F64 ? (int64_t)1 << 19 : (int64_t)5 << 18;
+    const bool want2 = b->pair_mode == 2 || (b->pair_mode == 0 && nodes >= min2);
+    // two-step width: 64 columns up to 2^22 nodes, where 128 leave fewer tiles than the device
+    // holds (FP64 2.4 M nodes 96.6 against 100.4, FP32 storage 100 against 110), 128 beyond (6.8 M
+    // nodes: FP64 203 against 213, FP32 134 against 145), and 256 where the instances are wide
+    // enough not to leave half its lanes idle
     int max_side = 0;
     for (int i = 0; i < b->count; ++i) max_side = std::max(max_side, b->inst[i].kp.nx);
-    const int t2 = std::min(b->tile_set ? 256 : (max_side >= 768 ? 256 : 128), b->threads);
+    const int t2 = std::min(b->tile_set ? 256 : (max_side >= 768 ? 256 : (nodes <= ((int64_t)1 << 22) ? 64 : 128)), b->threads);
     const int slots2 = want2 ? device_slots_pair(b->prec, t2) : 0;
     if (slots2 > 0) {
         double best2 = 1e300;
@@ -138,15 +149,27 @@ static int batch_plan(lbm3_batch* b)
             plan_lattice(i, b->inst[i].kp.nx, b->inst[i].kp.ny, t2, b->rows2, eb, all2, 6);
     }
     b->threads2 = t2;
-    std::vector<Tile> T = xcd_order(all, 8), T2 = xcd_order(all2, 8);
+    // the blocks of single steps: the smaller ones while they are at most one per compute unit
+    std::vector<Tile> blk;
+    if (!b->tile_set && b->rows_by_side.empty() && b->pair_mode != 2 && all2.empty() && nodes <= kBatchBlockNodes) {
+        for (int y : {kBlockYSmall, kBlockY}) {
+            blk.clear();
+            for (int i = 0; i < b->count; ++i)
+                plan_blocks(i, b->inst[i].kp.nx, b->inst[i].kp.ny, kBlockCols, y - 4, blk);
+            b->block_lanes_y = y;
+            if ((int)blk.size() <= device_cus()) break;
+        }
+    }
+    std::vector<Tile> T = xcd_order(all, 8), T2 = xcd_order(all2, 8), TB = xcd_order(blk, 8);
     (void)hipStreamSynchronize(b->stream);
     drop_graphs(b);
     if (b->dtiles) (void)hipFree(b->dtiles);
     if (b->dtiles2) (void)hipFree(b->dtiles2);
     if (b->dobs) (void)hipFree(b->dobs);
-    b->dtiles = b->dtiles2 = nullptr;
+    if (b->dblocks) (void)hipFree(b->dblocks);
+    b->dtiles = b->dtiles2 = b->dblocks = nullptr;
     b->dobs = nullptr;
-    b->ntiles = b->ntiles2 = 0;
+    b->ntiles = b->ntiles2 = b->nblocks = 0;
     hipError_t e = hipMalloc((void**)&b->dtiles, T.size() * sizeof(Tile));
     if (e == hipSuccess) e = hipMalloc((void**)&b->dobs, obs.size() * sizeof(Tile));
     if (e == hipSuccess && !T2.empty()) e = hipMalloc((void**)&b->dtiles2, T2.size() * sizeof(Tile));
@@ -154,7 +177,11 @@ static int batch_plan(lbm3_batch* b)
     if (e == hipSuccess) e = hipMemcpy(b->dobs, obs.data(), obs.size() * sizeof(Tile), hipMemcpyHostToDevice);
     if (e == hipSuccess && !T2.empty())
         e = hipMemcpy(b->dtiles2, T2.data(), T2.size() * sizeof(Tile), hipMemcpyHostToDevice);
+    if (e == hipSuccess && !TB.empty()) e = hipMalloc((void**)&b->dblocks, TB.size() * sizeof(Tile));
+    if (e == hipSuccess && !TB.empty())
+        e = hipMemcpy(b->dblocks, TB.data(), TB.size() * sizeof(Tile), hipMemcpyHostToDevice);
     if (e != hipSuccess) return hip_fail(e, "batch tile plan upload");
+    b->nblocks = (int)TB.size();
     b->ntiles = (int)T.size();
     b->ntiles2 = (int)T2.size();
     return LBM3_OK;
@@ -186,6 +213,9 @@ static hipError_t launch_steady(lbm3_batch* b, int c, bool two, int64_t step)
     if (two)
         e = launch_pair(b->prec, b->buf[c], b->buf[c ^ 1], b->dinst, b->dtiles2, b->ntiles2, b->threads2, step,
                         b->stream, b->pt, b->dstep);
+    else if (b->nblocks > 0)
+        e = launch_block_list(b->prec, b->buf[c], b->buf[c ^ 1],
+                              BlockList{b->dinst, b->dblocks, b->dstep, b->nblocks, b->block_lanes_y}, step, b->stream, b->pt);
     else
         e = launch_tiles(b->prec, Fmt::FAC, Fmt::FAC, b->buf[c], b->buf[c ^ 1], b->dinst, b->dtiles, b->ntiles,
                          b->threads, step, 0, b->stream, b->pt, b->dstep);
@@ -234,6 +264,7 @@ int lbm3_batch_destroy(lbm3_batch_t* b)
     if (b->dtiles) (void)hipFree(b->dtiles);
     if (b->dtiles2) (void)hipFree(b->dtiles2);
     if (b->dobs) (void)hipFree(b->dobs);
+    if (b->dblocks) (void)hipFree(b->dblocks);
     if (b->staging) (void)hipFree(b->staging);
     if (b->partials) (void)hipFree(b->partials);
     if (b->obs_dev) (void)hipFree(b->obs_dev);

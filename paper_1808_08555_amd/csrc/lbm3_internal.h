@@ -203,6 +203,14 @@ struct BlockGrid {
         rows = bh + (by < rh ? 1 : 0);
     }
 };
+// The blocks of a batch: its tiles as a list.
+struct BlockList {
+    const Instance* inst;
+    const Tile* tiles;
+    const int64_t* step_dev;  // the device's step counter, which salts the stochastic rounding
+    int32_t count;
+    int32_t lanes_y;  // kBlockY or kBlockYSmall
+};
 // cus: compute units of the device
 BlockGrid block_grid(const KParams& kp, int cus);
 // Two steps per launch: the grid of the smallest blocks that are at most one per compute unit, or
@@ -220,11 +228,19 @@ hipError_t tiles_f32_block2(const void* fin, void* fout, const BlockGrid& bg, ui
                             hipStream_t stream);
 hipError_t tiles_f32s_block2(const void* fin, void* fout, const BlockGrid& bg, uint32_t salt_a, uint32_t salt_b, bool pt,
                             hipStream_t stream);
+hipError_t tiles_f64_block_list(const void* fin, void* fout, const BlockList& bl, uint32_t salt, bool pt,
+                                hipStream_t stream);
+hipError_t tiles_f32_block_list(const void* fin, void* fout, const BlockList& bl, uint32_t salt, bool pt,
+                                hipStream_t stream);
+hipError_t tiles_f32s_block_list(const void* fin, void* fout, const BlockList& bl, uint32_t salt, bool pt,
+                                hipStream_t stream);
 // The FP64 block step (factored state in) that also writes the adjoint's tape, as
 // tiles_f64_tape does.
 hipError_t tiles_f64_block_tape(const void* fin, void* fout, const BlockGrid& bg, double* tape, hipStream_t stream);
 hipError_t launch_block(Prec prec, const void* fin, void* fout, const BlockGrid& bg, int64_t step, hipStream_t stream,
                         bool pt = false);
+hipError_t launch_block_list(Prec prec, const void* fin, void* fout, const BlockList& bl, int64_t step, hipStream_t stream,
+                             bool pt);
 hipError_t launch_block2(Prec prec, const void* fin, void* fout, const BlockGrid& bg, int64_t step, hipStream_t stream,
                          bool pt = false);
 

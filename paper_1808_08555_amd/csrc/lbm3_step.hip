@@ -179,6 +179,18 @@ hipError_t launch_block(Prec prec, const void* fin, void* fout, const BlockGrid&
     return hipErrorInvalidValue;
 }
 
+hipError_t launch_block_list(Prec prec, const void* fin, void* fout, const BlockList& bl, int64_t step, hipStream_t st,
+                             bool pt)
+{
+    const uint32_t salt = step_salt(step);
+    switch (prec) {
+        case Prec::F64: return tiles_f64_block_list(fin, fout, bl, salt, pt, st);
+        case Prec::F32S: return tiles_f32s_block_list(fin, fout, bl, salt, pt, st);
+        case Prec::F32: return tiles_f32_block_list(fin, fout, bl, salt, pt, st);
+    }
+    return hipErrorInvalidValue;
+}
+
 hipError_t launch_block2(Prec prec, const void* fin, void* fout, const BlockGrid& bg, int64_t step, hipStream_t st,
                          bool pt)
 {

@@ -1625,17 +1625,41 @@ __device__ __forceinline__ void block_pull(FD f_dag, const C (*cv)[9][CWM], int 
     for (int k = 0; k < 3; ++k) r0[k] = (gp[k] + gz[k]) + gm[k];
 }
 
-template <typename S, typename C, int BX, int BY, bool PT, Tape TAPE = Tape::None>
+// A workgroup's block, its lattice's parameters and the lattice's offset in the state: from a
+// lattice's grid, or from the list of a batch.
+__device__ __forceinline__ KParams block_of(const BlockGrid& bg, int& x0, int& y0, int& cols, int& rows, int64_t& off)
+{
+    bg.block((int)blockIdx.x, x0, y0, cols, rows);
+    off = 0;
+    return bg.kp;
+}
+__device__ __forceinline__ KParams block_of(const BlockList& bl, int& x0, int& y0, int& cols, int& rows, int64_t& off)
+{
+    const Tile tl = bl.tiles[blockIdx.x];
+    x0 = tl.x0;
+    y0 = tl.y0;
+    cols = tl.cols;
+    rows = tl.rows;
+    off = bl.inst[tl.inst].offset;
+    return bl.inst[tl.inst].kp;
+}
+
+template <typename S, typename C, int BX, int BY, bool PT, Tape TAPE = Tape::None, typename Grid = BlockGrid>
 __global__ __launch_bounds__(BX * BY) __attribute__((amdgpu_waves_per_eu(2))) void k_block(
-    const S* __restrict__ fin, S* __restrict__ fout, BlockGrid bg, uint32_t salt, double* __restrict__ tape = nullptr)
+    const S* __restrict__ fin, S* __restrict__ fout, Grid bg, uint32_t salt, double* __restrict__ tape = nullptr)
 {
     static_assert(BX % 64 == 0 || 64 % BX == 0, "waves are whole tile rows");
     __shared__ BlockLds<C, BX, BY> L;
-    const KParams& kp = bg.kp;
+    int x0, y0, cols, rows;
+    int64_t off;
+    const KParams kp = block_of(bg, x0, y0, cols, rows, off);
+    fin += off;
+    fout += off;
+    if constexpr (kRounds<S, C> && std::is_same_v<Grid, BlockList>) {
+        if (bg.step_dev) salt = step_salt(*bg.step_dev);
+    }
     const int nx = kp.nx, ny = kp.ny;
     const int t = threadIdx.x, tx = t % BX, ty = t / BX;
-    int x0, y0, cols, rows;
-    bg.block((int)blockIdx.x, x0, y0, cols, rows);
     const bool in1 = tx <= cols + 3 && ty <= rows + 3;
     const bool in2 = tx >= 1 && tx <= cols + 2 && ty >= 1 && ty <= rows + 2;
     const bool in3 = tx >= 2 && tx <= cols + 1 && ty >= 2 && ty <= rows + 1;
@@ -1864,6 +1888,25 @@ hipError_t tiles_block_any(const void* fin, void* fout, const BlockGrid& bg, uin
                   : block_launch<S, C, kBlockYSmall, false>(fin, fout, bg, salt, nullptr, st);
     return pt ? block_launch<S, C, kBlockY, true>(fin, fout, bg, salt, nullptr, st)
               : block_launch<S, C, kBlockY, false>(fin, fout, bg, salt, nullptr, st);
+}
+
+template <typename S, typename C, int BY>
+hipError_t block_list_launch(const void* fin, void* fout, const BlockList& bl, uint32_t salt, bool pt, hipStream_t st)
+{
+    if (pt)
+        hipLaunchKernelGGL((k_block<S, C, kBlockX, BY, true, Tape::None, BlockList>), dim3(bl.count), dim3(kBlockX * BY), 0,
+                           st, (const S*)fin, (S*)fout, bl, salt, (double*)nullptr);
+    else
+        hipLaunchKernelGGL((k_block<S, C, kBlockX, BY, false, Tape::None, BlockList>), dim3(bl.count), dim3(kBlockX * BY),
+                           0, st, (const S*)fin, (S*)fout, bl, salt, (double*)nullptr);
+    return hipGetLastError();
+}
+
+template <typename S, typename C>
+hipError_t tiles_block_list_any(const void* fin, void* fout, const BlockList& bl, uint32_t salt, bool pt, hipStream_t st)
+{
+    return bl.lanes_y == kBlockYSmall ? block_list_launch<S, C, kBlockYSmall>(fin, fout, bl, salt, pt, st)
+                                      : block_list_launch<S, C, kBlockY>(fin, fout, bl, salt, pt, st);
 }
 
 template <typename S, typename C, int BX, int BY>

@@ -33,4 +33,10 @@ hipError_t tiles_f32_block2(const void* fin, void* fout, const BlockGrid& bg, ui
     return tiles_block2_any<float, float>(fin, fout, bg, salt_a, salt_b, pt, stream);
 }
 
+hipError_t tiles_f32_block_list(const void* fin, void* fout, const BlockList& bl, uint32_t salt, bool pt,
+                                hipStream_t stream)
+{
+    return tiles_block_list_any<float, float>(fin, fout, bl, salt, pt, stream);
+}
+
 }  // namespace tcg

@@ -35,4 +35,10 @@ hipError_t tiles_f32s_block2(const void* fin, void* fout, const BlockGrid& bg, u
     return tiles_block2_any<float, double>(fin, fout, bg, salt_a, salt_b, pt, stream);
 }
 
+hipError_t tiles_f32s_block_list(const void* fin, void* fout, const BlockList& bl, uint32_t salt, bool pt,
+                                hipStream_t stream)
+{
+    return tiles_block_list_any<float, double>(fin, fout, bl, salt, pt, stream);
+}
+
 }  // namespace tcg

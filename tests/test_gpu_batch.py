@@ -53,6 +53,30 @@ def test_batch_matches_plain_step_bitwise(precision):
     lbm3.lbm3_batch_destroy(b)
 
 
+@pytest.mark.parametrize("precision,sides,steps", [("fp64", [28, 27, 30], 1), ("fp64", [61, 1, 97, 130] * 9, 1),
+                                                   ("fp64", [512, 511, 29], 1), ("fp64", [512, 512], 2),
+                                                   ("fp32", [45, 64, 29] * 20, 1), ("fp32", [724, 724, 512], 1),
+                                                   ("fp32", [724, 724, 513], 2), ("fp32_storage", [70, 33] * 25, 1),
+                                                   ("fp32_storage", [1145], 2)])
+def test_batch_default_launch_equals_plain_lattices_bitwise(precision, sides, steps):
+    """Batches in their default launch: blocks of both heights (one per compute unit or more),
+    and both sides of the node counts from which two steps go into a launch; 23 steps (the
+    first, one graph of 20, two eager), every instance against the lattice stepped alone, bit for
+    bit."""
+    ws = [inputs.Workload("rand", n, n + 3 * (n < 500), (0.011, 0.013, 0.017), (0.7, 1.0, 1.3),
+                          rho=inputs.random_mixture(n, n + 3 * (n < 500), 40 + n % 7, tiny_fraction=0.0)) for n in sides]
+    b = _make_batch(ws, precision)
+    assert lbm3.lbm3_batch_get_pair_launch(b)[0] == steps
+    lbm3.lbm3_batch_step(b, 23)
+    for i, w in enumerate(ws[:6]):
+        _, rho = _batch_state(b, i, w)
+        L = lbm3.Lattice(w.nx, w.ny, w.sigma, w.tau, w.rho0, w.beta0, precision).init(w.rho)
+        ref = L.set_steps_per_launch(1).step(23).densities()
+        L.close()
+        assert np.array_equal(rho, ref), (i, w.nx)
+    lbm3.lbm3_batch_destroy(b)
+
+
 @pytest.mark.parametrize("precision", ["fp64", "fp32", "fp32_storage"])
 @pytest.mark.parametrize("threads", [0, 64, 256])
 def test_batch_two_step_pass_matches_plain_step_bitwise(precision, threads):
