@@ -36,7 +36,8 @@ def log(msg: str):
     print(f"[bench] {msg}", file=sys.stderr, flush=True)
 
 
-def kernel_source_hash(files=("lbm3_step_impl.h", "lbm3_rounding.h", "lbm3_tiles_f64.hip", "lbm3_internal.h")) -> str:
+def kernel_source_hash(files=("lbm3_step_impl.h", "lbm3_device.h", "lbm3_rounding.h", "lbm3_tiles_f64.hip",
+                              "lbm3_internal.h")) -> str:
     """Hash of the kernel sources a profile summary was taken from (the 2D step's by
     default; the D3Q19 form's summaries use its own source)."""
     h = hashlib.sha256()
@@ -56,7 +57,7 @@ def profile_figure(kernel_tag: str, kind: str, key: str):
     text = open(path).read()
     m = re.search(r"kernel_source_sha256_16:\s*([0-9a-f]+)", text)
     t = re.search(re.escape(key) + r":\s*([0-9.eE+]+)", text)
-    files = ("lbm3d.hip", "lbm3_rounding.h") if kernel_tag.startswith("lbm3d") else None
+    files = ("lbm3d.hip", "lbm3_device.h", "lbm3_rounding.h") if kernel_tag.startswith("lbm3d") else None
     current = kernel_source_hash(files) if files else kernel_source_hash()
     if not m or not t or m.group(1) != current:
         return None
@@ -236,7 +237,7 @@ def bench_d3q19(torch, lbm3, inputs, n: int, steps: int, precision: str = "fp64"
     t = a.elapsed_time(b) / 1e3
     L.close()
     lu = n ** 3 * steps
-    b = 2 * 3 * q * (8 if precision == "fp64" else 4)
+    b = 2 * (q + 9) * (8 if precision == "fp64" else 4)
     res = {"workload": f"D3Q{q} {n}^3, two tangent spheres of radius {R:g}, {precision}, {steps} steps",
            "mlups": round(lu / t / 1e6, 1), "bytes_per_lu_stated": b,
            "frac_of_peak": round(b * lu / t / 1e9 / HBM_PEAK_GBS, 4), "kernel": "k3_march (one launch per step)"}

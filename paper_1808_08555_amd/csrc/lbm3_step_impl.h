@@ -706,8 +706,8 @@ __device__ __forceinline__ void march(const S* __restrict__ fin, S* __restrict__
 // Lane t of either step sits on column x0 - 6 + t.  A forms densities on lanes 1..cols+10
 // and recolours lanes 3..cols+8 (B's source columns); B forms densities on lanes 4..cols+7
 // and outputs lanes 6..cols+5, so cols <= NT - 12.  Every iteration has three phases, each
-// closed by a barrier that both steps' waves reach (the same number of times: three per
-// pre-roll and three per iteration of a loop of the same length).  Both steps run the same
+// closed by a barrier that both steps' waves reach (the same number of times: five in
+// the pre-roll and three per iteration of a loop of the same length).  Both steps run the same
 // stage in the same phase, so the heavy stages meet at the same barrier:
 //   phase 0: densities (stage 1; B pulls the row A recoloured in the previous iteration)
 //   phase 1: stress (stage 2; B stores the f_dag_i of its previous output row)
@@ -1074,9 +1074,9 @@ __device__ __forceinline__ void pair_step_b(S* __restrict__ fout, const KParams&
 }
 
 // The same two-step pass with each thread carrying both steps (used for FP32, whose two
-// steps fit one thread's registers at two waves per SIMD; measured 14% faster there than the
-// wave-specialised form at 4096^2, while FP64 runs 46% faster wave-specialised).  Lane t sits
-// on column x0 - 6 + t.  A forms densities on lanes 1..cols+10 and recolours lanes 3..cols+8 (B's
+// steps fit one thread's registers at two waves per SIMD; us per step, this form and the
+// wave-specialised one: 1448^2 50.8 and 48.8, 2048^2 87.8 and 87.7, 4096^2 267 and 285, 8192^2
+// 1042 and 1219; FP64 runs faster wave-specialised).  Lane t sits on column x0 - 6 + t.  A forms densities on lanes 1..cols+10 and recolours lanes 3..cols+8 (B's
 // source columns); B forms densities on lanes 4..cols+7 and outputs lanes 6..cols+5, so
 // cols <= NT - 12.  A runs six rows ahead: iteration j consumes A's source row y0 - 4 + j,
 // A recolours row y0 - 7 + j, B consumes that row at once and outputs row y0 - 10 + j.

@@ -5,8 +5,9 @@
 // State: factored per node, Q + 9 values before streaming: f_dag_i (Q), c_k (3), V_0 and V_1
 // (3 each; V_2 = -(V_0 + V_1)), from which Eq. (13) gives every recoloured population,
 // f_ddag_{i,k} = c_k f_dag_i + w_i V_k . e_i.  Two buffers (read one, write the other), 28
-// values per node for D3Q19 and 36 for D3Q27 in place of the 57 and 81 populations.  A freshly initialised lattice holds its three densities instead (FP64, at the
-// start of the first buffer); the first step reads those.
+// values per node for D3Q19 and 36 for D3Q27 in place of the 57 and 81 populations.  A freshly
+// initialised lattice holds its three densities instead (FP64, at the start of the first buffer);
+// the first step reads those.
 //
 // A step is one launch of the fused march (k3_march): workgroups own x-y blocks of a z
 // segment and march up z.  What a node's densities need of its neighbours' factored values
@@ -84,9 +85,8 @@ int64_t zbytes3(int nx, int ny, int q)
     return ((int64_t)nx * ny + group3<S>() - 1) / group3<S>() * (q + 9) * kLine;
 }
 
-// Makes a lane's 32-bit offset a value the optimiser must take afresh from here: left alone, it
-// widens the offsets to 64 bits outside the march's loop, which doubles their registers and
-// replaces the scalar-base form of every access by a 64-bit vector address.
+// A 32-bit lane offset is made new to the optimiser at each use (lbm3_device.h); a 64-bit one is
+// used as it is.
 __device__ __forceinline__ void refresh(uint64_t&) {}
 // Has x computed here: a sum that only the next iteration reads would be moved to the end of
 // this one, with everything that it is made of kept in registers till then.
@@ -310,7 +310,8 @@ __device__ __forceinline__ void collide3(C rho, C itau, const C (&ft)[Q], const 
 // stores; the stores alone add 109 us, the loads' path through L1 most of the rest (about 15
 // cycles per wave instruction, whatever its width).  Measured against the march over 3 Q stored
 // populations that it replaced, us per step at 128^3 (FP64 / FP32 storage / FP32): D3Q19 723 /
-// 413 / 338 -> 304 / 214 / 192, D3Q27 1159 / 667 / 460 -> 427 / 272 / 251; 48^3 D3Q19 FP64 63 -> 37.
+// 413 / 338 -> 304 / 214 / 192, D3Q27 1159 / 667 / 460 -> 427 / 272 / 251; 48^3 D3Q19 FP64 63 -> 37 (35 with the
+// small tiles).
 // Non-temporal stores made it 1-15% slower, non-temporal loads 10-20%.
 // The arithmetic of every node has a fixed order, so the result does not depend on the tile
 // shape.  With FP64 arithmetic two waves per SIMD fit in registers (512 lanes of 256), with
