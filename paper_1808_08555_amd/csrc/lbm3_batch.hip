@@ -72,6 +72,36 @@ static void drop_graphs(lbm3_batch* b)
         }
 }
 
+// Rows per segment for all instances: those for which rounds of resident workgroups x (rows + 2
+// halo warm-up rows) is least.  Every value from 2 to 512 is tried: of the 17 between powers of
+// two that were, none put the two-step launch of 64 FP32 instances (6.3 M nodes, sides 128 to 512)
+// into one round of the 1024 resident workgroups (64 rows make 1032 tiles), and it took three
+// rounds of 24 rows, 160 us a step; one of 74 takes 153.  37 instances of sides 64 to 512 (2.4 M
+// nodes): FP64 97.3 -> 92.7, FP32 storage 99.7 -> 84.9, FP32 66.6 -> 59.3.
+static int fitted_rows(const lbm3_batch* b, int threads, int slots, int halo)
+{
+    std::vector<long> strips(b->count);
+    for (int i = 0; i < b->count; ++i) {
+        const KParams& kp = b->inst[i].kp;
+        std::vector<Tile> L;
+        plan_lattice(i, kp.nx, kp.ny, threads, kp.ny, (int)elem_bytes(b->prec), L, halo);
+        strips[i] = (long)L.size();
+    }
+    if (slots < 1) slots = 1;
+    int rows = 64;
+    double best = 1e300;
+    for (int r = 2; r <= 512; ++r) {
+        long tiles = 0;
+        for (int i = 0; i < b->count; ++i) tiles += strips[i] * ((b->inst[i].kp.ny + r - 1) / r);
+        const double cost = (double)((tiles + slots - 1) / slots) * (r + 2 * halo);
+        if (cost < best) {
+            best = cost;
+            rows = r;
+        }
+    }
+    return rows;
+}
+
 static int batch_plan(lbm3_batch* b)
 {
     std::vector<Tile> all;
@@ -81,22 +111,7 @@ static int batch_plan(lbm3_batch* b)
     const int eb = (int)elem_bytes(b->prec);
     // default rows per segment: one value for all instances, chosen (like auto_rows) so that
     // the whole launch takes the fewest rounds of resident workgroups, then the fewest rows
-    const int slots = std::max(1, device_slots(b->prec, b->threads));
-    int auto_r = 64;
-    double best = 1e300;
-    for (int r : {2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256, 384, 512}) {
-        long tiles = 0;
-        for (int i = 0; i < b->count; ++i) {
-            std::vector<Tile> L;
-            plan_lattice(i, b->inst[i].kp.nx, b->inst[i].kp.ny, b->threads, r, eb, L);
-            tiles += (long)L.size();
-        }
-        const double cost = (double)((tiles + slots - 1) / slots) * (r + 6);
-        if (cost < best) {
-            best = cost;
-            auto_r = r;
-        }
-    }
+    const int auto_r = fitted_rows(b, b->threads, device_slots(b->prec, b->threads), 3);
     for (int i = 0; i < b->count; ++i) {
         const KParams& kp = b->inst[i].kp;
         auto it = b->rows_by_side.find(kp.nx);
@@ -117,34 +132,21 @@ static int batch_plan(lbm3_batch* b)
     for (int i = 0; i < b->count; ++i) nodes += (int64_t)b->inst[i].kp.nx * b->inst[i].kp.ny;
     // Pairs of steps from 2^19 nodes in FP64 and 5 x 2^18 in FP32 and FP32 storage, single steps on
     // blocks below (us per step of a batch, blocks and pairs, and in brackets the march's single
-    // steps: FP64 52 k nodes 7.5 and 13.6 (18.2), 503 k 30.7 and 29.5 (37.6), 930 k 60.2 and 44.8
-    // (69.8); FP32 storage 930 k 42.8 and 48.0 (61.5), 1.46 M 62.6 and 58.4 (79.5); FP32 52 k 5.6 and
-    // 12.8 (13.3), 930 k 27.0 and 31.8 (39.2), 1.46 M 42.8 and 40.1 (58.2)).
+    // steps: FP64 52 k nodes 7.5 and 13.6 (18.2), 503 k 30.7 and 29.5 (37.6), 930 k 60.2 and 41.0
+    // (69.8); FP32 storage 930 k 42.8 and 48.0 (61.5), 1.46 M 62.6 and 57.2 (79.5); FP32 52 k 5.6 and
+    // 12.8 (13.3), 930 k 27.0 and 31.8 (39.2), 1.46 M 42.8 and 38.5 (58.2)).
     const int64_t min2 = b->prec == Prec::F64 ? (int64_t)1 << 19 : (int64_t)5 << 18;
     const bool want2 = b->pair_mode == 2 || (b->pair_mode == 0 && nodes >= min2);
     // two-step width: 64 columns up to 2^22 nodes, where 128 leave fewer tiles than the device
-    // holds (FP64 2.4 M nodes 96.6 against 100.4, FP32 storage 100 against 110), 128 beyond (6.8 M
-    // nodes: FP64 203 against 213, FP32 134 against 145), and 256 where the instances are wide
+    // holds (with the same rows, FP64 2.4 M nodes 96.6 against 100.4, FP32 storage 100 against 110),
+    // 128 beyond (6.8 M nodes: FP64 203 against 213, FP32 134 against 145), and 256 where the instances are wide
     // enough not to leave half its lanes idle
     int max_side = 0;
     for (int i = 0; i < b->count; ++i) max_side = std::max(max_side, b->inst[i].kp.nx);
     const int t2 = std::min(b->tile_set ? 256 : (max_side >= 768 ? 256 : (nodes <= ((int64_t)1 << 22) ? 64 : 128)), b->threads);
     const int slots2 = want2 ? device_slots_pair(b->prec, t2) : 0;
     if (slots2 > 0) {
-        double best2 = 1e300;
-        for (int r : {2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256, 384, 512}) {
-            long tiles = 0;
-            for (int i = 0; i < b->count; ++i) {
-                std::vector<Tile> L;
-                plan_lattice(i, b->inst[i].kp.nx, b->inst[i].kp.ny, t2, r, eb, L, 6);
-                tiles += (long)L.size();
-            }
-            const double cost = (double)((tiles + slots2 - 1) / slots2) * (r + 12);
-            if (cost < best2) {
-                best2 = cost;
-                b->rows2 = r;
-            }
-        }
+        b->rows2 = fitted_rows(b, t2, slots2, 6);
         for (int i = 0; i < b->count; ++i)
             plan_lattice(i, b->inst[i].kp.nx, b->inst[i].kp.ny, t2, b->rows2, eb, all2, 6);
     }
