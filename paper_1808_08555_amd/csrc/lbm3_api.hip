@@ -413,6 +413,22 @@ static int ensure_staging(lbm3* h, size_t doubles)
     return LBM3_OK;
 }
 
+// The observables of the handle's state: the workgroups' partial sums, then their reduction into
+// out (device).  A factored state of a small lattice is observed on its blocks, without the march's
+// warm-up rows (a call without densities: 64^2 FP64 28.3 us on the march, 22.3 on blocks, 256^2 31.2
+// and 25.5, 512^2, 817 blocks, 42.0 and 41.0, 720^2 49.8 and 57.3: the reduction of many partials).
+constexpr int kObsBlocks = 512;
+static hipError_t observe_into(lbm3* h, double* partials, double* rho_out, double* out)
+{
+    const bool pt = h->p.forcing == LBM3_FORCING_PERTURBATION;
+    const bool blocks = h->blocks && h->fmt == Fmt::FAC && h->bgrid.count <= kObsBlocks;
+    hipError_t e = blocks ? launch_observe_blocks(h->prec, h->buf[h->cur], h->bgrid, partials, rho_out, h->stream, pt)
+                          : launch_observe_tiles(h->prec, h->fmt, h->buf[h->cur], h->dinst, h->dtiles, h->ntiles,
+                                                 h->threads, partials, rho_out, h->stream, pt);
+    if (e == hipSuccess) e = launch_reduce_obs(partials, blocks ? h->bgrid.count : h->ntiles, out, h->stream);
+    return e;
+}
+
 static int ensure_partials(lbm3* h, int nblocks)
 {
     if (h->partials_cap >= nblocks) return LBM3_OK;
@@ -576,14 +592,10 @@ int lbm3_observables(lbm3_t* h, lbm3_obs* out, double* rho_out, double* f_out)
         return LBM3_ESTATE;
     }
     const int64_t n = (int64_t)h->kp.nx * h->kp.ny;
-    int rc = ensure_partials(h, h->ntiles);
+    int rc = ensure_partials(h, std::max(h->ntiles, kObsBlocks));
     if (!rc && (rho_out || f_out)) rc = ensure_staging(h, (size_t)27 * n);
     if (rc) return rc;
-    hipError_t e = launch_observe_tiles(h->prec, h->fmt, h->buf[h->cur], h->dinst, h->dtiles,
-                                        h->ntiles, h->threads, h->partials,
-                                        rho_out ? h->staging : nullptr, h->stream,
-                                        h->p.forcing == LBM3_FORCING_PERTURBATION);
-    if (e == hipSuccess) e = launch_reduce_obs(h->partials, h->ntiles, h->obs_dev, h->stream);
+    hipError_t e = observe_into(h, h->partials, rho_out ? h->staging : nullptr, h->obs_dev);
     if (e == hipSuccess)
         e = hipMemcpyAsync(h->obs_host, h->obs_dev, kObsFields * sizeof(double),
                            hipMemcpyDeviceToHost, h->stream);
@@ -626,10 +638,7 @@ int lbm3_observables_noalloc(lbm3_t* h, lbm3_obs* out)
     double* reduced = base + (size_t)kNoAllocMaxTiles * kObsFields;
     // every workgroup writes all of its partials and the reduction all of its outputs, so
     // nothing left from an earlier call is read
-    hipError_t e = launch_observe_tiles(h->prec, h->fmt, h->buf[h->cur], h->dinst, h->dtiles, h->ntiles,
-                                        h->threads, partials, nullptr, h->stream,
-                                        h->p.forcing == LBM3_FORCING_PERTURBATION);
-    if (e == hipSuccess) e = launch_reduce_obs(partials, h->ntiles, reduced, h->stream);
+    hipError_t e = observe_into(h, partials, nullptr, reduced);
     if (e == hipSuccess)
         e = hipMemcpyAsync(h->obs_host, reduced, kObsFields * sizeof(double), hipMemcpyDeviceToHost, h->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);

@@ -234,11 +234,21 @@ hipError_t tiles_f32_block_list(const void* fin, void* fout, const BlockList& bl
                                 hipStream_t stream);
 hipError_t tiles_f32s_block_list(const void* fin, void* fout, const BlockList& bl, uint32_t salt, bool pt,
                                 hipStream_t stream);
+hipError_t tiles_f64_block_obs(const void* fin, const BlockGrid& bg, bool pt, double* partials, double* rho_out,
+                               hipStream_t stream);
+hipError_t tiles_f32_block_obs(const void* fin, const BlockGrid& bg, bool pt, double* partials, double* rho_out,
+                               hipStream_t stream);
+hipError_t tiles_f32s_block_obs(const void* fin, const BlockGrid& bg, bool pt, double* partials, double* rho_out,
+                               hipStream_t stream);
 // The FP64 block step (factored state in) that also writes the adjoint's tape, as
 // tiles_f64_tape does.
 hipError_t tiles_f64_block_tape(const void* fin, void* fout, const BlockGrid& bg, double* tape, hipStream_t stream);
 hipError_t launch_block(Prec prec, const void* fin, void* fout, const BlockGrid& bg, int64_t step, hipStream_t stream,
                         bool pt = false);
+// Observables of a factored state on the block step's grid: count partials, and rho_out as
+// launch_observe_tiles.
+hipError_t launch_observe_blocks(Prec prec, const void* fin, const BlockGrid& bg, double* partials, double* rho_out,
+                                 hipStream_t stream, bool pt);
 hipError_t launch_block_list(Prec prec, const void* fin, void* fout, const BlockList& bl, int64_t step, hipStream_t stream,
                              bool pt);
 hipError_t launch_block2(Prec prec, const void* fin, void* fout, const BlockGrid& bg, int64_t step, hipStream_t stream,

@@ -179,6 +179,17 @@ hipError_t launch_block(Prec prec, const void* fin, void* fout, const BlockGrid&
     return hipErrorInvalidValue;
 }
 
+hipError_t launch_observe_blocks(Prec prec, const void* fin, const BlockGrid& bg, double* partials, double* rho_out,
+                                 hipStream_t st, bool pt)
+{
+    switch (prec) {
+        case Prec::F64: return tiles_f64_block_obs(fin, bg, pt, partials, rho_out, st);
+        case Prec::F32S: return tiles_f32s_block_obs(fin, bg, pt, partials, rho_out, st);
+        case Prec::F32: return tiles_f32_block_obs(fin, bg, pt, partials, rho_out, st);
+    }
+    return hipErrorInvalidValue;
+}
+
 hipError_t launch_block_list(Prec prec, const void* fin, void* fout, const BlockList& bl, int64_t step, hipStream_t st,
                              bool pt)
 {

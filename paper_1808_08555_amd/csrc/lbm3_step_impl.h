@@ -423,6 +423,25 @@ __device__ __forceinline__ void force_or_stress(const C (*tring)[3][NT], int s0,
     }
 }
 
+// A node's part of the observables: densities, momentum, kinetic energy, max|u|, nonfinite flag.
+template <typename C>
+__device__ __forceinline__ void observe_node(double (&acc)[kObsFields], const C (&rk)[3], C ux, C uy, C mxh, C myh)
+{
+    const double rho = double(rk[0]) + double(rk[1]) + double(rk[2]);
+    acc[0] += double(rk[0]);
+    acc[1] += double(rk[1]);
+    acc[2] += double(rk[2]);
+    acc[3] += double(mxh);
+    acc[4] += double(myh);
+    const double uu = double(ux) * double(ux) + double(uy) * double(uy);
+    acc[5] += 0.5 * rho * uu;
+    const double um = sqrt(uu);
+    acc[6] = (um > acc[6] || um != um) ? um : acc[6];
+    const bool fin_ok = isfinite(double(rk[0])) && isfinite(double(rk[1])) && isfinite(double(rk[2])) &&
+                        isfinite(double(mxh)) && isfinite(double(myh)) && isfinite(uu);
+    if (!fin_ok) acc[7] = 1.0;
+}
+
 // The y-marching body shared by the stepping and observing kernels.  The workgroup owns
 // output columns [x0, x0 + cols) (cols <= NT - 6) and output rows [y0, y0 + rows).  Lane t
 // sits on column x0 - 3 + t; lanes 1..cols+4 form densities, 2..cols+3 gradients and
@@ -654,20 +673,7 @@ __device__ __forceinline__ void march(const S* __restrict__ fin, S* __restrict__
                 for (int q = 0; q < 4; ++q)
                     st_at(fout + ((int64_t)(12 + q) * pl + orow), xoff, to_storage<S, C>(V[q], bits));
             } else {
-                const double rho = double(rB[0]) + double(rB[1]) + double(rB[2]);
-                acc[0] += double(rB[0]);
-                acc[1] += double(rB[1]);
-                acc[2] += double(rB[2]);
-                acc[3] += double(mxh);
-                acc[4] += double(myh);
-                const double uu = double(ux) * double(ux) + double(uy) * double(uy);
-                acc[5] += 0.5 * rho * uu;
-                const double um = sqrt(uu);
-                acc[6] = (um > acc[6] || um != um) ? um : acc[6];
-                const bool fin_ok = isfinite(double(rB[0])) && isfinite(double(rB[1])) &&
-                                    isfinite(double(rB[2])) && isfinite(double(mxh)) &&
-                                    isfinite(double(myh)) && isfinite(uu);
-                if (!fin_ok) acc[7] = 1.0;
+                observe_node<C>(acc, rB, ux, uy, mxh, myh);
                 if (rho_out) {
                     const int64_t N = (int64_t)nx * ny;
                     const int64_t o = (int64_t)yo * nx + x;
@@ -1492,7 +1498,9 @@ int tiles_occupancy(int threads)
 //      (collide_recolour), the factored store, rounded as the march rounds it.
 // Factored input and output only (a state in the 27-population format takes one step of
 // the march first).  With TAPE (FP64) the owned lanes also write the adjoint's tape as the
-// march does: densities, totals, concentration gradients and force, tape[20][ny][nx].
+// march does: densities, totals, concentration gradients and force, tape[20][ny][nx].  With OBS
+// the owned lanes' observables are summed over the workgroup into tape[8 blockIdx.x ..] instead of
+// a next state, and with rho_out their densities are written.
 constexpr int kBlockX = 32;
 // The tape of a step: none, stored as usual, or past the caches.  On a lattice whose two state
 // buffers and a step's tape (416 bytes per node) outgrow the 256 MB last-level cache, a tape left
@@ -1644,9 +1652,10 @@ __device__ __forceinline__ KParams block_of(const BlockList& bl, int& x0, int& y
     return bl.inst[tl.inst].kp;
 }
 
-template <typename S, typename C, int BX, int BY, bool PT, Tape TAPE = Tape::None, typename Grid = BlockGrid>
+template <typename S, typename C, int BX, int BY, bool PT, Tape TAPE = Tape::None, typename Grid = BlockGrid, bool OBS = false>
 __global__ __launch_bounds__(BX * BY) __attribute__((amdgpu_waves_per_eu(2))) void k_block(
-    const S* __restrict__ fin, S* __restrict__ fout, Grid bg, uint32_t salt, double* __restrict__ tape = nullptr)
+    const S* __restrict__ fin, S* __restrict__ fout, Grid bg, uint32_t salt, double* __restrict__ tape = nullptr,
+    double* __restrict__ rho_out = nullptr)
 {
     static_assert(BX % 64 == 0 || 64 % BX == 0, "waves are whole tile rows");
     __shared__ BlockLds<C, BX, BY> L;
@@ -1654,7 +1663,8 @@ __global__ __launch_bounds__(BX * BY) __attribute__((amdgpu_waves_per_eu(2))) vo
     int64_t off;
     const KParams kp = block_of(bg, x0, y0, cols, rows, off);
     fin += off;
-    fout += off;
+    if constexpr (!OBS) fout += off;
+    double acc[kObsFields] = {0, 0, 0, 0, 0, 0, 0, 0};
     if constexpr (kRounds<S, C> && std::is_same_v<Grid, BlockList>) {
         if (bg.step_dev) salt = step_salt(*bg.step_dev);
     }
@@ -1732,14 +1742,27 @@ __global__ __launch_bounds__(BX * BY) __attribute__((amdgpu_waves_per_eu(2))) vo
         }
         C fd[9], ck[3], V[6], ux, uy, mxh, myh;
         collide_recolour<C, PT>(f0, r0, irho, n, Fx, Fy, K, fd, ck, V, ux, uy, mxh, myh, Tn);
-        NodeBits bits(((uint32_t)y * (uint32_t)nx + (uint32_t)x) * 27u ^ salt);
-        const uint32_t o = ys[1] + xs[1];
+        if constexpr (OBS) {
+            observe_node<C>(acc, r0, ux, uy, mxh, myh);
+            if (rho_out) {
 #pragma unroll
-        for (int i = 0; i < 9; ++i) st_plain(fout, o + (uint32_t)i * plane, to_storage<S, C>(fd[i], bits));
+                for (int k = 0; k < 3; ++k) rho_out[k * NN + on] = double(r0[k]);
+            }
+        } else {
+            NodeBits bits(((uint32_t)y * (uint32_t)nx + (uint32_t)x) * 27u ^ salt);
+            const uint32_t o = ys[1] + xs[1];
 #pragma unroll
-        for (int k = 0; k < 3; ++k) st_plain(fout, o + (uint32_t)(9 + k) * plane, to_storage<S, C>(ck[k], bits));
+            for (int i = 0; i < 9; ++i) st_plain(fout, o + (uint32_t)i * plane, to_storage<S, C>(fd[i], bits));
 #pragma unroll
-        for (int q = 0; q < 4; ++q) st_plain(fout, o + (uint32_t)(12 + q) * plane, to_storage<S, C>(V[q], bits));
+            for (int k = 0; k < 3; ++k) st_plain(fout, o + (uint32_t)(9 + k) * plane, to_storage<S, C>(ck[k], bits));
+#pragma unroll
+            for (int q = 0; q < 4; ++q) st_plain(fout, o + (uint32_t)(12 + q) * plane, to_storage<S, C>(V[q], bits));
+        }
+    }
+    if constexpr (OBS) {
+        static_assert(sizeof(L) >= sizeof(double) * kObsFields * BX * BY, "LDS too small for the reduction");
+        __syncthreads();  // the stress has been read by every lane
+        block_reduce_obs<BX * BY>(acc, reinterpret_cast<double (*)[BX * BY]>(&L), tape + (int64_t)blockIdx.x * kObsFields);
     }
 }
 
@@ -1888,6 +1911,25 @@ hipError_t tiles_block_any(const void* fin, void* fout, const BlockGrid& bg, uin
                   : block_launch<S, C, kBlockYSmall, false>(fin, fout, bg, salt, nullptr, st);
     return pt ? block_launch<S, C, kBlockY, true>(fin, fout, bg, salt, nullptr, st)
               : block_launch<S, C, kBlockY, false>(fin, fout, bg, salt, nullptr, st);
+}
+
+template <typename S, typename C, int BY, bool PT>
+hipError_t block_obs_launch(const void* fin, const BlockGrid& bg, double* partials, double* rho_out, hipStream_t st)
+{
+    hipLaunchKernelGGL((k_block<S, C, kBlockX, BY, PT, Tape::None, BlockGrid, true>), dim3(bg.count), dim3(kBlockX * BY), 0,
+                       st, (const S*)fin, (S*)nullptr, bg, 0u, partials, rho_out);
+    return hipGetLastError();
+}
+
+template <typename S, typename C>
+hipError_t tiles_block_obs_any(const void* fin, const BlockGrid& bg, bool pt, double* partials, double* rho_out,
+                               hipStream_t st)
+{
+    if (bg.lanes_y == kBlockYSmall)
+        return pt ? block_obs_launch<S, C, kBlockYSmall, true>(fin, bg, partials, rho_out, st)
+                  : block_obs_launch<S, C, kBlockYSmall, false>(fin, bg, partials, rho_out, st);
+    return pt ? block_obs_launch<S, C, kBlockY, true>(fin, bg, partials, rho_out, st)
+              : block_obs_launch<S, C, kBlockY, false>(fin, bg, partials, rho_out, st);
 }
 
 template <typename S, typename C, int BY>

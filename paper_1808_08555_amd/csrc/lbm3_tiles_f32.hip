@@ -39,4 +39,10 @@ hipError_t tiles_f32_block_list(const void* fin, void* fout, const BlockList& bl
     return tiles_block_list_any<float, float>(fin, fout, bl, salt, pt, stream);
 }
 
+hipError_t tiles_f32_block_obs(const void* fin, const BlockGrid& bg, bool pt, double* partials, double* rho_out,
+                               hipStream_t stream)
+{
+    return tiles_block_obs_any<float, float>(fin, bg, pt, partials, rho_out, stream);
+}
+
 }  // namespace tcg

@@ -41,4 +41,10 @@ hipError_t tiles_f32s_block_list(const void* fin, void* fout, const BlockList& b
     return tiles_block_list_any<float, double>(fin, fout, bl, salt, pt, stream);
 }
 
+hipError_t tiles_f32s_block_obs(const void* fin, const BlockGrid& bg, bool pt, double* partials, double* rho_out,
+                               hipStream_t stream)
+{
+    return tiles_block_obs_any<float, double>(fin, bg, pt, partials, rho_out, stream);
+}
+
 }  // namespace tcg

@@ -56,4 +56,10 @@ hipError_t tiles_f64_block_list(const void* fin, void* fout, const BlockList& bl
     return tiles_block_list_any<double, double>(fin, fout, bl, salt, pt, stream);
 }
 
+hipError_t tiles_f64_block_obs(const void* fin, const BlockGrid& bg, bool pt, double* partials, double* rho_out,
+                               hipStream_t stream)
+{
+    return tiles_block_obs_any<double, double>(fin, bg, pt, partials, rho_out, stream);
+}
+
 }  // namespace tcg

@@ -754,6 +754,28 @@ def test_two_step_blocks_equal_single_steps_bitwise(shape, threads, forcing, pre
     assert np.array_equal(fa, fb)
 
 
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "fp32_storage"])
+@pytest.mark.parametrize("shape", [(1, 1), (28, 4), (29, 5), (31, 33), (448, 64), (449, 64), (448, 384), (448, 385)])
+def test_observables_on_blocks_equal_the_march(shape, precision):
+    """Observables of a stepped small lattice (on its blocks: of both heights, up to 512 of them and
+    one row beyond) against those of the march: densities and max|u| bit for bit, the sums, whose
+    terms are the same and whose order differs, to 1e-12 of the sum of their absolute values."""
+    nx, ny = shape
+    rho = inputs.random_mixture(nx, ny, 8, tiny_fraction=0.0)
+    A = lbm3.Lattice(nx, ny, precision=precision).init(rho).step(3)
+    B = lbm3.Lattice(nx, ny, precision=precision).init(rho).set_tile(64, 0).step(3)
+    oa, ra, _ = A.observables(want_rho=True)
+    ob, rb, _ = B.observables(want_rho=True)
+    A.close()
+    B.close()
+    assert np.array_equal(ra, rb)
+    assert oa["u_max"] == ob["u_max"] and oa["nonfinite"] == ob["nonfinite"] == 0
+    total = float(rb.sum())
+    assert np.abs(np.asarray(oa["mass"]) - np.asarray(ob["mass"])).max() <= 1e-12 * total
+    assert np.abs(np.asarray(oa["momentum"]) - np.asarray(ob["momentum"])).max() <= 1e-12 * total * ob["u_max"]
+    assert abs(oa["kinetic_energy"] - ob["kinetic_energy"]) <= 1e-12 * max(ob["kinetic_energy"], 1e-300)
+
+
 def _factored_planes(L):
     """The 16 stored planes of a stepped lattice, as [16, ny, nx] in their storage type."""
     ptr, eb, pl, pitch, nq = lbm3.lbm3_state_buffer(L.h)
