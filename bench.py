@@ -237,7 +237,7 @@ def bench_d3q19(torch, lbm3, inputs, n: int, steps: int, precision: str = "fp64"
     t = a.elapsed_time(b) / 1e3
     L.close()
     lu = n ** 3 * steps
-    b = 2 * (q + 9) * (8 if precision == "fp64" else 4)
+    b = 2 * (q + 9 + (precision == "fp32_storage")) * (8 if precision == "fp64" else 4)
     res = {"workload": f"D3Q{q} {n}^3, two tangent spheres of radius {R:g}, {precision}, {steps} steps",
            "mlups": round(lu / t / 1e6, 1), "bytes_per_lu_stated": b,
            "frac_of_peak": round(b * lu / t / 1e9 / HBM_PEAK_GBS, 4), "kernel": "k3_march (one launch per step)"}

@@ -309,7 +309,7 @@ int lbm3_adjoint_pipeline_slots(int64_t nodes, uint64_t ws_two_slots, uint64_t w
  * number of links, 19 or 27.
  * lbm3d_create_lattice: p as for lbm3_create (nx, ny from it), nz in 1..65535, q = 19 or
  *   27, at most 2^29 nodes (else LBM3_EINVAL); allocates the two state buffers of Q + 9
- *   values per node (in the storage type) and a staging buffer for exports (3Q + 3 doubles per
+ *   values per node (in the storage type; Q + 10 with LBM3_FP32_STORAGE) and a staging buffer for exports (3Q + 3 doubles per
  *   node).
  * lbm3d_create: lbm3d_create_lattice with q = 19.
  * lbm3d_init_fields: rho host [3][nz][ny][nx] (x fastest), finite, >= 0, with rho > 0 at

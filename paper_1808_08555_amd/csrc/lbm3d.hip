@@ -5,7 +5,8 @@
 // State: factored per node, Q + 9 values before streaming: f_dag_i (Q), c_k (3), V_0 and V_1
 // (3 each; V_2 = -(V_0 + V_1)), from which Eq. (13) gives every recoloured population,
 // f_ddag_{i,k} = c_k f_dag_i + w_i V_k . e_i.  Two buffers (read one, write the other), 28
-// values per node for D3Q19 and 36 for D3Q27 in place of the 57 and 81 populations.  A freshly
+// values per node for D3Q19 and 36 for D3Q27 in place of the 57 and 81 populations; with FP32
+// storage one word more, further bits of the c_k (split_c).  A freshly
 // initialised lattice holds its three densities instead (FP64, at the start of the first buffer);
 // the first step reads those.
 //
@@ -73,16 +74,44 @@ constexpr int64_t group3()
     return kLine / (int64_t)sizeof(S);
 }
 // byte offset of node n = y nx + x of a z plane
-template <typename S, int Q, typename Off>
+template <typename S, int NV, typename Off>
 __host__ __device__ __forceinline__ Off node_off3(int64_t n)
 {
     const int64_t G = group3<S>();
-    return (Off)(n / G) * (Off)((Q + 9) * kLine) + (Off)(n % G) * (Off)sizeof(S);
+    return (Off)(n / G) * (Off)(NV * kLine) + (Off)(n % G) * (Off)sizeof(S);
 }
 template <typename S>
-int64_t zbytes3(int nx, int ny, int q)
+int64_t zbytes3(int nx, int ny, int nv)
 {
-    return ((int64_t)nx * ny + group3<S>() - 1) / group3<S>() * (q + 9) * kLine;
+    return ((int64_t)nx * ny + group3<S>() - 1) / group3<S>() * nv * kLine;
+}
+// values of a node: f_dag_i (Q), c_k (3), V_0 and V_1 (6) and, where stores round, the word of
+// the c_k's further bits
+template <typename S, typename C, int Q>
+constexpr int kVals3 = Q + 9 + (kRounds<S, C> ? 1 : 0);
+inline int vals3(Prec prec, int q) { return q + 9 + (prec == Prec::F32S ? 1 : 0); }
+
+// With FP32 storage of FP64 arithmetic a c_k keeps the ten mantissa bits after a float's 23 as
+// well, the three of a node in one word (bits 10 k to 10 k + 9).  One c_k multiplies the f_dag_i of
+// every link: rounded to a float, its error would pass to a density whole, where those of
+// 3 Q populations, rounded one by one, average.  Split in two: the float toward zero, and the
+// bits; both of the value rounded stochastically to 33 mantissa bits (as round_stochastic, whose
+// notes on zero, Inf and NaN hold; below the smallest normal float the further bits change a
+// value by no more than the float's own last place).  RMS error of the densities against FP64,
+// 3 Q populations, c_k in floats, and with the bits: random mixture 20^3 after 10 steps D3Q19
+// 1.5e-8, 2.5e-8, 1.3e-8, D3Q27 1.7e-8, 2.5e-8, 1.4e-8; two spheres after 100 3.0e-8, 4.2e-8,
+// 2.8e-8 and 3.1e-8, 3.5e-8, 2.9e-8.  Us per step at 128^3 without the bits and with them: D3Q19
+// 217 and 220, D3Q27 268 and 276.
+__device__ __forceinline__ float split_c(double v, uint32_t bits, int k, uint32_t& word)
+{
+    const uint64_t s = (uint64_t)__double_as_longlong(v) + (uint64_t)(bits >> 13);
+    word |= ((uint32_t)(s >> 19) & 0x3ffu) << (10 * k);
+    return (float)__longlong_as_double((long long)(s & ~((1ull << 29) - 1ull)));
+}
+__device__ __forceinline__ double join_c(float hi, uint32_t word, int k)
+{
+    const uint64_t u = (uint64_t)__double_as_longlong((double)hi);
+    return __longlong_as_double((long long)(u | (uint64_t)((word >> (10 * k)) & 0x3ffu) << 19));
 }
 
 // A 32-bit lane offset is made new to the optimiser at each use (lbm3_device.h); a 64-bit one is
@@ -393,7 +422,7 @@ __device__ __forceinline__ void march3(const void* __restrict__ in, const Geo3& 
 {
     using Sh = Tile3Shape<ROWS>;
     using Hold = Hold3<S, C, Q, ROWS>;
-    constexpr int TX = Sh::TX, T3 = Sh::T;
+    constexpr int TX = Sh::TX, T3 = Sh::T, NV = kVals3<S, C, Q>;
     const int t = threadIdx.x, tx = t % TX, ty = t / TX;
     const int sx = tl.sx;  // lane tx sits on column x0 - sx + tx
     const bool in2 = tx >= sx - 1 && tx <= tl.cols + sx && ty >= 1 && ty <= tl.rows + 2;
@@ -406,7 +435,7 @@ __device__ __forceinline__ void march3(const void* __restrict__ in, const Geo3& 
         const int64_t ys[3] = {(int64_t)(y == 0 ? g.ny - 1 : y - 1) * g.nx, (int64_t)y * g.nx,
                                (int64_t)(y == g.ny - 1 ? 0 : y + 1) * g.nx};
 #pragma unroll
-        for (int a = 0; a < 9; ++a) lo[a] = node_off3<S, Q, Off>(ys[a / 3] + xs[a % 3]);
+        for (int a = 0; a < 9; ++a) lo[a] = node_off3<S, NV, Off>(ys[a / 3] + xs[a % 3]);
     }
     const int64_t pl = (int64_t)g.nx * g.ny, np = (int64_t)y * g.nx + x;  // nodes of a plane; the lane's
     const uint64_t fin = (uint64_t)in, fout = (uint64_t)out;
@@ -439,7 +468,7 @@ __device__ __forceinline__ void march3(const void* __restrict__ in, const Geo3& 
     else if (e < 2 * cw + Sh::TY) ru = 0, rw = e - 2 * cw + 1;
     else ru = Sh::CX - 1, rw = e - 2 * cw - Sh::TY + 1;
     const bool ring = edge_cv && e < 2 * cw + (sx == 2 ? 2 * Sh::TY : 0) && ru <= tl.cols + 5 && rw <= tl.rows + 5;
-    Off ro = node_off3<S, Q, Off>((int64_t)wrapi(tl.y0 - 3 + rw, g.ny) * g.nx + wrapi(tl.x0 - 3 + ru, g.nx));
+    Off ro = node_off3<S, NV, Off>((int64_t)wrapi(tl.y0 - 3 + rw, g.ny) * g.nx + wrapi(tl.x0 - 3 + ru, g.nx));
     lds_t* cr = (lds_t*)&L.cv[0][0] + rw * Sh::CX + ru;
     settle(cr);
 
@@ -457,7 +486,7 @@ __device__ __forceinline__ void march3(const void* __restrict__ in, const Geo3& 
         const uint64_t base = fin + s * g.zbytes;
         refresh(o);
 #pragma unroll
-        for (int i = 0; i < 9; ++i) v[i] = ld_value<S>(base, o, Q + i);
+        for (int i = 0; i < NV - Q; ++i) v[i] = ld_value<S>(base, o, Q + i);
     };
     auto load_t = [&](int p, S (&v)[Q]) {
         const uint64_t base[3] = {fin + (p == 0 ? g.nz - 1 : p - 1) * g.zbytes, fin + p * g.zbytes,
@@ -477,7 +506,7 @@ __device__ __forceinline__ void march3(const void* __restrict__ in, const Geo3& 
     }
     // vf: f_dag_i; vc: c_k, V_k of the lane's node; vx: totals, or in the two edge waves the c_k,
     // V_k of the ring
-    S vf[Q], vx[Q], vc[9];
+    S vf[Q], vx[Q], vc[NV - Q];
 #pragma unroll
     for (int i = 0; i < Q; ++i) vf[i] = vx[i] = S(0);
 
@@ -485,13 +514,18 @@ __device__ __forceinline__ void march3(const void* __restrict__ in, const Geo3& 
     const int J = tl.depth + 6;
     RowCursor sf(tl.z0 - 3, g.nz), sc(tl.z0 - 3, g.nz);  // the next plane of load_f and of load_cv
     RowCursor dst(tl.z0 - 4, g.nz), tot(tl.z0, g.nz);    // plane s - 1; the next plane of load_t
-    auto publish = [&]() {
+    auto expand = [&](lds_t* p, const S* v) {
 #pragma unroll
-        for (int i = 0; i < 9; ++i) cv[i * NC] = C(vc[i]);
-        if (ring) {
-#pragma unroll
-            for (int i = 0; i < 9; ++i) cr[i * NC] = C(vx[i]);
+        for (int i = 0; i < 9; ++i) {
+            if constexpr (kRounds<S, C>)
+                p[i * NC] = i < 3 ? join_c(v[i], __float_as_uint(v[9]), i) : C(v[i]);
+            else
+                p[i * NC] = v[i];
         }
+    };
+    auto publish = [&]() {
+        expand(cv, vc);
+        if (ring) expand(cr, vx);
     };
     auto load_next_cv = [&]() {
         const int s = sc.next();
@@ -626,8 +660,15 @@ __device__ __forceinline__ void march3(const void* __restrict__ in, const Geo3& 
                     bits.skip(Q);
                     const uint64_t base = fout + z2 * g.zbytes;
                     refresh(lo[4]);
+                    if constexpr (kRounds<S, C>) {
+                        uint32_t word = 0;
 #pragma unroll
-                    for (int k = 0; k < 3; ++k) st_value<S>(base, lo[4], Q + k, to_storage<S, C>(cc[k], bits));
+                        for (int k = 0; k < 3; ++k) st_value<S>(base, lo[4], Q + k, split_c(cc[k], bits.next(), k, word));
+                        st_value<S>(base, lo[4], Q + 9, __uint_as_float(word));
+                    } else {
+#pragma unroll
+                        for (int k = 0; k < 3; ++k) st_value<S>(base, lo[4], Q + k, S(cc[k]));
+                    }
 #pragma unroll
                     for (int a = 0; a < 6; ++a) st_value<S>(base, lo[4], Q + 3 + a, to_storage<S, C>(V[a], bits));
                 }
@@ -794,9 +835,15 @@ __global__ __launch_bounds__(256) void k3_export(const void* __restrict__ in, In
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
         const int64_t zs = nb.zo[1 - L3Z[i]];
-        const int64_t o = node_off3<S, Q, int64_t>(nb.at(-L3X[i], -L3Y[i], -L3Z[i]) - zs);
+        const int64_t o = node_off3<S, kVals3<S, C, Q>, int64_t>(nb.at(-L3X[i], -L3Y[i], -L3Z[i]) - zs);
         const char* b = (const char*)in + zs / pl * g.zbytes + o;
         auto value = [&](int v) { return C(*(const S*)(b + v * kLine)); };
+        auto conc = [&](int k) {
+            if constexpr (kRounds<S, C>)
+                return join_c(*(const S*)(b + (Q + k) * kLine), *(const uint32_t*)(b + (Q + 9) * kLine), k);
+            else
+                return value(Q + k);
+        };
         const C fd = value(i);
         C V[3][3];
 #pragma unroll
@@ -808,7 +855,7 @@ __global__ __launch_bounds__(256) void k3_export(const void* __restrict__ in, In
 #pragma unroll
         for (int k = 0; k < 3; ++k)
             f[(int64_t)(k * Q + i) * g.N + j] =
-                double(fma(value(Q + k), fd, w3<C, Q>(i) * edot<C>(i, V[k][0], V[k][1], V[k][2])));
+                double(fma(conc(k), fd, w3<C, Q>(i) * edot<C>(i, V[k][0], V[k][1], V[k][2])));
     }
 }
 
@@ -1054,7 +1101,8 @@ int lbm3d_create_lattice(const lbm3_params* p, int32_t nz, int32_t q, void* hip_
     h->q = q;
     derive(p, &h->kp, nullptr, nullptr, nullptr);
     h->g = Geo3{p->nx, p->ny, nz, (int64_t)p->nx * p->ny * nz,
-                h->prec == Prec::F64 ? zbytes3<double>(p->nx, p->ny, q) : zbytes3<float>(p->nx, p->ny, q)};
+                h->prec == Prec::F64 ? zbytes3<double>(p->nx, p->ny, vals3(h->prec, q))
+                                     : zbytes3<float>(p->nx, p->ny, vals3(h->prec, q))};
     h->stream = (hipStream_t)hip_stream;
     const int64_t N = h->g.N;
     hipError_t e = hipSuccess;
