@@ -282,3 +282,39 @@ def test_fp32_storage_is_as_exact_as_populations_rounded_one_by_one(q):
     L.close()
     print(q, "rms error", err, "3 Q populations", model)
     assert err <= 1.05 * np.mean(model)
+
+
+@pytest.mark.parametrize("q", QS)
+@pytest.mark.parametrize("r", [1.0, 0.9993, 0.87])
+def test_fp32_fluid_at_rest_keeps_its_density(r, q):
+    """A uniform fluid at rest, FP32, 60 steps: its density stays within 4 units of 2^-24.  A step's
+    roundings (of the Q products w_i rho, and of their sum, small ones first) come to less than
+    that, and the drift ends at a density that they leave as it is; summed link by link it went on
+    to 8 units and more."""
+    rho = np.zeros((3, 5, 13, 33))
+    rho[2] = np.float32(r)
+    L = lbm3.Lattice3D(33, 13, 5, (0.01,) * 3, precision="fp32", q=q).init(rho).step(60)
+    d = (L.densities() - rho) * 2.0 ** 24
+    L.close()
+    print(q, r, d.min(), d.max())
+    assert np.abs(d).max() <= 4
+
+
+@pytest.mark.parametrize("q", QS)
+def test_fp32_is_as_exact_as_populations_summed_in_fp32(q):
+    """A random mixture of three fluids on 20^3, one step, FP32: the densities' RMS error against
+    the FP64 oracle is no larger than that of the exact populations, each rounded to FP32, added
+    one after another in FP32."""
+    rho = inputs.random_mixture_3d(20, 20, 20, 4, tiny_fraction=0.0)
+    p = oracle.Params(20, 20, SIG, TAU)
+    f = d3.step(p, 20, d3.init(p, 20, rho, q))
+    exact = f.sum(axis=1)
+    model = np.zeros(exact.shape, np.float32)
+    for i in range(q):
+        model += f[:, i].astype(np.float32)
+    rms = lambda r: float(np.sqrt(((r - exact) ** 2).mean()))  # noqa: E731
+    L = lbm3.Lattice3D(20, 20, 20, SIG, TAU, precision="fp32", q=q).init(rho).step(1)
+    err = rms(L.densities())
+    L.close()
+    print(q, "rms error", err, "populations", rms(model))
+    assert err <= rms(model)
