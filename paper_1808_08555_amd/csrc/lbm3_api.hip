@@ -291,9 +291,9 @@ int upload_plan(lbm3* h)
     if (h->dtiles2) (void)hipFree(h->dtiles2);
     h->dtiles = h->dtiles2 = nullptr;
     h->ntiles = h->ntiles2 = 0;
-    hipError_t e = hipMalloc((void**)&h->dtiles, T.size() * sizeof(Tile));
-    if (e == hipSuccess && !T2.empty()) e = hipMalloc((void**)&h->dtiles2, T2.size() * sizeof(Tile));
-    if (e == hipSuccess && !h->dinst) e = hipMalloc((void**)&h->dinst, sizeof(Instance));
+    hipError_t e = device_malloc((void**)&h->dtiles, T.size() * sizeof(Tile));
+    if (e == hipSuccess && !T2.empty()) e = device_malloc((void**)&h->dtiles2, T2.size() * sizeof(Tile));
+    if (e == hipSuccess && !h->dinst) e = device_malloc((void**)&h->dinst, sizeof(Instance));
     Instance I{};
     I.kp = h->kp;
     I.offset = 0;
@@ -438,7 +438,7 @@ static int ensure_partials(lbm3* h, int nblocks)
         h->partials = nullptr;
         h->partials_cap = 0;
     }
-    hipError_t e = hipMalloc((void**)&h->partials, (size_t)nblocks * kObsFields * sizeof(double));
+    hipError_t e = device_malloc((void**)&h->partials, (size_t)nblocks * kObsFields * sizeof(double));
     if (e != hipSuccess) return hip_fail(e, "hipMalloc(partials)");
     h->partials_cap = nblocks;
     return LBM3_OK;
@@ -492,7 +492,7 @@ int lbm3_create(const lbm3_params* p, void* hip_stream, lbm3_t** out)
         lbm3_destroy(h);
         return rc;
     }
-    e = hipMalloc((void**)&h->obs_dev, kObsFields * sizeof(double));
+    e = device_malloc((void**)&h->obs_dev, kObsFields * sizeof(double));
     if (e == hipSuccess) e = hipHostMalloc((void**)&h->obs_host, kObsFields * sizeof(double));
     if (e != hipSuccess) {
         rc = hip_fail(e, "allocation of observables buffers");

@@ -172,14 +172,14 @@ static int batch_plan(lbm3_batch* b)
     b->dtiles = b->dtiles2 = b->dblocks = nullptr;
     b->dobs = nullptr;
     b->ntiles = b->ntiles2 = b->nblocks = 0;
-    hipError_t e = hipMalloc((void**)&b->dtiles, T.size() * sizeof(Tile));
-    if (e == hipSuccess) e = hipMalloc((void**)&b->dobs, obs.size() * sizeof(Tile));
-    if (e == hipSuccess && !T2.empty()) e = hipMalloc((void**)&b->dtiles2, T2.size() * sizeof(Tile));
+    hipError_t e = device_malloc((void**)&b->dtiles, T.size() * sizeof(Tile));
+    if (e == hipSuccess) e = device_malloc((void**)&b->dobs, obs.size() * sizeof(Tile));
+    if (e == hipSuccess && !T2.empty()) e = device_malloc((void**)&b->dtiles2, T2.size() * sizeof(Tile));
     if (e == hipSuccess) e = hipMemcpy(b->dtiles, T.data(), T.size() * sizeof(Tile), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(b->dobs, obs.data(), obs.size() * sizeof(Tile), hipMemcpyHostToDevice);
     if (e == hipSuccess && !T2.empty())
         e = hipMemcpy(b->dtiles2, T2.data(), T2.size() * sizeof(Tile), hipMemcpyHostToDevice);
-    if (e == hipSuccess && !TB.empty()) e = hipMalloc((void**)&b->dblocks, TB.size() * sizeof(Tile));
+    if (e == hipSuccess && !TB.empty()) e = device_malloc((void**)&b->dblocks, TB.size() * sizeof(Tile));
     if (e == hipSuccess && !TB.empty())
         e = hipMemcpy(b->dblocks, TB.data(), TB.size() * sizeof(Tile), hipMemcpyHostToDevice);
     if (e != hipSuccess) return hip_fail(e, "batch tile plan upload");
@@ -198,7 +198,7 @@ static int ensure_batch_staging(lbm3_batch* b, size_t doubles)
         b->staging = nullptr;
         b->staging_cap = 0;
     }
-    hipError_t e = hipMalloc((void**)&b->staging, doubles * sizeof(double));
+    hipError_t e = device_malloc((void**)&b->staging, doubles * sizeof(double));
     if (e != hipSuccess) return hip_fail(e, "hipMalloc(batch staging)");
     b->staging_cap = doubles;
     return LBM3_OK;
@@ -330,14 +330,14 @@ int lbm3_batch_create(const lbm3_params* p, int32_t count, void* hip_stream, lbm
     }
     const size_t bytes = (size_t)total * elem_bytes(b->prec);
     if (e == hipSuccess) e = alloc_state_pair(bytes, b->buf);
-    if (e == hipSuccess) e = hipMalloc((void**)&b->dinst, count * sizeof(Instance));
+    if (e == hipSuccess) e = device_malloc((void**)&b->dinst, count * sizeof(Instance));
     if (e == hipSuccess)
         e = hipMemcpy(b->dinst, b->inst.data(), count * sizeof(Instance), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMalloc((void**)&b->obs_dev, kObsFields * sizeof(double));
+    if (e == hipSuccess) e = device_malloc((void**)&b->obs_dev, kObsFields * sizeof(double));
     if (e == hipSuccess) e = hipHostMalloc((void**)&b->obs_host, kObsFields * sizeof(double));
     if (e == hipSuccess && b->prec == Prec::F32S) {
         const int64_t zero = 0;
-        e = hipMalloc((void**)&b->dstep, sizeof(int64_t));
+        e = device_malloc((void**)&b->dstep, sizeof(int64_t));
         if (e == hipSuccess) e = hipMemcpy(b->dstep, &zero, sizeof zero, hipMemcpyHostToDevice);
     }
     if (e != hipSuccess) {
@@ -515,7 +515,7 @@ int lbm3_batch_observables(lbm3_batch_t* b, int32_t idx, lbm3_obs* out, double* 
         if (b->partials) (void)hipFree(b->partials);
         b->partials = nullptr;
         b->partials_cap = 0;
-        hipError_t e = hipMalloc((void**)&b->partials, (size_t)nb * kObsFields * sizeof(double));
+        hipError_t e = device_malloc((void**)&b->partials, (size_t)nb * kObsFields * sizeof(double));
         if (e != hipSuccess) return hip_fail(e, "hipMalloc(batch partials)");
         b->partials_cap = nb;
     }

@@ -58,7 +58,8 @@ int check_rho_fields(const double* rho, const double* u, int64_t n);
 int upload_plan(lbm3* h);
 // Device memory that outlives its owner for the next one (lbm3_pool.hip): pool_free may keep a
 // block, so its owner has waited for every stream that uses it.  device_malloc is hipMalloc,
-// tried again without the kept blocks when memory runs out.
+// tried again without the kept blocks when memory runs out; every allocation goes through one of
+// the two.
 hipError_t pool_malloc(void** p, size_t bytes);
 void pool_free(void* p);
 void pool_trim();

@@ -1128,12 +1128,12 @@ int lbm3d_create_lattice(const lbm3_params* p, int32_t nz, int32_t q, void* hip_
         h->ntiles = (int)tiles.size();
     }
     if (e == hipSuccess) e = alloc_state_pair((size_t)h->g.zbytes * nz, h->buf);
-    if (e == hipSuccess) e = hipMalloc(&h->dtiles, tiles.size() * sizeof(Tile3));
+    if (e == hipSuccess) e = device_malloc((void**)&h->dtiles, tiles.size() * sizeof(Tile3));
     if (e == hipSuccess)
         e = hipMemcpy(h->dtiles, tiles.data(), tiles.size() * sizeof(Tile3), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMalloc(&h->partials, tiles.size() * 8 * sizeof(double));
-    if (e == hipSuccess) e = hipMalloc(&h->staging, (size_t)3 * q * N * sizeof(double));
-    if (e == hipSuccess) e = hipMalloc(&h->rho, (size_t)3 * N * sizeof(double));
+    if (e == hipSuccess) e = device_malloc((void**)&h->partials, tiles.size() * 8 * sizeof(double));
+    if (e == hipSuccess) e = device_malloc((void**)&h->staging, (size_t)3 * q * N * sizeof(double));
+    if (e == hipSuccess) e = device_malloc((void**)&h->rho, (size_t)3 * N * sizeof(double));
     if (e != hipSuccess) {
         rc = hip_fail(e, "hipMalloc (three-dimensional lattice)");
         release3(h);
