@@ -746,7 +746,8 @@ static int ensure_ws(lbm3* h, size_t bytes)
 {
     if (h->adj_ws_bytes >= bytes) return LBM3_OK;
     if (h->adj_ws) {
-        // (the sweep that used it has waited for its streams)
+        if (h->adj_stream) (void)hipStreamSynchronize(h->adj_stream);
+        if (h->adj_stream2) (void)hipStreamSynchronize(h->adj_stream2);
         pool_free(h->adj_ws);
         h->adj_ws = nullptr;
         h->adj_ws_bytes = 0;
@@ -930,7 +931,11 @@ int lbm3_adjoint(lbm3_t* h, const double* drho1_T, double dsigma[3], double* drh
     if (e == hipSuccess) e = hipMemcpyAsync(gT, drho1_T, N * sizeof(double), hipMemcpyHostToDevice, st);
     if (e == hipSuccess)
         e = hipMemcpyAsync(dsf, sf_tiles.data(), sf_tiles.size() * sizeof(Tile), hipMemcpyHostToDevice, st);
-    if (e != hipSuccess) return hip_fail(e, "adjoint set-up");
+    if (e != hipSuccess) {
+        // the copies queued so far read this call's arrays and write the workspace
+        (void)hipStreamSynchronize(st);
+        return hip_fail(e, "adjoint set-up");
+    }
     int cl = 0;
     hipLaunchKernelGGL(k_adj_seed, grid, blk, 0, st, gT, g, lam[cl]);
     // The sweep takes the segments last to first.  Segment s is recomputed from its

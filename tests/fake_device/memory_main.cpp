@@ -164,11 +164,51 @@ static void check_retry()
     }
 }
 
+// Each runtime call of a reverse sweep failing in turn: an error is returned, no work is left on the
+// sweep's streams (its workspace goes to another owner next, and the host arrays of its copies
+// end with the call), and no event or memory is lost.
+static void check_faults()
+{
+    const int nx = 24, ny = 20;
+    std::vector<double> rho((size_t)3 * nx * ny, 0.3), g((size_t)nx * ny, 0.1);
+    double ds[3];
+    int failures = 0;
+    for (int at = 0;; ++at) {
+        lbm3_params p = params(nx, ny);
+        lbm3_t* h = nullptr;
+        CHECK(lbm3_create(&p, nullptr, &h) == LBM3_OK && lbm3_init_fields(h, rho.data(), nullptr) == LBM3_OK &&
+              lbm3_adjoint_record(h, 6, 2) == LBM3_OK);
+        CHECK(lbm3_adjoint(h, g.data(), ds, rho.data()) == LBM3_OK);  // the handle's streams are there
+        CHECK(lbm3_init_fields(h, rho.data(), nullptr) == LBM3_OK && lbm3_adjoint_record(h, 6, 2) == LBM3_OK);
+        const size_t events = device().events.size();
+        device().calls = 0;
+        device().fail_at = at;
+        device().failed = false;
+        const int rc = lbm3_adjoint(h, g.data(), ds, rho.data());
+        const bool failed = device().failed;
+        device().fail_at = -1;
+        CHECK((rc != LBM3_OK) == failed);
+        for (hipStream_t s : device().streams)
+            if (device().pending.count(s)) {
+                std::printf("call %d failed: work left on a stream of the sweep\n", at);
+                ++g_bad;
+            }
+        CHECK(device().events.size() == events);
+        lbm3_destroy(h);
+        tcg::pool_trim();
+        CHECK(device().used == 0 && device().events.empty() && device().streams.empty());
+        if (!failed) break;
+        ++failures;
+    }
+    CHECK(failures > 20);
+}
+
 int main(int argc, char** argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "pool") check_pool();
     else if (what == "retry") check_retry();
+    else if (what == "faults") check_faults();
     else ++g_bad;
     std::printf(g_bad ? "FAILED\n" : "ok\n");
     return g_bad != 0;

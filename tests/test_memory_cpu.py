@@ -41,8 +41,9 @@ def driver(tmp_path_factory):
     return run
 
 
-@pytest.mark.parametrize("what", ["pool", "retry"])
+@pytest.mark.parametrize("what", ["pool", "retry", "faults"])
 def test_memory(driver, what):
     """pool: what the pool of workspaces keeps and gives back; retry: every allocation of the
-    library finds the memory that the pool keeps."""
+    library finds the memory that the pool keeps; faults: each runtime call of a reverse sweep
+    failing in turn leaves no work, event or memory behind."""
     assert driver("memory_main", what).strip() == "ok"
