@@ -180,8 +180,10 @@ int lbm3_derived(const lbm3_params *p, double X[3], double g[3], double nu[3]);
  * the device's resident slots).  Setting a shape keeps one-step launches on the
  * march (a small lattice otherwise takes them on blocks, see
  * lbm3_set_steps_per_launch).  Results do not depend on the shape (bitwise).
+ * clear_tile forgets a shape: the launches are those of a new handle again.
  * get_tile returns the march's shape, with the rows actually used. */
 int lbm3_set_tile(lbm3_t *h, int32_t threads, int32_t rows);
+int lbm3_clear_tile(lbm3_t *h);
 int lbm3_get_tile(const lbm3_t *h, int32_t *threads, int32_t *rows);
 
 /* How many steps one launch advances in lbm3_step: 0 = chosen by size (two on
@@ -241,8 +243,10 @@ int lbm3_state_buffer(const lbm3_t *h, void **dev_ptr, int32_t *elem_bytes, int6
  *   the rows of the instances with nx == side (threads must equal the batch's).
  *   Threads set this way are also the two-step launch's width (at most 256);
  *   otherwise that width is 64, 128 on more than 2^22 nodes in all, or 256 when an
- *   instance is 768 or more wide.
+ *   instance is 768 or more wide.  A shape of either kind keeps one-step launches on
+ *   the march (a small batch otherwise takes them on blocks, as a small lattice does).
  *   Results do not depend on the shape.
+ * lbm3_batch_clear_tile: forgets all shapes: the launches are those of a new batch again.
  * lbm3_batch_set_steps_per_launch: as lbm3_set_steps_per_launch, for the whole
  *   batch (0 = two when the instances hold 2^19 nodes or more in all in FP64, 5 x 2^18
  *   or more in FP32 and FP32 storage); the
@@ -257,6 +261,7 @@ int lbm3_batch_init_fields(lbm3_batch_t *b, int32_t idx, const double *rho, cons
 int lbm3_batch_step(lbm3_batch_t *b, int64_t n);
 int lbm3_batch_observables(lbm3_batch_t *b, int32_t idx, lbm3_obs *out, double *rho_out);
 int lbm3_batch_set_tile(lbm3_batch_t *b, int32_t size_class_side, int32_t threads, int32_t rows);
+int lbm3_batch_clear_tile(lbm3_batch_t *b);
 int lbm3_batch_set_steps_per_launch(lbm3_batch_t *b, int32_t mode);
 int lbm3_batch_get_pair_launch(const lbm3_batch_t *b, int32_t *steps, int32_t *threads, int32_t *rows,
                                int32_t *workgroups);

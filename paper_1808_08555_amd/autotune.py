@@ -1,7 +1,9 @@
 """Measured choice of the fused step's launch shape.
 
 A launch shape is (threads per workgroup, rows per segment); results of the step do not
-depend on it (bitwise), only its speed does.  ``tune_lattice`` times candidate shapes on a
+depend on it (bitwise), only its speed does.  A handle without one takes launches that no
+shape gives (small lattices and batches run on blocks), so the untouched handle is a
+candidate too.  ``tune_lattice`` times candidate shapes on a
 lattice of the requested size, ``tune_batch`` tunes a batch (the workgroup size for the
 whole launch, then the rows of each size class by coordinate descent).  Results are cached
 in a JSON file keyed by GPU architecture, precision and size(s); the path is
@@ -76,17 +78,31 @@ def _cell_fields(nx: int, ny: int):
     return np.ascontiguousarray(np.tile(rho_c, (1,) + reps)[:, :ny, :nx])
 
 
+def _apply_lattice(hit: dict, lattice):
+    if lattice is not None:
+        if hit["default"]:
+            lattice.clear_tile()
+        else:
+            lattice.set_tile(*hit["tile"])
+    return tuple(hit["tile"])
+
+
 def tune_lattice(nx: int, ny: int, precision: str = "fp64", steps: int = 20,
-                 force: bool = False, verbose: bool = False):
-    """Fastest (threads, rows) for an nx x ny lattice; rows 0 means the slot-fitted choice."""
+                 force: bool = False, verbose: bool = False, lattice=None):
+    """Fastest (threads, rows) for an nx x ny lattice; rows 0 means the slot-fitted choice.
+    A ``lattice`` given is set to that shape, or, where a lattice without one is faster (the rule
+    up to about a million nodes), to none."""
     import torch
-    key = f"lattice/{_arch(torch)}/{precision}/{nx}x{ny}"
+    key = f"lattice2/{_arch(torch)}/{precision}/{nx}x{ny}"
     if not force:
         hit = _load().get(key)
         if hit:
-            return tuple(hit["tile"])
+            return _apply_lattice(hit, lattice)
     st = torch.cuda.current_stream()
     L = lbm3.Lattice(nx, ny, precision=precision, stream=st).init(_cell_fields(nx, ny))
+    default_ms = _time(torch, L.step, steps)
+    if verbose:
+        print(f"  {precision} {nx}x{ny} no shape: {default_ms:.4f} ms/step")
     best = None
     for t in THREADS:
         for r in ROWS:
@@ -99,34 +115,45 @@ def tune_lattice(nx: int, ny: int, precision: str = "fp64", steps: int = 20,
             if best is None or ms < best[0]:
                 best = (ms, t, r)
     L.close()
-    _store(key, {"tile": [best[1], best[2]], "ms_per_step": best[0]})
-    return best[1], best[2]
+    hit = {"tile": [best[1], best[2]], "ms_per_step": best[0], "default": default_ms <= best[0],
+           "default_ms_per_step": default_ms}
+    _store(key, hit)
+    return _apply_lattice(hit, lattice)
 
 
 def tune_batch(batch, sizes, precision: str, steps: int = 20, force: bool = False,
                verbose: bool = False):
     """Tunes a batch handle in place: threads for the whole one-step launch, then rows per
     size class, then whether two steps per launch (the two-step pass on its own plan) beat
-    one.  ``sizes`` lists the instances' nx (size classes are its distinct values).  Returns
-    (threads, {side: rows}); the chosen steps per launch is set on the handle
-    (lbm3_batch_get_pair_launch reads it back)."""
+    one, and whether the batch without any of these (blocks or pairs by its size) beats them.
+    ``sizes`` lists the instances' nx (size classes are its distinct values).  Returns
+    (threads, {side: rows}), the fastest shape, also where none is set; the chosen steps per launch
+    is set on the handle (lbm3_batch_get_pair_launch reads it back)."""
     import torch
     classes = sorted(set(int(s) for s in sizes))
-    key = f"batch3/{_arch(torch)}/{precision}/" + ",".join(f"{s}" for s in sorted(int(s) for s in sizes))
+    key = f"batch4/{_arch(torch)}/{precision}/" + ",".join(f"{s}" for s in sorted(int(s) for s in sizes))
     hit = None if force else _load().get(key)
     if hit:
         t = int(hit["threads"])
-        lbm3.lbm3_batch_set_tile(batch, 0, t, 0)
         rows = {int(k): int(v) for k, v in hit["rows"].items()}
-        for s, r in rows.items():
-            lbm3.lbm3_batch_set_tile(batch, s, t, r)
+        if hit["default"]:
+            lbm3.lbm3_batch_clear_tile(batch)
+        else:
+            lbm3.lbm3_batch_set_tile(batch, 0, t, 0)
+            for s, r in rows.items():
+                lbm3.lbm3_batch_set_tile(batch, s, t, r)
         lbm3.lbm3_batch_set_steps_per_launch(batch, int(hit["steps_per_launch"]))
         return t, rows
-    lbm3.lbm3_batch_set_steps_per_launch(batch, 1)
 
     def run(n):
         lbm3.lbm3_batch_step(batch, n)
 
+    lbm3.lbm3_batch_clear_tile(batch)
+    lbm3.lbm3_batch_set_steps_per_launch(batch, 0)
+    default_ms = _time(torch, run, steps)
+    if verbose:
+        print(f"  batch without a shape: {default_ms:.4f} ms/step")
+    lbm3.lbm3_batch_set_steps_per_launch(batch, 1)
     best_t, best_ms = None, None
     for t in THREADS:
         lbm3.lbm3_batch_set_tile(batch, 0, t, 0)
@@ -162,10 +189,15 @@ def tune_batch(batch, sizes, precision: str, steps: int = 20, force: bool = Fals
             print(f"  batch two steps per launch, width {t}: {ms:.4f} ms/step")
         if ms < best_ms:
             best_ms, mode, final_t = ms, 2, t
+    default = default_ms <= best_ms
+    if default:
+        best_ms, mode = default_ms, 0
+        lbm3.lbm3_batch_clear_tile(batch)
+    else:
+        lbm3.lbm3_batch_set_tile(batch, 0, final_t, 0)
+        for s in classes:
+            lbm3.lbm3_batch_set_tile(batch, s, final_t, rows[s])
     lbm3.lbm3_batch_set_steps_per_launch(batch, mode)
-    lbm3.lbm3_batch_set_tile(batch, 0, final_t, 0)
-    for s in classes:
-        lbm3.lbm3_batch_set_tile(batch, s, final_t, rows[s])
-    _store(key, {"threads": final_t, "rows": {str(k): v for k, v in rows.items()},
+    _store(key, {"threads": final_t, "rows": {str(k): v for k, v in rows.items()}, "default": default,
                  "steps_per_launch": mode, "ms_per_step": best_ms})
     return final_t, rows

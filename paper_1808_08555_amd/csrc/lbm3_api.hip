@@ -688,6 +688,26 @@ int lbm3_set_tile(lbm3_t* h, int32_t threads, int32_t rows)
     return rc;
 }
 
+int lbm3_clear_tile(lbm3_t* h)
+{
+    if (!h) {
+        set_error("handle is NULL");
+        return LBM3_EINVAL;
+    }
+    const int old_t = h->threads, old_r = h->rows_request;
+    const bool old_set = h->tile_set;
+    default_tile(h->kp, h->prec, &h->threads, &h->rows_request);
+    h->tile_set = false;
+    int rc = upload_plan(h);
+    if (rc) {
+        h->threads = old_t;
+        h->rows_request = old_r;
+        h->tile_set = old_set;
+        (void)upload_plan(h);
+    }
+    return rc;
+}
+
 int lbm3_get_pair_launch(const lbm3_t* h, int32_t* steps, int32_t* threads, int32_t* workgroups)
 {
     if (!h) {

@@ -31,7 +31,7 @@ struct lbm3_batch {
     void* buf[2] = {nullptr, nullptr};
     int cur = 0;
     int64_t step = 0;
-    int threads = 256;
+    int threads = 256, default_threads = 256;
     bool tile_set = false;  // threads chosen by lbm3_batch_set_tile (then also the two-step width)
     bool pt = false;        // every instance uses the perturbation operator of Eqs. (4)-(5)
     std::map<int, int> rows_by_side;  // rows per segment for instances with nx == side
@@ -319,7 +319,7 @@ int lbm3_batch_create(const lbm3_params* p, int32_t count, void* hip_stream, lbm
         total += (b->inst[i].kp.span + 255) / 256 * 256;
         max_side = std::max(max_side, std::max(p[i].nx, p[i].ny));
     }
-    b->threads = max_side >= 2000 ? 512 : (max_side >= 500 ? 256 : (max_side >= 124 ? 128 : 64));
+    b->threads = b->default_threads = max_side >= 2000 ? 512 : (max_side >= 500 ? 256 : (max_side >= 124 ? 128 : 64));
     hipError_t e = hipSuccess;
     if (hip_stream) {
         b->stream = (hipStream_t)hip_stream;
@@ -377,6 +377,18 @@ int lbm3_batch_set_tile(lbm3_batch_t* b, int32_t side, int32_t threads, int32_t 
         }
         b->rows_by_side[side] = rows;
     }
+    return batch_plan(b);
+}
+
+int lbm3_batch_clear_tile(lbm3_batch_t* b)
+{
+    if (!b) {
+        set_error("batch is NULL");
+        return LBM3_EINVAL;
+    }
+    b->threads = b->default_threads;
+    b->tile_set = false;
+    b->rows_by_side.clear();
     return batch_plan(b);
 }
 

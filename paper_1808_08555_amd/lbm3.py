@@ -92,6 +92,7 @@ def lib():
             "lbm3_last_error": (ctypes.c_char_p, []),
             "lbm3_derived": (I, [P, _DP, _DP, _DP]),
             "lbm3_set_tile": (I, [H, ctypes.c_int32, ctypes.c_int32]),
+            "lbm3_clear_tile": (I, [H]),
             "lbm3_get_tile": (I, [H, ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int32)]),
             "lbm3_set_steps_per_launch": (I, [H, ctypes.c_int32]),
             "lbm3_get_pair_launch": (I, [H, ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int32),
@@ -104,6 +105,7 @@ def lib():
             "lbm3_batch_step": (I, [H, ctypes.c_int64]),
             "lbm3_batch_observables": (I, [H, ctypes.c_int32, ctypes.POINTER(lbm3_obs), _DP]),
             "lbm3_batch_set_tile": (I, [H, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32]),
+            "lbm3_batch_clear_tile": (I, [H]),
             "lbm3_batch_set_steps_per_launch": (I, [H, ctypes.c_int32]),
             "lbm3_batch_get_pair_launch": (I, [H] + [ctypes.POINTER(ctypes.c_int32)] * 4),
             "lbm3_batch_destroy": (I, [H]),
@@ -239,6 +241,10 @@ def lbm3_set_tile(h, threads: int, rows: int):
     _check(lib().lbm3_set_tile(h, int(threads), int(rows)), "lbm3_set_tile")
 
 
+def lbm3_clear_tile(h):
+    _check(lib().lbm3_clear_tile(h), "lbm3_clear_tile")
+
+
 def lbm3_set_steps_per_launch(h, mode: int):
     """0 = by lattice size, 1 = one step per launch, 2 = two steps per launch where possible."""
     _check(lib().lbm3_set_steps_per_launch(h, int(mode)), "lbm3_set_steps_per_launch")
@@ -311,6 +317,10 @@ def lbm3_batch_observables(b, idx: int, nx: int, ny: int, want_rho: bool = False
 
 def lbm3_batch_set_tile(b, side: int, threads: int, rows: int):
     _check(lib().lbm3_batch_set_tile(b, int(side), int(threads), int(rows)), "lbm3_batch_set_tile")
+
+
+def lbm3_batch_clear_tile(b):
+    _check(lib().lbm3_batch_clear_tile(b), "lbm3_batch_clear_tile")
 
 
 def lbm3_batch_set_steps_per_launch(b, mode: int):
@@ -392,6 +402,10 @@ class Lattice:
 
     def set_tile(self, threads: int, rows: int):
         lbm3_set_tile(self.h, threads, rows)
+        return self
+
+    def clear_tile(self):
+        lbm3_clear_tile(self.h)
         return self
 
     def tile(self):

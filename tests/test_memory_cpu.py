@@ -47,3 +47,7 @@ def test_memory(driver, what):
     library finds the memory that the pool keeps; faults: each runtime call of a reverse sweep
     failing in turn leaves no work, event or memory behind."""
     assert driver("memory_main", what).strip() == "ok"
+
+
+def test_a_cleared_shape_brings_the_default_launches_back(driver):
+    assert driver("dispatch_main", "clear").strip() == "ok"
