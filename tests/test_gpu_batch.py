@@ -77,6 +77,26 @@ def test_batch_default_launch_equals_plain_lattices_bitwise(precision, sides, st
     lbm3.lbm3_batch_destroy(b)
 
 
+@pytest.mark.parametrize("precision,sides,steps", [("fp64", [61, 1, 97, 130] * 9, 1), ("fp64", [300, 130, 28] * 7, 2),
+                                                   ("fp32", [45, 64, 29] * 20, 1), ("fp32_storage", [70, 33] * 25, 1)])
+def test_batch_default_launch_equals_plain_lattices_at_every_instance(precision, sides, steps):
+    """Batches of many instances in their default launch (blocks, and pairs of steps), each
+    instance with an input of its own: 23 steps, all of them against the lattice stepped alone, bit
+    for bit."""
+    ws = [inputs.Workload("rand", n, n + 3, (0.011, 0.013, 0.017), (0.7, 1.0, 1.3),
+                          rho=inputs.random_mixture(n, n + 3, 90 + i, tiny_fraction=0.0)) for i, n in enumerate(sides)]
+    b = _make_batch(ws, precision)
+    assert lbm3.lbm3_batch_get_pair_launch(b)[0] == steps
+    lbm3.lbm3_batch_step(b, 23)
+    for i, w in enumerate(ws):
+        _, rho = _batch_state(b, i, w)
+        L = lbm3.Lattice(w.nx, w.ny, w.sigma, w.tau, w.rho0, w.beta0, precision).init(w.rho)
+        ref = L.set_steps_per_launch(1).step(23).densities()
+        L.close()
+        assert np.array_equal(rho, ref), (i, w.nx)
+    lbm3.lbm3_batch_destroy(b)
+
+
 @pytest.mark.parametrize("precision", ["fp64", "fp32", "fp32_storage"])
 @pytest.mark.parametrize("threads", [0, 64, 256])
 def test_batch_two_step_pass_matches_plain_step_bitwise(precision, threads):

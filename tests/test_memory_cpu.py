@@ -15,6 +15,11 @@ HERE = os.path.join(ROOT, "tests", "fake_device")
 PKG = os.path.join(ROOT, "paper_1808_08555_amd")
 
 
+def _check(cmd):
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-3000:]
+
+
 @pytest.fixture(scope="module")
 def driver(tmp_path_factory):
     """Builds a driver (its main file's name) and returns a function that runs it."""
@@ -28,11 +33,16 @@ def driver(tmp_path_factory):
     def run(main, *args):
         if main not in built:
             exe = str(tmp_path_factory.mktemp("fake") / main)
-            r = subprocess.run(["g++", "-std=c++17", "-O1", "-I/opt/rocm/include", "-I", os.path.join(ROOT, "include"),
-                                "-I", HERE, os.path.join(HERE, main + ".cpp"), os.path.join(HERE, "fake_hip.cpp"),
-                                os.path.join(PKG, "liblbm3.so"), "-Wl,-rpath," + PKG, "-Wl,-rpath-link,/opt/rocm/lib",
-                                "-rdynamic", "-o", exe], capture_output=True, text=True)
-            assert r.returncode == 0, r.stderr[-3000:]
+            inc = ["-I/opt/rocm/include", "-I", os.path.join(ROOT, "include"), "-I", os.path.join(PKG, "csrc"), "-I", HERE]
+            src = os.path.join(HERE, main + ".cpp")
+            if main == "grids_main":  # includes a header with device functions: only their host side is compiled
+                obj = exe + ".o"
+                _check(["/opt/rocm/bin/hipcc", "-x", "hip", "--offload-host-only", "-fPIC", "-std=c++17", "-O1", *inc, "-c", src,
+                        "-o", obj])
+                src = obj
+            _check(["g++", "-std=c++17", "-O1", *inc, src, os.path.join(HERE, "fake_hip.cpp"),
+                    os.path.join(PKG, "liblbm3.so"), "-Wl,-rpath," + PKG, "-Wl,-rpath-link,/opt/rocm/lib", "-rdynamic",
+                    "-o", exe])
             built[main] = exe
         r = subprocess.run([built[main], *args], capture_output=True, text=True, timeout=120)
         assert r.returncode == 0, r.stdout[-3000:] + r.stderr[-3000:]
@@ -51,3 +61,21 @@ def test_memory(driver, what):
 
 def test_a_cleared_shape_brings_the_default_launches_back(driver):
     assert driver("dispatch_main", "clear").strip() == "ok"
+
+
+def test_block_grids_cover_the_lattice(driver):
+    """The grids of the one-step and two-step blocks, for lattices around the sides of a block and
+    devices of different numbers of compute units."""
+    assert driver("grids_main").strip() == "ok"
+
+
+@pytest.mark.parametrize("q", [19, 27])
+@pytest.mark.parametrize("precision", [0, 1, 2])
+@pytest.mark.parametrize("cell,times", [((45, 19, 8), (5, 5, 1)), ((28, 24, 9), (8, 4, 1)), ((31, 5, 60), (3, 7, 3))])
+def test_a_box_and_its_repetition_take_different_tiles(driver, cell, times, precision, q):
+    """The pairs of boxes that tests/test_gpu_d3.py compares bit for bit (small and large tiles) do
+    take different tiles on 256 compute units."""
+    large = 24 if precision == 2 else 16
+    rows = [int(driver("dispatch_main", "box", *(str(c * t) for c, t in zip(cell, n)), str(q), str(precision)))
+            for n in ((1, 1, 1), times)]
+    assert rows == [8, large]
