@@ -59,7 +59,6 @@ struct AdjWS {
 
 struct Geo {
     int nx, ny;
-    int64_t plane, pitch;
     double sigma[3], g[3], beta0, inv_nu[3], cfac[3], guard;
 };
 
@@ -665,9 +664,11 @@ int sf_occupancy(int nt)
 // per step (blocks of kAdjBlockX x kAdjBlockY lanes); up to kSfBlockMaxNodes k_adj_local and
 // k_adj_sf_block (blocks of kSfBlockX x kSfBlockY lanes); above, or where the forward's
 // one-step launches keep to the march, k_adj_local and the march.
-// Measured (us per reverse step, fused and two kernels): 11.3 and 16.0 at 256^2, 22.5 and 26.7
-// at 360^2, 44.9 and 41.7 at 512^2, 73.8 and 71.7 at 720^2; the fused step runs A1 on the halo
-// ring too, which costs more than the launch it saves once the lattice fills the device.
+// Measured (us per taped forward step and reverse step, the latter fused and in two kernels): 20.0
+// and 21.6 at 128^2, 26.9 and 32.1 at 256^2, 41.2 and 45.8 at 360^2, 56.8 and 57.3 at 400 x 410, 61.2
+// and 63.0 at 450^2, 76.5 and 74.2 at 512^2, 134 and 130 at 720^2; the fused step runs A1 on the
+// halo ring too, which costs more than the launch it saves once the lattice fills the device.  The
+// lines cross at about 230 000 nodes, 3% or less apart from 2^17 on.
 constexpr int kSfBlockX = 32, kSfBlockY = 8;
 constexpr int kAdjBlockX = 32, kAdjBlockY = 16;
 constexpr int64_t kAdjFusedMaxNodes = (int64_t)1 << 17;
@@ -691,8 +692,6 @@ Geo geo_of(const KParams& kp)
     Geo g;
     g.nx = kp.nx;
     g.ny = kp.ny;
-    g.plane = kp.plane;
-    g.pitch = kp.pitch;
     for (int p = 0; p < 3; ++p) {
         g.sigma[p] = kp.sigma[p];
         g.g[p] = kp.g[p];

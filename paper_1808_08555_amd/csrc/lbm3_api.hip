@@ -239,9 +239,9 @@ int check_rho_fields(const double* rho, const double* u, int64_t n)
 // two-step pass exists, its own with the wider halo) and uploads them with the one-entry
 // instance table.  The two-step pass exists for every precision (64 to 256 threads); rows
 // requested explicitly apply to both lists.
-// Lattices up to this many nodes take their single steps on the block kernel.  The line is where
-// the two state buffers outgrow the 256 MB last-level cache: 2^20 nodes in FP64, 2^21 with the
-// factored state in floats.  Below it the block step reads what the step before left in that
+// Lattices up to this many nodes take their single steps on the block kernel: 2^20 in FP64 and
+// 7 x 2^18 with the state in floats, whose two factored buffers take 268 and 235 MB, what the 256 MiB
+// last-level cache holds.  Up to there the block step reads what the step before left in that
 // cache; beyond, its time per node rises by half (FP64: 57.6 us at 1024^2, 75.9 us at 1200 x
 // 1000; FP32: 34.9 us at 1300 x 1200, 70.8 us at 1448^2).
 static int64_t block_max_nodes(Prec prec) { return prec == Prec::F64 ? (int64_t)1 << 20 : (int64_t)7 << 18; }

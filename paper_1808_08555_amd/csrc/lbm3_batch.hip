@@ -2,8 +2,7 @@
 // one precision) in one device arena.  One launch of the fused step covers the tiles of
 // every instance (a flat tile list, dealt to the XCDs in contiguous runs); a captured
 // hipGraph of kGraphSteps such launches advances all instances with one graph launch.
-// Instances hold the factored state after their first step (FP64 and FP32; FP32 storage
-// keeps the 27 populations); a step that finds some instances freshly initialised
+// Instances hold the factored state after their first step; a step that finds some instances freshly initialised
 // (27-population format) runs as two launches over the same list, each skipping the
 // instances of the other format.  Once every instance holds the factored state, pairs of
 // steps can run as one launch of the two-step pass over its own tile list (six-column
@@ -17,7 +16,12 @@
 #include "lbm3_handle.h"
 
 namespace {
-constexpr int64_t kBatchBlockNodes = (int64_t)1 << 21;  // single steps on blocks up to this many
+// Single steps of batches up to this many nodes run on blocks (above the pairs' line only where one
+// step per launch was asked for).  Us per step, blocks and the march at its faster width: FP32
+// 0.98 M nodes 29.7 and 37.2, 1.62 M 43.8 and 53.3, 2.06 M 68.0 and 66.8, 2.95 M 105 and 97; FP32
+// storage 45.2 and 58.4, 66.6 and 81.6, 87.8 and 99.8, 134 and 140; FP64 within 4% either way from
+// 0.98 to 2.06 M.
+constexpr int64_t kBatchBlockNodes = (int64_t)1 << 21;
 constexpr int kGraphSteps = 20;  // steps per captured graph (a multiple of 4: parity kept with pairs)
 }
 

@@ -122,7 +122,7 @@ void free_state_pair(void* buf[2]);
 int auto_rows(int nx, int ny, int threads, int slots, int elem_bytes, int halo = 3);
 int device_cus();
 int device_slots(Prec prec, int threads);
-// resident slots of the two-step pass (0 where it does not exist: FP32 storage, 512 threads)
+// resident slots of the two-step pass (0 where it does not exist: 512 threads)
 int device_slots_pair(Prec prec, int threads);
 
 size_t elem_bytes(Prec p);

@@ -266,36 +266,28 @@ __device__ __forceinline__ void collide_recolour(const C (&f)[9], const C (&rk)[
 // source row by lane (fields 0-2 c_k, 3-8 V_k), read at lane t - e_x,i.  D0 = partial sums of
 // row s (directions with e_y = +1 and 0 received), D1 = those of row s + 1 (e_y = +1
 // received); direction groups by e_y: +1 {2, 5, 6}, 0 {0, 1, 3}, -1 {4, 7, 8}.  Completes row
-// s - 1 into r0, f0.  With PULL_ONCE the nine fields of the three source lanes t - 1, t, t + 1
+// s - 1 into r0, f0.  The nine fields of the three source lanes t - 1, t, t + 1
 // are read from LDS once (27 reads; each group pulls one direction from each of those lanes,
 // so reading per direction reads every field three times): measured +7% for the FP64
 // two-step pass, +11% for FP32, +13% for the FP64 step at 256^2, -3% for the FP64 one-step
 // kernel at 4096^2.  (The scheduling barriers keep the arithmetic of one group from being
 // interleaved with the next, which would hold the pulled values of all groups in registers
 // at once.)
-template <typename C, int NT, bool PULL_ONCE = true, typename FD>
+template <typename C, int NT, typename FD>
 __device__ __forceinline__ void pull_row(FD f_dag, const C (*X)[NT], int t, C (&d0r)[3], C (&d0f)[6],
                                          C (&d1r)[3], C (&d1f)[3], C (&r0)[3], C (&f0)[9])
 {
     // by e_x + 1: fields of lane t + 1 (e_x = -1), t (0), t - 1 (+1)
     C xs[3][9];
-    if constexpr (PULL_ONCE) {
 #pragma unroll
-        for (int e = 0; e < 3; ++e)
+    for (int e = 0; e < 3; ++e)
 #pragma unroll
-            for (int q = 0; q < 9; ++q) xs[e][q] = X[q][t + 1 - e];
-    }
+        for (int q = 0; q < 9; ++q) xs[e][q] = X[q][t + 1 - e];
     auto pull = [&](int i, C (&fk)[3]) {
         const C fdi = f_dag(i);
-        if constexpr (PULL_ONCE) {
-            const C* xl = xs[EX[i] + 1];
+        const C* xl = xs[EX[i] + 1];
 #pragma unroll
-            for (int k = 0; k < 3; ++k) fk[k] = recon<C>(xl[k], fdi, xl[3 + 2 * k], xl[4 + 2 * k], i);
-        } else {
-            const int l = t - EX[i];
-#pragma unroll
-            for (int k = 0; k < 3; ++k) fk[k] = recon<C>(X[k][l], fdi, X[3 + 2 * k][l], X[4 + 2 * k][l], i);
-        }
+        for (int k = 0; k < 3; ++k) fk[k] = recon<C>(xl[k], fdi, xl[3 + 2 * k], xl[4 + 2 * k], i);
     };
     auto group = [&](int a, int b, int c, C (&g)[3], C& ta, C& tb, C& tc) {
         C fa[3], fb[3], fc[3];

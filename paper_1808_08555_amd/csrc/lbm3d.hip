@@ -954,8 +954,10 @@ static std::vector<Tile3> plan3(const Geo3& g, const int (&slots)[2], Prec prec,
     // Where no tile has more than TX - 6 columns the lanes start one column earlier: they then
     // cover every column whose c_k, V_k stage 1 reads, and the ring of nodes around the lanes'
     // has no sides, whose nodes lie in a cache line each (D3Q19 FP64 128^3 325 -> 304 us, FP32
-    // storage 226 -> 214, 127^3 231 -> 216; FP32 127^3 188 -> 175, 96^3 78 -> 75, but 128^3 180 ->
-    // 192).  Tiles of both kinds side by side were slower (160^3, 27 and 26 columns: 384 -> 400).
+    // storage 226 -> 214, 127^3 231 -> 216; FP32 D3Q19 52^3 44 -> 35, 96^3 78 -> 74, 127^3 187 -> 175,
+    // 144^3 259 -> 241, D3Q27 127^3 239 -> 230, slower among 13 sides from 40 to 160 only at 128^3:
+    // 180 -> 193, D3Q27 238 -> 249).  Tiles of both kinds side by side were slower (160^3, 27 and 26
+    // columns: 384 -> 400).
     const int sx = (g.nx + ntx - 1) / ntx <= TX - 6 ? 3 : 2;
     std::vector<Tile3> L;
     L.reserve((size_t)ntx * nty * nseg);
