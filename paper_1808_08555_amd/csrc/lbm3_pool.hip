@@ -7,7 +7,8 @@
 // kernels run 5 and 8 ms.
 //
 // Blocks of 1 MiB or more that a handle gives back are kept, per device, up to 1/32 of the
-// device's memory in all (9 GB of 288); the oldest go back to the driver beyond that, all of
+// device's memory in all (9 GB of 288; a larger one is given back at once, and a run that needs
+// one, such as 1100 x 900 with 100 steps a segment, pays for it each time); the oldest go back to the driver beyond that, all of
 // them when an allocation of the library finds no memory, and on lbm3_release_cached.  A block
 // has one owner at a time.  The owner has waited for its streams before it gives a block back:
 // only buffers that never leave the library go through here (a lattice's state, which its

@@ -197,11 +197,11 @@ __device__ __forceinline__ void collide_recolour(const C (&f)[9], const C (&rk)[
     //   f_eq_i / tau + Phi_i = w_i [rho/tau + b + E (P/2 + H) + P + H],
     //   b = -(1.5 (rho/tau) u.u + 3 (1 - 1/(2 tau)) u.F),
     // whose last two terms change sign with e, and E, P/2 + H and P + H of the diagonals are
-    // sums of those of the axes: 59 operations for the nine directions, 92 one by one.  (The
-    // steps are bound by the vector instructions they issue; this form, 1/rho held from the
-    // densities and the shorter forms of recip, rsqrt_nr, the stress and the recolouring took
-    // the two-step pass from 488 + 511 to 417 + 430 of them per row in FP64, 449 to 424 us per
-    // step at 4096^2, and from 921 to 822 in FP32, 286 to 269 us.)  All that is small against
+    // sums of those of the axes: 59 operations for the nine directions, 92 one by one.  (This
+    // form, 1/rho held from the densities and the shorter forms of recip, rsqrt_nr, the stress and
+    // the recolouring took the two-step pass from 488 + 511 to 417 + 430 vector instructions per row in
+    // FP64, 449 to 424 us per step at 4096^2, and from 921 to 822 in FP32, 286 to 269 us; the SIMDs
+    // issue them in 49% of the cycles in FP64 and 68% in FP32.)  All that is small against
     // rho/tau is summed before it meets it: rounded at the scale of rho/tau one after another,
     // terms below half its last place are lost in the same direction at every node, and the
     // mass of an FP32 run drifted twice as fast (1.6e-6 in 200 steps against 0.8e-6).

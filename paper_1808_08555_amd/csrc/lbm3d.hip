@@ -335,17 +335,19 @@ __device__ __forceinline__ void collide3(C rho, C itau, const C (&ft)[Q], const 
 // Global loads are issued up to an iteration before their use, into the registers that their
 // previous values have just left (D3Q27 in FP64 issues its f_dag_i after stage 2, so that
 // they are not in registers beside stage 2's: no spills, 735 -> 462 us at 128^3).
-// What bounds it: memory.  A D3Q19 FP64 step at 128^3 takes 142 us without its loads and
+// What bounds it: memory, bytes and path.  A D3Q19 FP64 step at 128^3 moves 1.41 GB, 1.50 times what
+// it needs, at 4.6 TB/s, 74% of a large copy's rate.  It takes 142 us without its loads and
 // stores; the stores alone add 109 us, the loads' path through L1 most of the rest (about 15
 // cycles per wave instruction, whatever its width).  Measured against the march over 3 Q stored
 // populations that it replaced, us per step at 128^3 (FP64 / FP32 storage / FP32): D3Q19 723 /
-// 413 / 338 -> 304 / 214 / 192, D3Q27 1159 / 667 / 460 -> 427 / 272 / 251; 48^3 D3Q19 FP64 63 -> 37 (35 with the
+// 413 / 338 -> 310 / 222 / 193, D3Q27 1159 / 667 / 460 -> 430 / 277 / 250; 48^3 D3Q19 FP64 63 -> 37 (34 with the
 // small tiles).
 // Non-temporal stores made it 1-15% slower, non-temporal loads 10-20%.
 // The arithmetic of every node has a fixed order, so the result does not depend on the tile
 // shape.  RMS error of the densities against that of the march over 3 Q populations, mean ratio
 // over 48 drawn boxes after 20, 100 and 300 steps: FP32 D3Q19 0.29, 0.89 and 0.97, D3Q27 0.17, 0.56
-// and 0.79; FP64 (random mixture and spheres, against 80 bits) 0.5 to 1.04 up to 100 steps.  With FP64 arithmetic two waves per SIMD fit in registers (512 lanes of 256), with
+// and 0.79; FP64 (random mixture and spheres, against 80 bits) 0.5 to 1.04 up to 100 steps.
+// With FP64 arithmetic two waves per SIMD fit in registers (512 lanes of 256), with
 // FP32 three (768 lanes): 336 owned columns of 512 lanes, 560 of 768.
 // Small boxes take tiles of 8 rows of lanes (see plan3).
 template <int ROWS>
