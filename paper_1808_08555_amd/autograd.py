@@ -66,7 +66,9 @@ class TernaryRun(torch.autograd.Function):
 def ternary_run(sigma: torch.Tensor, rho0: torch.Tensor, steps: int, ckpt_every: int | None = None,
                 tau=(1.0, 1.0, 1.0), rho_pure=(1.0, 1.0, 1.0), beta0: float = 0.7) -> torch.Tensor:
     """rho_1(x, T) after ``steps`` FP64 steps; differentiable in ``sigma`` and ``rho0``.
-    ``ckpt_every`` must divide ``steps`` (default: the largest divisor not above 100)."""
+    ``ckpt_every`` must divide ``steps`` (default: the largest divisor not above 100).  The device
+    workspaces of a run are kept for the next one, at most 1/32 of the device's memory;
+    ``lbm3.lbm3_release_cached()`` gives them back (to torch's allocator, for instance)."""
     steps = int(steps)
     if ckpt_every is None:
         ckpt_every = max(d for d in range(1, min(steps, 100) + 1) if steps % d == 0) if steps else 1
